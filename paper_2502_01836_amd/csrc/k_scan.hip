@@ -35,6 +35,7 @@
 #include "device_util.h"
 #include "kernels.h"
 #include "scan_bounds.h"
+#include "wave_sort.h"
 
 namespace leafi {
 
@@ -147,15 +148,44 @@ __device__ inline TileInfo decode_tile(int t, const StoreView &s, const RoundBuf
 // Up to this many kept keys, a list is cut by selection instead of a sort.
 constexpr int kListSelectMax = 16;
 
+// The c keys of a list sorted in the wavefront's registers (kMax past them)
+// and put back at its head, the first `keep` of them.
+template <int L, int R, typename K>
+__device__ __forceinline__ void sort_list_regs(K *lst, int c, int keep, int lane) {
+  K v[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) v[r] = lane + kWave * r < c ? lst[lane + kWave * r] : key_max<K>();
+  wave_lds_sync();  // every lane has read the list before its head is rewritten
+  wave_sort_regs<L>(v, lane);
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (lane * R + r < keep) lst[lane * R + r] = v[r];
+}
+
+// Sorts the c keys of a list, of which the first `keep` are wanted: in
+// registers, by the smallest power of two of keys that holds it; a list of
+// over 512 keys (only more than 128 wanted keys bring one) in LDS.  One copy
+// of the networks per kernel: inlined at each of its uses, they push the scan
+// loop out of the instruction cache.
+template <typename K>
+__device__ __noinline__ void sort_list(K *lst, int c, int keep, int lane) {
+  if (c <= 16) sort_list_regs<16, 1>(lst, c, keep, lane);
+  else if (c <= kWave) sort_list_regs<kWave, 1>(lst, c, keep, lane);
+  else if (c <= 2 * kWave) sort_list_regs<kWave, 2>(lst, c, keep, lane);
+  else if (c <= 4 * kWave) sort_list_regs<kWave, 4>(lst, c, keep, lane);
+  else if (c <= 8 * kWave) sort_list_regs<kWave, 8>(lst, c, keep, lane);
+  else wave_sort_keys_n(lst, c, lane);
+}
+
 // Keep the kprime best keys of list j, in ascending order at its head, and
 // refresh the threshold.  Few wanted (kprime <= kListSelectMax): kprime
 // rounds of a wavefront minimum over the keys above the previous round's
-// (the keys of one list are distinct: one per row); otherwise a bitonic sort.
+// (the keys of one list are distinct: one per row); otherwise a sort.
 template <typename K>
-__device__ inline void compact_list(K *keys, int *cnt, K *thr, int j, int cap, int kprime, int lane) {
+__device__ __forceinline__ void compact_list(K *keys, int *cnt, K *thr, int j, int cap, int kprime, int lane) {
   constexpr K kMax = key_max<K>();
   K *lst = keys + static_cast<int64_t>(j) * (cap + 1);
-  int c = cnt[j];
+  const int c = __builtin_amdgcn_readfirstlane(cnt[j]);
   if (kprime <= kListSelectMax) {
     K prev = 0, mine = kMax;  // lane r keeps the r-th smallest
     int keep = 0;
@@ -190,8 +220,9 @@ __device__ inline void compact_list(K *keys, int *cnt, K *thr, int j, int cap, i
     wave_lds_sync();
     return;
   }
-  wave_sort_keys_n(lst, c, lane);  // in place: the list's capacity need not be a power of two
-  int keep = c < kprime ? c : kprime;
+  const int keep = c < kprime ? c : kprime;
+  if (c > 1) sort_list(lst, c, keep, lane);
+  wave_lds_sync();
   if (lane == 0) {
     cnt[j] = keep;
     if (keep == kprime) thr[j] = lst[kprime - 1];  // else the list is not full: keep the threshold
