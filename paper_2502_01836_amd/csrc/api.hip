@@ -424,7 +424,7 @@ int64_t scan_round(leafi_index *ix, int64_t nq, bool bf16, int kprime, int kmax,
   int64_t ib = items >= 0 ? items : std::max<int64_t>(items_bound, 1);
   // one wavefront per item, a persistent grid of what is resident at once
   // (three four-wavefront work-groups per CU)
-  int grid_r = static_cast<int>(std::min<int64_t>(ib, static_cast<int64_t>(ix->num_cus) * (ro->small ? 1 : 12)));
+  int grid_r = static_cast<int>(std::min<int64_t>(ib, static_cast<int64_t>(ix->num_cus) * (ro->small ? 1 : 16)));
   // a search round's rerank skips candidates that cannot enter their query's
   // top k; not in a round of one leaf per query, whose bound comes from that
   // one item's own keys: it certifies no item and trims few candidates
@@ -433,7 +433,7 @@ int64_t scan_round(leafi_index *ix, int64_t nq, bool bf16, int kprime, int kmax,
     launch_query_bound(s, q, b, nq, mq, kprime, kmax, ix->max_chunks_for(chunk), ix->leaf_eps_max, w.cand.get(),
                        w.qbound.get(), st);
   }
-  launch_item_rerank(s, q, b, mq, kprime, kmax, bf16, w.cand.get(), grid_r, ix->max_chunks_for(chunk), st,
+  launch_item_rerank(s, q, b, mq, kprime, kmax, bf16, w.cand.get(), grid_r, st,
                      bound ? w.qbound.get() : nullptr);
   return items;
 }

@@ -14,6 +14,7 @@
 #include "device_util.h"
 #include "kernels.h"
 #include "scan_bounds.h"
+#include "wave_sort.h"
 
 namespace leafi {
 
@@ -276,18 +277,56 @@ __global__ void __launch_bounds__(256) k_query_bound(StoreView s, QueryView qv, 
   }
 }
 
+// Adds (q_t - x_t)^2 of four elements to the FP32 and the FP64 sum.
+__device__ __forceinline__ void add_diff4(const float4 &a, const float4 &x, float &p, double &pd) {
+  const float d0 = a.x - x.x, d1 = a.y - x.y, d2 = a.z - x.z, d3 = a.w - x.w;
+  p = fmaf(d0, d0, p);
+  p = fmaf(d1, d1, p);
+  p = fmaf(d2, d2, p);
+  p = fmaf(d3, d3, p);
+  const double e0 = static_cast<double>(a.x) - static_cast<double>(x.x);
+  const double e1 = static_cast<double>(a.y) - static_cast<double>(x.y);
+  const double e2 = static_cast<double>(a.z) - static_cast<double>(x.z);
+  const double e3 = static_cast<double>(a.w) - static_cast<double>(x.w);
+  pd = fma(e0, e0, pd);
+  pd = fma(e1, e1, pd);
+  pd = fma(e2, e2, pd);
+  pd = fma(e3, e3, pd);
+}
+
+// Sorts of the first n of 64 R keys by as few lanes as hold them.
+template <int R, typename K>
+__device__ __forceinline__ void sort_first(K (&v)[R], int n, int lane) {
+  if (n <= 16 * R) wave_sort_regs<16>(v, lane);
+  else wave_sort_regs<kWave>(v, lane);
+}
+
+// LDS of one wavefront of the rerank: the item's best keys (later its FP32
+// keys), and their FP64 distances.
+__host__ __device__ constexpr size_t rerank_slice_bytes(int R) { return static_cast<size_t>(64 * R) * 16; }
+
+// One wavefront per item, up to 64 R candidates each (R registers per lane):
+//  1. the item's kp best keys: its chunk lists are sorted, so each is merged
+//     in registers into the best 64 R so far (7 to 9 comparator stages per
+//     list), eight registers' worth of lists in flight together; in a search
+//     round a list whose smallest key is beyond the query's bound U is
+//     skipped whole;
+//  2. the candidates that can still enter the query's top k (the keys are
+//     ascending, so a prefix) have their rows read once, FP32 and FP64 sums
+//     together, two groups of candidates in flight;
+//  3. FP32 keys sorted for the k-th, whose error band names the exact
+//     candidates; those sorted by (FP64 distance, row).
+// Bound by latency (an item's loads are a chain of three), so the wavefront's
+// LDS is kept to 16 bytes per candidate and the sorts off it.
+template <int R>
 __global__ void __launch_bounds__(256, 3) k_item_rerank(StoreView s, QueryView qv, RoundBufs b, int mq, int kprime,
-                                                     int kmax, int bf16, int PB, int slice_u64,
-                                                     const uint64_t *__restrict__ cand,
-                                                     const float *__restrict__ qbound) {
-  extern __shared__ uint64_t smem[];
-  // blockDim / 64 wavefronts per work-group, one item each, own LDS slice
+                                                        int kmax, int bf16, const uint64_t *__restrict__ cand,
+                                                        const float *__restrict__ qbound) {
+  constexpr int kCap = kWave * R;
+  __shared__ uint64_t smem[4 * 2 * kCap];
   const int wave = threadIdx.x / kWave, wpb = blockDim.x / kWave;
-  uint64_t *buf = smem + static_cast<size_t>(wave) * slice_u64;        // [PB]
-  uint64_t *k32 = buf + PB;                                             // [PK]
-  const int PK = pow2_at_least(kprime < 2 ? 2 : kprime);
-  double *d64 = reinterpret_cast<double *>(buf + PB + PK);             // [PK]
-  uint32_t *r64 = reinterpret_cast<uint32_t *>(d64 + PK);              // [PK]
+  uint64_t *keys = smem + static_cast<size_t>(wave) * 2 * kCap;  // [kCap]
+  double *d64 = reinterpret_cast<double *>(keys + kCap);         // [kCap]
   const int lane = threadIdx.x & (kWave - 1);
   const int m = s.m;
   const int n_items = static_cast<int>(b.ctl[kCtlItems]);
@@ -302,7 +341,7 @@ __global__ void __launch_bounds__(256, 3) k_item_rerank(StoreView s, QueryView q
   // a search round reranks only the items k_query_bound listed
   const int n_work = qbound ? static_cast<int>(b.ctl[kCtlLive]) : n_items;
   for (int w_i = blockIdx.x * wpb + wave; w_i < n_work; w_i += gridDim.x * wpb) {
-    const int item = qbound ? b.item_live[w_i] : w_i;
+    const int item = __builtin_amdgcn_readfirstlane(qbound ? b.item_live[w_i] : w_i);
     const int L = b.item_leaf[item];
     const int64_t q = b.item_q[item];
     // everything else the item needs from memory, requested together
@@ -310,6 +349,8 @@ __global__ void __launch_bounds__(256, 3) k_item_rerank(StoreView s, QueryView q
     const int ist0 = b.leaf_istart[L], ist1 = b.leaf_istart[L + 1];
     const int64_t off0 = s.leaf_off[L], off1 = s.leaf_off[L + 1];
     const float tau_q = b.tau[q], qn_q = qv.qn16[q], qe_q = qv.qeps[q], le_L = s.leaf_eps[L];
+    const float U = qbound ? qbound[q] : __builtin_inff();
+    const int64_t t0 = b.tile_start[L];
     const int pos = item - ist0;
     const int g = pos / mq, j = pos - (pos / mq) * mq;
     const int C = static_cast<int>((off1 - off0 + b.chunk - 1) / b.chunk);
@@ -317,229 +358,181 @@ __global__ void __launch_bounds__(256, 3) k_item_rerank(StoreView s, QueryView q
     // the query's own candidate count (its lists hold kp keys in kprime slots)
     const int kp = item_kprime(b.kp_query, kprime, k, bf16 != 0);
     const int PKi = pow2_at_least(kp < 2 ? 2 : kp);
-    int n = C * kprime;
-    uint64_t kth_override = 0;  // nonzero: the certificate's key (see below)
+    const int n = C * kprime;
+    const double dq = bf16_delta(static_cast<double>(qn_q), m);
+    uint64_t best[R];  // key e in lane e / R, register e mod R
     if (kp <= kSelectMax && n <= kWave * kSelectPerLane) {
       // few keys wanted from many: kp rounds of a wavefront minimum, each
       // lane holding as few registers as n needs
-      const int64_t t0 = b.tile_start[L];
-      if (n <= kWave) select_keys<1>(cand, t0, G, g, mq, j, kprime, kp, n, lane, buf);
-      else if (n <= 4 * kWave) select_keys<4>(cand, t0, G, g, mq, j, kprime, kp, n, lane, buf);
-      else select_keys<kSelectPerLane>(cand, t0, G, g, mq, j, kprime, kp, n, lane, buf);
+      if (n <= kWave) select_keys<1>(cand, t0, G, g, mq, j, kprime, kp, n, lane, keys);
+      else if (n <= 4 * kWave) select_keys<4>(cand, t0, G, g, mq, j, kprime, kp, n, lane, keys);
+      else select_keys<kSelectPerLane>(cand, t0, G, g, mq, j, kprime, kp, n, lane, keys);
       wave_lds_sync();
-    } else if (qbound) {
-      // Search rounds: only keys whose lower bound does not exceed the
-      // query's bound U can enter its top k.  They are a prefix of the sorted
-      // keys (the bound grows with the key), so they are gathered and sorted
-      // alone and the item's results do not change.  With fewer than kp of
-      // them the kp-th key is among the dropped ones: the smallest dropped
-      // key, whose bound exceeds U, certifies every row left out.
-      const double Ud = static_cast<double>(qbound[q]);
-      const double dq = bf16_delta(static_cast<double>(qn_q), m);
-      const uint64_t lanes_below = (1ull << lane) - 1ull;
-      int nf = 0;
-      uint64_t dropped = kKeyMax;
-      for (int e0 = 0; e0 < n; e0 += kWave) {
-        const int e = e0 + lane;
-        uint64_t v = kKeyMax;
-        if (e < n) {
-          const int c = e / kprime;
-          v = cand[(tile_of(b.tile_start, L, g, c, G) * mq + j) * kprime + (e - c * kprime)];
-        }
-        bool keep = false;
-        if (v != kKeyMax) {
-          const double x = static_cast<double>(key_d2(v)) - dq;
-          const double lower = (x > 0.0 ? sqrt(x) : 0.0) - qe_q - le_L;
-          keep = !(lower > Ud);
-          if (!keep) dropped = v < dropped ? v : dropped;
-        }
-        const uint64_t km = __ballot(keep);
-        if (keep) buf[nf + __popcll(km & lanes_below)] = v;
-        nf += __popcll(km);
-      }
-      dropped = wave_min_u64(dropped);
-      const int want = nf > kp ? nf : kp;
-      const int P = pow2_at_least(want < 2 ? 2 : want);
-      for (int e = nf + lane; e < P; e += kWave) buf[e] = kKeyMax;
-      wave_lds_sync();
-      wave_sort_u64(buf, P, lane);
-      if (nf < kp) kth_override = dropped;
+#pragma unroll
+      for (int r = 0; r < R; ++r) best[r] = lane * R + r < kp ? keys[lane * R + r] : kKeyMax;
     } else {
-      int P = pow2_at_least(n < 2 ? 2 : n);
-      for (int e = lane; e < P; e += kWave) {
-        uint64_t v = kKeyMax;
-        if (e < n) {
-          int c = e / kprime;
-          v = cand[(tile_of(b.tile_start, L, g, c, G) * mq + j) * kprime + (e - c * kprime)];
+      // Search rounds: a key whose squared distance exceeds T (rounded up
+      // past every key the exact test below keeps) has a lower bound above
+      // U, and so have the keys after it in its list.  The smallest key
+      // dropped this way also certifies every row its list left out.
+      float T = __builtin_inff();
+      if (U < __builtin_inff()) {
+        const double t = static_cast<double>(U) + qe_q + le_L;
+        T = static_cast<float>((t * t + dq) * (1.0 + 1e-6));
+        T = nextafterf(T, __builtin_inff());
+      }
+      const uint32_t tb = f2u(T);
+#pragma unroll
+      for (int r = 0; r < R; ++r) best[r] = kKeyMax;
+      constexpr int kLists = 8 / R;  // lists in flight together
+      for (int c0 = 0; c0 < C; c0 += kLists) {
+        uint64_t w[kLists][R];
+#pragma unroll
+        for (int v = 0; v < kLists; ++v)
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            // descending: lane 63's last register holds the list's smallest key
+            const int e = kCap - 1 - (lane * R + r);
+            const int c = c0 + v < C ? c0 + v : c0;
+            const bool in = c0 + v < C && e < kp;
+            const uint64_t x = cand[((t0 + static_cast<int64_t>(c) * G + g) * mq + j) * kprime + (e < kp ? e : 0)];
+            w[v][r] = in ? x : kKeyMax;
+          }
+#pragma unroll
+        for (int v = 0; v < kLists; ++v) {
+          const uint32_t head =
+              static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(w[v][R - 1] >> 32), kWave - 1));
+          if (head > tb) continue;  // uniform: beyond U, empty, or past the item's lists
+          wave_merge_low(best, w[v], lane);
         }
-        buf[e] = v;
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (lane * R + r >= kp) best[r] = kKeyMax;
+        keys[lane * R + r] = best[r];
       }
       wave_lds_sync();
-      wave_sort_u64(buf, P, lane);
     }
-    uint64_t kth = kth_override != 0 ? kth_override : buf[kp - 1];
-    // number of real candidates among the first kp
+    const uint64_t kth = keys[kp - 1];
+    // the real candidates among the first kp; in search rounds only those
+    // that can still enter the query's top k (lower bound not above U)
     int nc = 0;
-    for (int e = 0; e < kp; ++e) nc += buf[e] != kKeyMax ? 1 : 0;
-    if (qbound) {
-      // search rounds: only candidates that can still enter the query's top k
-      // (lower bound not above the query's bound) are reranked; the keys are
-      // ascending, so they are a prefix
-      const float U = qbound[q];
-      const double dq = bf16_delta(static_cast<double>(qn_q), m);
-      int use = 0;
-      for (int e = 0; e < nc; ++e) {
-        const double v = static_cast<double>(key_d2(buf[e])) - dq;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      bool use = best[r] != kKeyMax;
+      if (use && qbound) {
+        const double v = static_cast<double>(key_d2(best[r])) - dq;
         const double lower = (v > 0.0 ? sqrt(v) : 0.0) - qe_q - le_L;
-        if (lower > static_cast<double>(U)) break;
-        ++use;
+        use = !(lower > static_cast<double>(U));
       }
-      nc = use;
+      nc += __popcll(__ballot(use));
     }
-    // FP32 direct-difference rerank: CB candidates at a time, G lanes each
-    // (all their rows are in flight together), 4 consecutive elements per lane
+    // FP32 scan items: the candidates' keys already hold FP32
+    // direct-difference values (same error bound), ascending; only those
+    // within the band of the k-th need their rows
+    float band = __builtin_inff();
+    int nr = nc;  // candidates whose rows are read
+    if (!bf16) {
+      if (nc >= k) band = key_d2(keys[k - 1]) * (1.0f + 2.0f * delta32);
+      nr = 0;
+#pragma unroll
+      for (int r = 0; r < R; ++r) nr += __popcll(__ballot(lane * R + r < nc && key_d2(best[r]) <= band));
+    }
+    // direct differences: CB candidates at a time, GL lanes each, 4
+    // consecutive elements per lane; two such groups in flight
     const float *qp = qv.q32 + q * m;
     const int CB = PKi < 8 ? PKi : 8, GL = kWave / CB;
     const int sub = lane & (GL - 1), cb = lane / GL;
-    // FP64 for every candidate within the FP32 error band of the k-th
-    float band = __builtin_inff();
-    int nb = 0;
-    if (PKi <= 8 && m <= 16 * GL) {
-      // Few candidates (CB == PK): each lane group holds its candidate's row
-      // and the query's matching elements in registers for both passes, so
-      // the rows are read once.  Same sums in the same order as below.
-      constexpr int kHold = 4;
-      const int e = cb;
-      uint32_t row = 0;
-      float4 qa[kHold], xa[kHold];
-      float p = 0.0f;
-      if (e < nc) {
-        row = key_row(buf[e]);
-        const float *xp = s.x32 + static_cast<int64_t>(row) * m;
-#pragma unroll
-        for (int i = 0; i < kHold; ++i) {
-          const int t = 4 * sub + i * 4 * GL;
-          if (t < m) {
-            qa[i] = *reinterpret_cast<const float4 *>(qp + t);
-            xa[i] = *reinterpret_cast<const float4 *>(xp + t);
-          }
+    for (int e0 = 0; e0 < nr; e0 += 2 * CB) {
+      const int ea = e0 + cb, eb = e0 + CB + cb;
+      const bool two = e0 + CB < nr;  // uniform
+      const uint32_t ra = key_row(keys[ea < nr ? ea : nr - 1]);
+      const uint32_t rb = two ? key_row(keys[eb < nr ? eb : nr - 1]) : ra;
+      const float *xa = s.x32 + static_cast<int64_t>(ra) * m, *xb = s.x32 + static_cast<int64_t>(rb) * m;
+      float pa = 0.0f, pb = 0.0f;
+      double da = 0.0, db = 0.0;
+      if (two) {
+#pragma unroll 4
+        for (int t = 4 * sub; t < m; t += 4 * GL) {
+          const float4 a = *reinterpret_cast<const float4 *>(qp + t);
+          const float4 x = *reinterpret_cast<const float4 *>(xa + t);
+          const float4 y = *reinterpret_cast<const float4 *>(xb + t);
+          add_diff4(a, x, pa, da);
+          add_diff4(a, y, pb, db);
         }
-#pragma unroll
-        for (int i = 0; i < kHold; ++i) {
-          if (4 * sub + i * 4 * GL < m) {
-            float d = qa[i].x - xa[i].x;
-            p = fmaf(d, d, p);
-            d = qa[i].y - xa[i].y;
-            p = fmaf(d, d, p);
-            d = qa[i].z - xa[i].z;
-            p = fmaf(d, d, p);
-            d = qa[i].w - xa[i].w;
-            p = fmaf(d, d, p);
-          }
+      } else {
+#pragma unroll 8
+        for (int t = 4 * sub; t < m; t += 4 * GL) {
+          const float4 a = *reinterpret_cast<const float4 *>(qp + t);
+          const float4 x = *reinterpret_cast<const float4 *>(xa + t);
+          add_diff4(a, x, pa, da);
         }
       }
-      for (int o = GL >> 1; o > 0; o >>= 1) p += __shfl_xor(p, o, kWave);
-      if (sub == 0) k32[e] = e < nc ? make_key(p, row) : kKeyMax;
-      wave_lds_sync();
-      wave_sort_u64(k32, PKi, lane);
-      if (nc >= k) band = key_d2(k32[k - 1]) * (1.0f + 2.0f * delta32);
-      for (int i = 0; i < nc; ++i) nb += key_d2(k32[i]) <= band ? 1 : 0;
-      // the band's members are exactly the candidates whose FP32 value is
-      // within it (every lane of a group holds its candidate's value)
-      const bool inb = e < nc && p <= band;
-      double pd = 0.0;
-      if (inb) {
-#pragma unroll
-        for (int i = 0; i < kHold; ++i) {
-          if (4 * sub + i * 4 * GL < m) {
-            double d = static_cast<double>(qa[i].x) - static_cast<double>(xa[i].x);
-            pd = fma(d, d, pd);
-            d = static_cast<double>(qa[i].y) - static_cast<double>(xa[i].y);
-            pd = fma(d, d, pd);
-            d = static_cast<double>(qa[i].z) - static_cast<double>(xa[i].z);
-            pd = fma(d, d, pd);
-            d = static_cast<double>(qa[i].w) - static_cast<double>(xa[i].w);
-            pd = fma(d, d, pd);
-          }
-        }
+      for (int o = GL >> 1; o > 0; o >>= 1) {
+        pa += __shfl_xor(pa, o, kWave);
+        da += __shfl_xor(da, o, kWave);
       }
-      for (int o = GL >> 1; o > 0; o >>= 1) pd += __shfl_xor(pd, o, kWave);
+      if (two)
+        for (int o = GL >> 1; o > 0; o >>= 1) {
+          pb += __shfl_xor(pb, o, kWave);
+          db += __shfl_xor(db, o, kWave);
+        }
+      wave_lds_sync();  // this step's rows are read before their keys are replaced
       if (sub == 0) {
-        d64[e] = inb ? pd : __builtin_inf();
-        r64[e] = inb ? row : 0xffffffffu;
-      }
-    } else if (!bf16) {
-      // FP32 scan items: the candidates' keys already hold FP32
-      // direct-difference values (same error bound), ascending
-      for (int e = lane; e < PKi; e += kWave) k32[e] = e < nc ? buf[e] : kKeyMax;
-      wave_lds_sync();
-    } else {
-      for (int e0 = 0; e0 < PKi; e0 += CB) {
-        const int e = e0 + cb;
-        float p = 0.0f;
-        uint32_t row = 0;
-        if (e < nc) {
-          row = key_row(buf[e]);
-          const float *xp = s.x32 + static_cast<int64_t>(row) * m;
-          // unrolled so a lane's loads of the row are in flight together (at
-          // most 8 per lane for m <= 256: GL >= 8)
-#pragma unroll 8
-          for (int t = 4 * sub; t < m; t += 4 * GL) {
-            const float4 a = *reinterpret_cast<const float4 *>(qp + t);
-            const float4 x = *reinterpret_cast<const float4 *>(xp + t);
-            float d = a.x - x.x;
-            p = fmaf(d, d, p);
-            d = a.y - x.y;
-            p = fmaf(d, d, p);
-            d = a.z - x.z;
-            p = fmaf(d, d, p);
-            d = a.w - x.w;
-            p = fmaf(d, d, p);
-          }
+        if (ea < nr) {
+          if (bf16) keys[ea] = make_key(pa, ra);
+          d64[ea] = da;
         }
-        for (int o = GL >> 1; o > 0; o >>= 1) p += __shfl_xor(p, o, kWave);
-        if (sub == 0) k32[e] = e < nc ? make_key(p, row) : kKeyMax;
-      }
-      wave_lds_sync();
-      wave_sort_u64(k32, PKi, lane);
-    }
-    if (!(PKi <= 8 && m <= 16 * GL)) {
-      if (nc >= k) band = key_d2(k32[k - 1]) * (1.0f + 2.0f * delta32);
-      for (int e = 0; e < nc; ++e) nb += key_d2(k32[e]) <= band ? 1 : 0;
-      for (int e0 = 0; e0 < PKi; e0 += CB) {
-        const int e = e0 + cb;
-        double p = 0.0;
-        uint32_t row = 0xffffffffu;
-        if (e < nb) {
-          row = key_row(k32[e]);
-          const float *xp = s.x32 + static_cast<int64_t>(row) * m;
-#pragma unroll 8
-          for (int t = 4 * sub; t < m; t += 4 * GL) {
-            const float4 a = *reinterpret_cast<const float4 *>(qp + t);
-            const float4 x = *reinterpret_cast<const float4 *>(xp + t);
-            double d = static_cast<double>(a.x) - static_cast<double>(x.x);
-            p = fma(d, d, p);
-            d = static_cast<double>(a.y) - static_cast<double>(x.y);
-            p = fma(d, d, p);
-            d = static_cast<double>(a.z) - static_cast<double>(x.z);
-            p = fma(d, d, p);
-            d = static_cast<double>(a.w) - static_cast<double>(x.w);
-            p = fma(d, d, p);
-          }
-        }
-        for (int o = GL >> 1; o > 0; o >>= 1) p += __shfl_xor(p, o, kWave);
-        if (sub == 0) {
-          d64[e] = e < nb ? p : __builtin_inf();
-          r64[e] = row;
+        if (two && eb < nr) {
+          if (bf16) keys[eb] = make_key(pb, rb);
+          d64[eb] = db;
         }
       }
     }
     wave_lds_sync();
-    wave_sort_dbl_tag(d64, r64, PKi, lane);
-    int keep = nb < k ? nb : k;
-    for (int i = lane; i < keep; i += kWave) {
-      b.item_d2[static_cast<int64_t>(item) * kmax + i] = d64[i];
-      b.item_row[static_cast<int64_t>(item) * kmax + i] = static_cast<int32_t>(r64[i]);
+    uint64_t p32[R];
+    ExactKey ex[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int e = lane * R + r;
+      p32[r] = e < nr ? keys[e] : kKeyMax;
+      ex[r].d = static_cast<uint64_t>(__double_as_longlong(e < nr ? d64[e] : __builtin_inf()));
+      ex[r].row = e < nr ? key_row(p32[r]) : 0xffffffffu;
+    }
+    // FP64 for every candidate within the FP32 error band of the k-th
+    int nb = nr;
+    if (bf16) {
+      if (nc >= k) {
+        uint64_t srt[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) srt[r] = p32[r];
+        if (nr > 1) sort_first<R>(srt, nr, lane);
+        uint32_t kd = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          if (r == (k - 1) % R) kd = static_cast<uint32_t>(srt[r] >> 32);
+        band = u2f(__builtin_amdgcn_readlane(kd, (k - 1) / R)) * (1.0f + 2.0f * delta32);
+      }
+      nb = 0;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const bool inb = lane * R + r < nr && key_d2(p32[r]) <= band;
+        if (!inb) {
+          ex[r].d = static_cast<uint64_t>(__double_as_longlong(__builtin_inf()));
+          ex[r].row = 0xffffffffu;
+        }
+        nb += __popcll(__ballot(inb));
+      }
+    }
+    if (nr > 1) sort_first<R>(ex, nr, lane);
+    const int keep = nb < k ? nb : k;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int e = lane * R + r;
+      if (e < keep) {
+        b.item_d2[static_cast<int64_t>(item) * kmax + e] = __longlong_as_double(static_cast<long long>(ex[r].d));
+        b.item_row[static_cast<int64_t>(item) * kmax + e] = static_cast<int32_t>(ex[r].row);
+      }
     }
     // Certificate: every row of the item outside the candidate list has a
     // scan key >= kth.  BF16: the computed value is within delta16 of the
@@ -547,14 +540,16 @@ __global__ void __launch_bounds__(256, 3) k_item_rerank(StoreView s, QueryView q
     // by at most qeps and leaf_eps, so d(q, x) >= sqrt(kth - delta16) - eps.
     // FP32: the direct-difference value is within a relative delta32.
     // With a tau threshold T (search rounds), rows at or above T were never
-    // candidates, so the list's own bound is capped by T's.
+    // candidates, so the list's own bound is capped by T's.  (Rows of lists
+    // skipped by U, and candidates past it, are farther than U, which is at
+    // least the query's new tau.)
     if (lane == 0) {
       float bound = __builtin_inff();
       float kd = kth != kKeyMax ? key_d2(kth) : __builtin_inff();
       if (bf16 && b.use_tau) kd = fminf(kd, tau_threshold(tau_q, qn_q, qe_q, le_L, m));
       if (kd < __builtin_inff()) {
         if (bf16) {
-          double v = static_cast<double>(kd) - bf16_delta(qn_q, m);
+          double v = static_cast<double>(kd) - dq;
           bound = static_cast<float>((v > 0.0 ? sqrt(v) : 0.0) - qe_q - le_L);
         } else {
           bound = static_cast<float>(sqrt(static_cast<double>(kd) * (1.0 - delta32)));
@@ -569,13 +564,6 @@ __global__ void __launch_bounds__(256, 3) k_item_rerank(StoreView s, QueryView q
 
 }  // namespace
 
-int rerank_lds_bytes(int max_chunks, int kprime, int *PB) {
-  int n = max_chunks * kprime;
-  *PB = pow2_at_least(n < 2 ? 2 : n);
-  int PK = pow2_at_least(kprime < 2 ? 2 : kprime);
-  return (*PB + PK) * 8 + PK * 8 + PK * 4;
-}
-
 void launch_query_bound(StoreView s, QueryView q, RoundBufs b, int64_t nq, int mq, int kprime, int kmax, int cmax,
                         float eps_max, const uint64_t *cand, float *qbound, hipStream_t st) {
   if (nq <= 0) return;
@@ -587,15 +575,14 @@ void launch_query_bound(StoreView s, QueryView q, RoundBufs b, int64_t nq, int m
 }
 
 void launch_item_rerank(StoreView s, QueryView q, RoundBufs b, int mq, int kprime, int kmax, bool bf16,
-                        const uint64_t *cand, int grid, int max_chunks, hipStream_t st, const float *qbound) {
-  int PB;
-  const size_t slice = round_up(rerank_lds_bytes(max_chunks, kprime, &PB), 16);
-  const int wpb = slice * 4 <= 65536 ? 4 : 1;
-  const size_t lds = slice * wpb;
-  allow_lds(reinterpret_cast<const void *>(k_item_rerank), lds);
-  const int blocks = (grid + wpb - 1) / wpb;
-  hipLaunchKernelGGL(k_item_rerank, dim3(blocks), dim3(64 * wpb), lds, st, s, q, b, mq, kprime, kmax, bf16 ? 1 : 0, PB,
-                     static_cast<int>(slice / 8), cand, qbound);
+                        const uint64_t *cand, int grid, hipStream_t st, const float *qbound) {
+  const dim3 blocks(ceil_div(grid, 4));  // four items (wavefronts) per work-group
+  auto launch = [&](auto kern) {
+    hipLaunchKernelGGL(kern, blocks, dim3(256), 0, st, s, q, b, mq, kprime, kmax, bf16 ? 1 : 0, cand, qbound);
+  };
+  if (kprime <= 64) launch(k_item_rerank<1>);
+  else if (kprime <= 128) launch(k_item_rerank<2>);
+  else launch(k_item_rerank<4>);
   LAUNCH_OK("item_rerank");
 }
 

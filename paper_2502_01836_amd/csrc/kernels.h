@@ -253,7 +253,7 @@ void launch_query_bound(StoreView s, QueryView q, RoundBufs b, int64_t nq, int m
 // qbound (a search round) only the items launch_query_bound listed are
 // reranked.
 void launch_item_rerank(StoreView s, QueryView q, RoundBufs b, int mq, int kprime, int kmax, bool bf16,
-                        const uint64_t *cand, int grid, int max_chunks, hipStream_t st, const float *qbound = nullptr);
+                        const uint64_t *cand, int grid, hipStream_t st, const float *qbound = nullptr);
 
 // Candidate-list geometry for kprime kept keys: queries per tile and list
 // capacity.  BF16: mq_pref queries per tile (16, 32, 48 or 64; others mean
