@@ -449,8 +449,8 @@ int leafi_autotune(leafi_index *index, const float *queries_dev, int64_t nq, con
 
 /* Set the BF16 scan's tile shape directly (what leafi_autotune chooses):
  * chunk_rows in {128, 256, ..., 4096}; queries_per_tile 16, 32, 48 or 64.
- * The default is 1024 rows and 32 queries.  Results do not depend on the
- * shape. */
+ * By default each pass's shape follows from its sizes (1024 rows and 32
+ * queries in leafi_search_knn_noalloc).  Results do not depend on the shape. */
 int leafi_set_tiling(leafi_index *index, int32_t chunk_rows, int32_t queries_per_tile);
 
 /* Item capacity of a planned batch's passes (see leafi_search_knn): at most

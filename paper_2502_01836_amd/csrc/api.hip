@@ -325,11 +325,42 @@ int pick_chunk(const leafi_index *ix, int kprime, int pref) {
     chunk *= 2;
   return chunk;
 }
-int pass_chunk(const leafi_index *ix, bool bf16, int kprime) {
-  return pick_chunk(ix, kprime, bf16 ? ix->tune_chunk : kFp32ChunkRows);
+// Tile shape of a BF16 pass the caller has not tuned (leafi_autotune,
+// leafi_set_tiling), from the items it is expected to hold: long tiles of
+// many queries while they leave every CU several (a tile pays about 10 us of
+// dependent loads and list sorts however few rows it has), shorter ones for
+// small passes, whose tiles would otherwise leave CUs idle and scan for
+// longer each.  Measured against 1,024 rows x 32 queries: 10M x 256, 1,024
+// queries 3.92 -> 3.34 ms (2,048 x 48; 4,096 rows 3.57); 2.5M x 96 ragged,
+// 4,096 queries 14.9 -> 11.6 ms; 20k x 256, 100 queries 128 -> 116 us (256
+// rows); one query at 1M 175 -> 168 us (256 rows).  An all-pairs pass, whose
+// lists fill once per tile however long it is, takes 4,096 rows (500 queries
+// x 128 leaves 1,618 -> 1,465 us).  A round of one leaf per query keeps 16
+// queries per tile (few share a leaf).
+constexpr int kShapeTiles = 2048;  // tiles a pass should have before its tiles grow longer
+PassShape pass_shape(const leafi_index *ix, bool bf16, int kprime, const ItemsEst &est, bool one_leaf) {
+  PassShape s;
+  int chunk = bf16 ? kChunkRows : kFp32ChunkRows, mq = 32;
+  if (bf16 && ix->tune_mq > 0) {
+    chunk = ix->tune_chunk;
+    mq = one_leaf ? 16 : ix->tune_mq;
+  } else if (bf16 && est.items >= 0) {
+    mq = one_leaf ? 16 : 48;
+    chunk = 2 * kRowAlign;
+    const int64_t groups = std::max(ceil_div(est.items, mq), std::min<int64_t>(est.items, ix->N));
+    for (int c = chunk; c <= (est.all_pairs ? 4096 : 2048); c *= 2)
+      if (groups * ix->total_chunks_for(c) >= static_cast<int64_t>(kShapeTiles) * ix->N) chunk = c;
+  } else if (bf16 && one_leaf) {
+    mq = 16;
+  }
+  s.chunk = pick_chunk(ix, kprime, chunk);
+  scan_geometry(bf16, kprime, mq, ix->m, &s.mq, &s.cap);
+  return s;
 }
-void pass_geometry(const leafi_index *ix, bool bf16, int kprime, int *mq, int *cap, bool one_leaf) {
-  scan_geometry(bf16, kprime, bf16 ? (one_leaf ? 16 : ix->tune_mq) : 32, ix->m, mq, cap);
+// Items of a search round of `want` leaves per query (0: every survivor, of
+// which an eighth of all leaves stands for what the bounds and filters leave).
+ItemsEst round_items_est(const leafi_index *ix, int64_t nq, int want) {
+  return ItemsEst{nq * (want == 0 ? std::max(1, ix->N / 8) : std::min(want, ix->N)), false};
 }
 
 int64_t tiles_bound(const leafi_index *ix, int64_t nq, int64_t items_bound, int mq, int chunk) {
@@ -339,12 +370,11 @@ int64_t tiles_bound(const leafi_index *ix, int64_t nq, int64_t items_bound, int 
   return std::min(a, b);
 }
 
-double round_bytes_bound(const leafi_index *ix, int64_t nq, int64_t items_bound, bool bf16, int kprime, int kmax) {
-  int mq, cap;
-  pass_geometry(ix, bf16, kprime, &mq, &cap);
-  const int chunk = pass_chunk(ix, bf16, kprime);
+double round_bytes_bound(const leafi_index *ix, int64_t nq, int64_t items_bound, bool bf16, int kprime, int kmax,
+                         const ItemsEst &est) {
+  const PassShape s = pass_shape(ix, bf16, kprime, est, false);
   return static_cast<double>(items_bound) * (kmax * 12.0 + 32.0) +
-         static_cast<double>(tiles_bound(ix, nq, items_bound, mq, chunk)) * mq * kprime * 8.0;
+         static_cast<double>(tiles_bound(ix, nq, items_bound, s.mq, s.chunk)) * s.mq * kprime * 8.0;
 }
 
 int64_t scan_round(leafi_index *ix, int64_t nq, bool bf16, int kprime, int kmax, hipStream_t st, Timing *tm,
@@ -352,10 +382,8 @@ int64_t scan_round(leafi_index *ix, int64_t nq, bool bf16, int kprime, int kmax,
   Workspace &w = ix->ws;
   RoundOpts def;
   if (!ro) ro = &def;
-  int mq, cap;
-  pass_geometry(ix, bf16, kprime, &mq, &cap, ro->one_leaf);
-  (void)cap;
-  const int chunk = pass_chunk(ix, bf16, kprime);
+  const PassShape shape = pass_shape(ix, bf16, kprime, ro->est, ro->one_leaf);
+  const int mq = shape.mq, chunk = shape.chunk;
   RoundBufs b0 = views(w);
   b0.chunk = chunk;
   b0.use_tau = ro->use_tau ? 1 : 0;
@@ -572,6 +600,7 @@ void search_batch(leafi_index *ix, const float *raw, int64_t nq, const int32_t *
     launch_round_worklist(ix, nq, want, use_f && filters_ready, st, deferred > 0);
     const int64_t bound = nq * static_cast<int64_t>(want == 0 ? N : std::min(want, N)) + deferred;
     ro.one_leaf = r == 0 && want == 1;
+    ro.est = round_items_est(ix, nq, want);
     int64_t items = scan_round(ix, nq, p.bf16, p.kprime, p.kmax, st, stats ? &tm : nullptr, bound, &ro);
     if (items == 0) break;
     launch_query_merge(nq, N, p.kmax, true, r > 0, views(w), st);
@@ -636,9 +665,8 @@ PassCap planned_cap(const leafi_index *ix, int64_t nq, const SearchPlan &p, int 
   const int kp = bf16 ? p.kprime : default_kprime(p.kmax, false);
   // one first-leaf round per query is sized with its one-leaf tiles
   const bool one = bf16 && r == 0 && p.schedule[0] == 1;
-  int mq, lcap;
-  pass_geometry(ix, bf16, kp, &mq, &lcap, one);
-  const int chunk = pass_chunk(ix, bf16, kp);
+  const PassShape shape = pass_shape(ix, bf16, kp, round_items_est(ix, nq, p.schedule[r]), one);
+  const int mq = shape.mq, chunk = shape.chunk;
   auto bytes = [&](int64_t items, int64_t tiles) {
     return static_cast<double>(items) * (p.kmax * 12.0 + 32.0) + static_cast<double>(tiles) * mq * kp * 8.0;
   };
@@ -717,8 +745,7 @@ void prepare_planned(leafi_index *ix, int64_t nq, const SearchPlan &p, bool use_
       const PassCap c = planned_cap(ix, nq, p, r, bf);
       items = std::max(items, c.items);
       const int kp = bf ? p.kprime : kprime_fb;
-      int mq, cap;
-      pass_geometry(ix, bf, kp, &mq, &cap, bf && r == 0 && p.schedule[0] == 1);
+      const int mq = pass_shape(ix, bf, kp, round_items_est(ix, nq, p.schedule[r]), bf && r == 0 && p.schedule[0] == 1).mq;
       cand = std::max(cand, static_cast<size_t>(std::max<int64_t>(c.tiles, 1)) * mq * kp);
     }
   }
@@ -764,6 +791,7 @@ void enqueue_planned(leafi_index *ix, const float *raw, int64_t nq, const int32_
     ro.may_read = false;
     ro.first_leaf = first_leaf;
     ro.one_leaf = r == 0 && p.schedule[0] == 1;
+    ro.est = round_items_est(ix, nq, p.schedule[r]);
     ro.use_tau = true;
     ro.kp_query = p.kp_query;
     ro.row_bytes = scan_row_bytes(ix, true);
@@ -964,17 +992,19 @@ void search_planned(leafi_index *ix, const float *raw, int64_t nq, const int32_t
   }
 }
 
-// All-pairs leaf scan: items = (query, leaf) for the lists already in place;
+// All-pairs leaf scan: n_items items = (query, leaf) of the lists already in place;
 // each item's exact top-k (bf16 scan, certificate, FP32 rescan of the
 // uncertified).  `consume` is called with the item count after the bf16 pass
 // and again after the rescan pass (rescanned items overwrite).
 template <typename Consume>
-void allpairs_items(leafi_index *ix, int64_t nq, int k, hipStream_t st, Consume consume, Timing *tm,
+void allpairs_items(leafi_index *ix, int64_t nq, int k, int64_t n_items, hipStream_t st, Consume consume, Timing *tm,
                     int64_t *n_fallback = nullptr) {
   Workspace &w = ix->ws;
   const bool bf16 = ix->m <= 256;
   int kprime = default_kprime(k, bf16);
-  int64_t items = scan_round(ix, nq, bf16, kprime, k, st, tm);
+  RoundOpts ro;
+  ro.est = ItemsEst{n_items, true};
+  int64_t items = scan_round(ix, nq, bf16, kprime, k, st, tm, -1, &ro);
   if (items == 0) return;
   RoundBufs b = views(w);
   hipLaunchKernelGGL(k_item_cert, dim3(ceil_div(items, 256)), dim3(256), 0, st, items, k, b);
@@ -1013,7 +1043,7 @@ void leaf_knn_prepared(leafi_index *ix, int64_t nq, int k, float *d_out, int64_t
   DevBuf<int32_t> tmp;
   fill_i32(w.kq.get(), nq, k, st);
   lists_all_leaves(ix, nq, tmp, st);
-  allpairs_items(ix, nq, k, st, [&](int64_t items) {
+  allpairs_items(ix, nq, k, nq * ix->N, st, [&](int64_t items) {
     launch_items_to_leaf_knn(items, ix->N, k, k, ix->rowid.get(), views(w), d_out, ids_out, st);
   }, tm);
   HIP_OK(hipStreamSynchronize(st));
@@ -1569,7 +1599,7 @@ int leafi_train_filters(leafi_index *ix, const leafi_train_opts *o, leafi_train_
       hipLaunchKernelGGL(k_fill_lists, dim3(ceil_div(nc, 256)), dim3(256), 0, st, w.qitem_leaf.get(),
                          w.qitem_cnt.get(), w.leaf_cnt.get(), nc, N, dloff.get(), dlst.get());
       LAUNCH_OK("fill_lists");
-      allpairs_items(ix, nc, 1, st, [&](int64_t items) {
+      allpairs_items(ix, nc, 1, static_cast<int64_t>(lst.size()), st, [&](int64_t items) {
         hipLaunchKernelGGL(k_items_to_examples, dim3(ceil_div(items, 256)), dim3(256), 0, st, items, 1, views(w),
                            ix->filt.filt_of_leaf.get(), n_g, n_gt, n_l, n_ex, ex_y.get(), q0);
         LAUNCH_OK("items_to_examples");

@@ -68,6 +68,21 @@ void reset_round(leafi_index *ix, hipStream_t st);
 // Zero the per-leaf and per-query item counts before a fallback pass.
 void reset_for_fallback(leafi_index *ix, int64_t nq, hipStream_t st);
 
+// Items a pass is expected to hold, for the choice of its tile shape (-1: not
+// known); all_pairs: a pass without thresholds (node-wise neighbours).
+struct ItemsEst {
+  int64_t items = -1;
+  bool all_pairs = false;
+};
+ItemsEst round_items_est(const leafi_index *ix, int64_t nq, int want);
+
+// Queries per scan tile, list capacity and rows per tile of a pass (one_leaf:
+// see RoundOpts).
+struct PassShape {
+  int mq = 0, cap = 0, chunk = 0;
+};
+PassShape pass_shape(const leafi_index *ix, bool bf16, int kprime, const ItemsEst &est, bool one_leaf);
+
 struct RoundOpts {
   bool may_read = true;         // false: never read counts back (planned / captured sequences)
   int64_t row_bytes = 0;        // > 0: account the round's unique leaf bytes in ctl[kCtlScanBytes]
@@ -80,6 +95,7 @@ struct RoundOpts {
   bool kp_query = false;        // each query keeps item_kprime(its k) candidates (mixed-k batches)
   bool one_leaf = false;        // at most one leaf per query (a first round of schedule 1): BF16 tiles
                                 // of 16 queries, whatever the tuned size (few queries share a leaf)
+  ItemsEst est;                 // what the pass is expected to hold
   int64_t cap_items = 0;        // > 0: the buffers hold this many items and cap_tiles scan tiles,
   int64_t cap_tiles = 0;        // checked on the device (RoundBufs::cap_items); 0: the bound holds
                                 // every layout
@@ -98,9 +114,8 @@ void add_scan_time(leafi_index *ix, Timing *tm);
 // Upper bound of the bound-sized buffers of a round that reads nothing back.
 constexpr double kPlannedLimit = 16.0 * (1 << 30);
 // Device bytes a scan pass of items_bound items needs (items and candidate lists).
-double round_bytes_bound(const leafi_index *ix, int64_t nq, int64_t items_bound, bool bf16, int kprime, int kmax);
-// Queries per scan tile and list capacity of a pass (one_leaf: see RoundOpts).
-void pass_geometry(const leafi_index *ix, bool bf16, int kprime, int *mq, int *cap, bool one_leaf = false);
+double round_bytes_bound(const leafi_index *ix, int64_t nq, int64_t items_bound, bool bf16, int kprime, int kmax,
+                         const ItemsEst &est);
 int default_kprime(int kmax, bool bf16);
 // d^f - offset for the (query, visit position) pairs listed per filter
 // (plist / pcnt, nq queries) with the installed filters, MLP or CNN.

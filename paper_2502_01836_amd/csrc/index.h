@@ -210,8 +210,8 @@ struct leafi_index {
   int64_t plan_tiles_seen = 0;
   double dev_mem = 0.0;  // the device's memory (bytes)
   // BF16 scan tiling (set by leafi_autotune or leafi_set_tiling): rows and
-  // queries per tile
-  int tune_chunk = leafi::kChunkRows;
-  int tune_mq = 32;
+  // queries per tile; 0: chosen per pass (pass_shape)
+  int tune_chunk = 0;
+  int tune_mq = 0;
   ~leafi_index();
 };

@@ -40,6 +40,23 @@ struct WorkspaceSwap {
   ~WorkspaceSwap() { std::swap(own, ix->ws); }
 };
 
+// The call's tile shape: the tuned one, or 1,024 rows x 32 queries, whose
+// buffers decide which batches fit the scratch area.
+struct FixedTiling {
+  leafi_index *ix;
+  const int chunk, mq;
+  explicit FixedTiling(leafi_index *i) : ix(i), chunk(i->tune_chunk), mq(i->tune_mq) {
+    if (mq == 0) {
+      ix->tune_chunk = kChunkRows;
+      ix->tune_mq = 32;
+    }
+  }
+  ~FixedTiling() {
+    ix->tune_chunk = chunk;
+    ix->tune_mq = mq;
+  }
+};
+
 }  // namespace
 }  // namespace leafi
 
@@ -55,6 +72,7 @@ extern "C" int leafi_search_knn_noalloc(leafi_index *ix, const float *queries, i
     LEAFI_CHECK_ARG(p.bf16, "the no-allocation search runs the BF16 scan");
     LEAFI_CHECK_ARG((o->flags & LEAFI_SEARCH_HOST_ROUNDS) == 0, "the no-allocation search has no host-driven rounds");
     if (nq == 0) return;
+    FixedTiling tiling(ix);
     LEAFI_CHECK_ARG(k_dev && t_dev && ids && dists, "NULL k, target or output pointer");
     LEAFI_CHECK_ARG(can_plan(ix, nq, p),
                     "the batch does not run as a planned launch sequence (its schedule needs a 0 within 8 rounds)");
