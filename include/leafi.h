@@ -332,10 +332,9 @@ typedef struct {
 
 #define LEAFI_SEARCH_NO_GRAPH 1     /* planned sequence as plain launches, never captured */
 #define LEAFI_SEARCH_HOST_ROUNDS 2  /* host-driven rounds (counts read back every round) */
-/* Filter inference tiles: by default a batch with at least one 32-query tile
- * per compute unit uses 64-query tiles (filter weights read half as often),
- * else 32-query tiles.  These flags force one size; values never depend on
- * it (every (query, filter) sum runs in the same order). */
+/* Filter inference tiles: by default the library chooses the queries a tile
+ * holds.  These flags force the small or the large size; values never depend
+ * on it (every (query, filter) sum runs in the same order). */
 #define LEAFI_SEARCH_FILTER_TILE_SMALL 4
 #define LEAFI_SEARCH_FILTER_TILE_LARGE 8
 

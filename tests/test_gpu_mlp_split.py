@@ -1,0 +1,64 @@
+"""MLP inference on split operands at the edges of its tiles: inputs and hidden
+units that are no multiple of 32 or 16, batches with a remainder, filters that
+share their rows among work-groups, and values that are not finite.  Bound:
+FP32 rounding of every term and partial sum (2^-24 each, m + h + 8 of them in a
+chain) of the magnitudes summed."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+def _pkg():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2502_01836_amd as pkg
+    pkg.load()
+    return pkg
+
+
+def _forward(w, x, m, h):
+    """FP64 predictions of one filter and the magnitude its terms sum to."""
+    w, x = w.astype(np.float64), x.astype(np.float64)
+    w1, b1, w2, b2 = w[: h * m].reshape(m, h), w[h * m: h * m + h], w[h * m + h: h * m + 2 * h], w[-1]
+    with np.errstate(invalid="ignore", over="ignore"):
+        out = np.fmax(x @ w1 + b1, 0.0) @ w2 + b2  # a NaN unit counts as 0, as in the kernels
+        mag = (np.abs(x) @ np.abs(w1) + np.abs(b1)) @ np.abs(w2) + np.abs(b2)
+    return out, mag
+
+
+def _draw(F, m, h, nq, seed):
+    g = np.random.default_rng(seed)
+    w = g.uniform(-1, 1, (F, h * m + 2 * h + 1)).astype(np.float32) / np.float32(np.sqrt(m))
+    return w, g.standard_normal((nq, m)).astype(np.float32)
+
+
+@pytest.mark.parametrize("F,m,h,nq", [(1, 4, 4, 1), (3, 36, 20, 33), (2, 32, 256, 65), (2, 256, 256, 500),
+                                      (300, 96, 96, 65), (2, 228, 144, 31), (3, 160, 200, 17), (2, 64, 64, 257),
+                                      (1100, 32, 16, 3), (2, 128, 252, 40), (4, 256, 64, 50), (2, 192, 160, 33)])
+def test_split_inference_at_tile_edges(F, m, h, nq):
+    pkg = _pkg()
+    w, x = _draw(F, m, h, nq, F + m + h)
+    got = pkg.mlp_infer(torch.from_numpy(w).cuda(), m, h, torch.from_numpy(x).cuda()).cpu().numpy()
+    for f in range(0, F, max(1, F // 7)):
+        want, mag = _forward(w[f], x, m, h)
+        assert np.all(np.abs(got[:, f] - want) <= (m + h + 8) * 2.0 ** -24 * mag)
+
+
+@pytest.mark.parametrize("m,h", [(256, 256), (96, 96)])
+def test_split_inference_with_values_that_are_not_finite(m, h):
+    pkg = _pkg()
+    w, x = _draw(3, m, h, 70, 5)
+    x[3, 7], x[40, 1] = np.nan, np.inf
+    x[66, 2] = 3.4e38       # finite, but a bf16 part would round it to infinity
+    w[1, 11] = np.inf       # input 0, hidden unit 11
+    got = pkg.mlp_infer(torch.from_numpy(w).cuda(), m, h, torch.from_numpy(x).cuda()).cpu().numpy()
+    for f in range(3):
+        want, mag = _forward(w[f], x, m, h)
+        fin = np.isfinite(want) & np.isfinite(mag) & (mag < 1e37)
+        assert np.all(np.abs(got[fin, f] - want[fin]) <= (m + h + 8) * 2.0 ** -24 * mag[fin])
+        rest = ~fin & (mag > 1e39)  # infinite in FP32 too
+        assert np.array_equal(np.isfinite(got[rest, f]), np.isfinite(want[rest]) & (np.abs(want[rest]) < 3.4e38))
+    assert got[3, 0] == w[0, -1]  # every hidden unit a NaN: the output bias alone
