@@ -8,7 +8,8 @@
 //   [W1 (C, 3) | b1 (C) | W2 (C_out, C_in, 3) | b2 (C) | w3 (C) | b3]
 // Tap t of a layer reads position p + t - 1 of its input (zero outside).
 //
-// Inference: one work-group per filter at a time (persistent over filters),
+// Inference of shapes whose activations do not fit the split-operand kernel
+// (k_cnn_split.hip): one work-group per filter at a time (persistent over filters),
 // the filter's weights staged in LDS once (W2 transposed to [c][t][o] so
 // four output channels are one 16-byte read) and its queries (all of them,
 // or the (query, leaf) pairs listed for it) passed through one by one: the
@@ -472,6 +473,7 @@ void cnn_check(int m, int C) { check_cnn_shape(m, C); }
 void launch_cnn_infer(const float *w, int F, int m, int C, const float *x, int64_t nq, float *out, hipStream_t st) {
   check_cnn_shape(m, C);
   if (F <= 0 || nq <= 0) return;
+  if (launch_cnn_infer_split(w, F, m, C, x, nq, out, nullptr, nullptr, 0, 0, nullptr, nullptr, nullptr, st)) return;
   const size_t lds = static_cast<size_t>(cnn_infer_lds_floats(m, C)) * sizeof(float);
   allow_lds(reinterpret_cast<const void *>(k_cnn_infer), lds);
   hipLaunchKernelGGL(k_cnn_infer, dim3(F), dim3(kCnnThreads), lds, st, w, F, m, C, x, nq, out, 0, nullptr, nullptr,
@@ -484,6 +486,7 @@ void launch_cnn_infer_pairs(const float *w, int F, int m, int C, const float *x,
                             float *dfo, hipStream_t st) {
   check_cnn_shape(m, C);
   if (F <= 0 || stride <= 0) return;
+  if (launch_cnn_infer_split(w, F, m, C, x, 0, nullptr, plist, pcnt, stride, N, pair, offsets, dfo, st)) return;
   const size_t lds = static_cast<size_t>(cnn_infer_lds_floats(m, C)) * sizeof(float);
   allow_lds(reinterpret_cast<const void *>(k_cnn_infer), lds);
   hipLaunchKernelGGL(k_cnn_infer, dim3(F), dim3(kCnnThreads), lds, st, w, F, m, C, x, int64_t(0), nullptr, 1, plist,

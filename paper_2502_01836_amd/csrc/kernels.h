@@ -353,6 +353,12 @@ int64_t cnn_param_count(int C);
 // LEAFI_EINVAL unless length m and C channels are multiples of 4 whose
 // inference fits in LDS.
 void cnn_check(int m, int C);
+// CNN inference on bf16 parts of the FP32 operands (k_cnn_split.hip): dense
+// (plist null) or listed pairs.  False, with nothing launched, for shapes
+// whose activations do not fit it.
+bool launch_cnn_infer_split(const float *w, int F, int m, int C, const float *x, int64_t nq, float *out,
+                            const int64_t *plist, const int32_t *pcnt, int64_t stride, int N, const int32_t *pair,
+                            const float *offsets, float *dfo, hipStream_t st);
 // d^f of every (query, filter): out [nq, F].
 void launch_cnn_infer(const float *w, int F, int m, int C, const float *x, int64_t nq, float *out, hipStream_t st);
 // Listed pairs, as launch_mlp_infer_pairs: dfo[e] = d^f - offsets[pair[q] F + f].
