@@ -365,8 +365,13 @@ void launch_cnn_infer(const float *w, int F, int m, int C, const float *x, int64
 void launch_cnn_infer_pairs(const float *w, int F, int m, int C, const float *x, const int64_t *plist,
                             const int32_t *pcnt, int64_t stride, int N, const int32_t *pair, const float *offsets,
                             float *dfo, hipStream_t st);
+// The matrix-core kernels of k_cnn_train.hip, which need no gradient scratch;
+// false, with nothing launched, for shapes they do not hold.
+bool launch_cnn_train_mfma(const TrainArgs &a, hipStream_t st);
+bool launch_cnn_sgd_step_mfma(float *w, int F, int m, int C, const float *x, const float *y, int batch, float lr,
+                              float *loss, hipStream_t st);
 // Full SGD training, one work-group per filter (a.h = channels); gbuf [F, P]
-// is gradient scratch.
+// is gradient scratch (the matrix-core kernel where it holds the shape).
 void launch_cnn_train(const TrainArgs &a, float *gbuf, hipStream_t st);
 // One SGD step per filter on explicit batches; gbuf [F, P] scratch.
 void launch_cnn_sgd_step(float *w, int F, int m, int C, const float *x, const float *y, int batch, float lr,
