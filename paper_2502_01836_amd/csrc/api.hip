@@ -181,6 +181,7 @@ RoundBufs views(Workspace &w) {
   b.item_cnt = w.item_cnt.get();
   b.item_bound = w.item_bound.get();
   b.item_live = w.item_live.get();
+  b.taud = w.qbound.get();  // k_query_bound turns it into the rerank's bound
   b.fb_q = w.fb_q.get();
   b.fb_leaf = w.fb_leaf.get();
   b.chunk = kChunkRows;

@@ -207,7 +207,7 @@ __global__ void __launch_bounds__(256) k_query_bound(StoreView s, QueryView qv, 
   for (int64_t q = blockIdx.x; q < nq; q += gridDim.x) {
     const int n_it = b.qitem_cnt[q];
     const int k = b.kq[q];
-    float U = b.tau[q];
+    float U = fminf(b.tau[q], b.taud[q]);  // (taud only falls; the scan is over)
     if (n_it > 0) {
       const int nlists = n_it * cmax;
       uint64_t *in = buf0, *out = buf1;

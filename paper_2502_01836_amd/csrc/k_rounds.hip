@@ -141,6 +141,7 @@ __global__ void __launch_bounds__(64 * kListWaves) k_worklist(int64_t nq, int N,
   const int64_t q = static_cast<int64_t>(blockIdx.x) * kListWaves + wave;
   CascadeCount c;
   if (q < nq) {
+    if (lane == 0) b.taud[q] = b.tau[q];
     if (qround && b.cursor[q] < N) {
       // serving: each query follows its own schedule from its own round count
       const int r = qround[q];
@@ -400,6 +401,7 @@ __global__ void __launch_bounds__(1024) k_first_round_layout(int64_t nq, int N, 
     b.qitem_idx[q * N] = slot;
     b.qitem_cnt[q] = 1;
     b.cursor[q] = 1;
+    b.taud[q] = __builtin_inff();
   }
   if (threadIdx.x == 0) {
     b.ctl[kCtlScanned] += nq;

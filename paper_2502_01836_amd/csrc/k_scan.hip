@@ -350,7 +350,8 @@ __global__ void __launch_bounds__(256, QB >= 3 ? 2 : 4) k_scan_bf16(StoreView s,
   uint32_t *thr = keys + MQ * (cap + 1);
   int *cnt = reinterpret_cast<int *>(thr + MQ);
   int *kpl = cnt + MQ;                                     // [MQ] candidates each list keeps
-  uint16_t *qs = reinterpret_cast<uint16_t *>(kpl + MQ);  // [MQ][m + 8], 16-byte aligned
+  int *lq = kpl + MQ;                                      // [MQ] each list's query
+  uint16_t *qs = reinterpret_cast<uint16_t *>(lq + MQ);   // [MQ][m + 8], 16-byte aligned
   int *s_leaf = reinterpret_cast<int *>(qs + MQ * (s.m + 8));  // [2], after the tile's queries
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
@@ -388,9 +389,10 @@ __global__ void __launch_bounds__(256, QB >= 3 ? 2 : 4) k_scan_bf16(StoreView s,
       int kp = kprime;
       if (j < ti.nqt) {
         const int64_t qq = b.item_q[ti.p0 + j];
+        lq[j] = static_cast<int>(qq);
         if (b.kp_query) kp = item_kprime(1, kprime, b.kq[qq], true);
         if (b.use_tau) {
-          const float T = tau_threshold(b.tau[qq], qv.qn16[qq], qv.qeps[qq], s.leaf_eps[ti.L], m);
+          const float T = tau_threshold(b.taud[qq], qv.qn16[qq], qv.qeps[qq], s.leaf_eps[ti.L], m);
           if (T < __builtin_inff()) t0 = key32_ceil(T);
         }
       }
@@ -452,6 +454,24 @@ __global__ void __launch_bounds__(256, QB >= 3 ? 2 : 4) k_scan_bf16(StoreView s,
     }
     finish_tile(keys, cnt, thr, kpl, t, MQ, ti.nqt, cap, kprime, ti.r0, wave, kWaves, lane, cand);
     __syncthreads();
+    // A list of k keys or more bounds its query's k-th distance: k distinct
+    // rows lie within the k-th key's distance (the key's step rounded up).
+    // Tiles that start later, on any CU, then collect fewer candidates; the
+    // rows they leave out are farther than that bound, so nothing that could
+    // enter a result is lost and every certificate stands.  (A stale read
+    // only means a larger bound.)
+    if (b.use_tau && threadIdx.x < static_cast<unsigned>(ti.nqt)) {
+      const int j = threadIdx.x, qq = lq[j], k = b.kq[qq];
+      if (k <= cnt[j]) {
+        const uint32_t kk = keys[static_cast<int64_t>(j) * (cap + 1) + k - 1];
+        const float kd = u2f((kk >> kLocalBits) << kDropBits | ((1u << kDropBits) - 1));
+        const double v = sqrt(static_cast<double>(kd) + bf16_delta(static_cast<double>(qv.qn16[qq]), m)) +
+                         qv.qeps[qq] + s.leaf_eps[ti.L];
+        float u = static_cast<float>(v);
+        if (static_cast<double>(u) < v) u = nextafterf(u, __builtin_inff());
+        if (u < b.taud[qq]) atomicMin(reinterpret_cast<unsigned int *>(b.taud + qq), f2u(u));
+      }
+    }
   }
 }
 
@@ -572,9 +592,9 @@ int resident_grid(K kern, size_t lds, int want) {
 constexpr int kLdsPerCu = 160 * 1024;
 
 // LDS of a BF16 scan work-group: 32-bit lists, thresholds, counts, per-list
-// candidate counts, the queries (row stride m + 8), two ints.
+// candidate counts and queries, the queries' rows (row stride m + 8), two ints.
 size_t scan_bf16_lds(int mq, int cap, int m) {
-  return static_cast<size_t>(mq) * (cap + 1) * 4 + static_cast<size_t>(mq) * 4 * 3 +
+  return static_cast<size_t>(mq) * (cap + 1) * 4 + static_cast<size_t>(mq) * 4 * 4 +
          static_cast<size_t>(mq) * (m + 8) * 2 + 16;
 }
 

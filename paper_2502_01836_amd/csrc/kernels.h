@@ -70,6 +70,10 @@ struct RoundBufs {
   int32_t *item_cnt;
   float *item_bound;    // lower bound on any row of the item that is not a candidate
   int32_t *item_live;   // a search round's items that its bounds did not certify (ctl[kCtlLive] of them)
+  // [queries] an upper bound of each query's k-th distance after this search
+  // round, from its tau down: the BF16 scan's tiles lower it (atomically, as
+  // the bits of a non-negative float) and start their thresholds from it
+  float *taud;
   // fallback list of (query, leaf) pairs
   int32_t *fb_q;
   int32_t *fb_leaf;
