@@ -387,7 +387,7 @@ int64_t scan_round(leafi_index *ix, int64_t nq, bool bf16, int kprime, int kmax,
   const int mq = shape.mq, chunk = shape.chunk;
   RoundBufs b0 = views(w);
   b0.chunk = chunk;
-  b0.use_tau = ro->use_tau ? 1 : 0;
+  b0.use_tau = ro->use_tau ? (ro->one_leaf ? 1 : 2) : 0;
   b0.kp_query = ro->kp_query ? 1 : 0;
   b0.cap_items = ro->cap_items;
   b0.cap_tiles = ro->cap_tiles;
@@ -424,7 +424,7 @@ int64_t scan_round(leafi_index *ix, int64_t nq, bool bf16, int kprime, int kmax,
   w.cand.reserve(static_cast<size_t>(std::max<int64_t>(tiles, 1)) * mq * kprime);
   RoundBufs b = views(w);
   b.chunk = chunk;
-  b.use_tau = ro->use_tau ? 1 : 0;
+  b.use_tau = b0.use_tau;
   b.kp_query = ro->kp_query ? 1 : 0;
   b.cap_items = ro->cap_items;
   b.cap_tiles = ro->cap_tiles;

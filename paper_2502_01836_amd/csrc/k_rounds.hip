@@ -401,7 +401,6 @@ __global__ void __launch_bounds__(1024) k_first_round_layout(int64_t nq, int N, 
     b.qitem_idx[q * N] = slot;
     b.qitem_cnt[q] = 1;
     b.cursor[q] = 1;
-    b.taud[q] = __builtin_inff();
   }
   if (threadIdx.x == 0) {
     b.ctl[kCtlScanned] += nq;

@@ -392,7 +392,7 @@ __global__ void __launch_bounds__(256, QB >= 3 ? 2 : 4) k_scan_bf16(StoreView s,
         lq[j] = static_cast<int>(qq);
         if (b.kp_query) kp = item_kprime(1, kprime, b.kq[qq], true);
         if (b.use_tau) {
-          const float T = tau_threshold(b.taud[qq], qv.qn16[qq], qv.qeps[qq], s.leaf_eps[ti.L], m);
+          const float T = tau_threshold(b.use_tau == 2 ? b.taud[qq] : b.tau[qq], qv.qn16[qq], qv.qeps[qq], s.leaf_eps[ti.L], m);
           if (T < __builtin_inff()) t0 = key32_ceil(T);
         }
       }
@@ -460,7 +460,7 @@ __global__ void __launch_bounds__(256, QB >= 3 ? 2 : 4) k_scan_bf16(StoreView s,
     // rows they leave out are farther than that bound, so nothing that could
     // enter a result is lost and every certificate stands.  (A stale read
     // only means a larger bound.)
-    if (b.use_tau && threadIdx.x < static_cast<unsigned>(ti.nqt)) {
+    if (b.use_tau == 2 && threadIdx.x < static_cast<unsigned>(ti.nqt)) {
       const int j = threadIdx.x, qq = lq[j], k = b.kq[qq];
       if (k <= cnt[j]) {
         const uint32_t kk = keys[static_cast<int64_t>(j) * (cap + 1) + k - 1];
