@@ -518,7 +518,7 @@ void infer_filters_dense(leafi_index *ix, const float *x, int64_t nq, float *out
 
 void eval_filters(leafi_index *ix, int64_t nq, int ftile, hipStream_t st) {
   Workspace &w = ix->ws;
-  launch_filter_pairs(nq, ix->N, w.lbs.get(), w.order.get(), ix->filt.filt_of_leaf.get(), views(w), w.plist.get(),
+  launch_filter_pairs(nq, ix->N, ix->filt.F, w.lbs.get(), w.order.get(), ix->filt.filt_of_leaf.get(), views(w), w.plist.get(),
                       w.pcnt.get(), w.dfo.get(), st);
   infer_filter_pairs(ix, nq, ftile, st);
 }
@@ -770,8 +770,8 @@ void prepare_planned(leafi_index *ix, int64_t nq, const SearchPlan &p, bool use_
 //    emits it, with no prune cascade launch;
 //  * the filter pairs need only an upper bound of tau (a larger tau selects
 //    a superset, and every pair it adds is pruned by its bound anyway), so
-//    the first round's merge selects them from its own new tau, and their
-//    inference runs right after it.
+//    the first round's merge selects them from its own new tau (for up to
+//    kMergePairsMaxN leaves), and their inference runs right after it.
 void enqueue_planned(leafi_index *ix, const float *raw, int64_t nq, const int32_t *k_dev, const float *t_dev,
                      const SearchPlan &p, bool use_f, int64_t *ids, float *dists, bool timed, hipStream_t st) {
   Workspace &w = ix->ws;
@@ -805,8 +805,9 @@ void enqueue_planned(leafi_index *ix, const float *raw, int64_t nq, const int32_
     const bool filters_next = use_f && r == 0 && !last;
     // rounds after the first may rescan a row the previous round merged
     launch_query_merge(nq, N, p.kmax, true, r > 0, views(w), st, nullptr, nullptr, nullptr,
-                       filters_next ? filter_pair_args(ix) : FilterPairArgs());
-    if (filters_next) infer_filter_pairs(ix, nq, p.ftile, st);
+                       filters_next && N <= kMergePairsMaxN ? filter_pair_args(ix) : FilterPairArgs());
+    if (filters_next && N > kMergePairsMaxN) eval_filters(ix, nq, p.ftile, st);
+    else if (filters_next) infer_filter_pairs(ix, nq, p.ftile, st);
     if (!last) {
       launch_round_worklist(ix, nq, p.schedule[r + 1], use_f, st, true);
       continue;

@@ -27,12 +27,14 @@ struct CascadeCount {
 
 // The cascade of query q (one wavefront) from its cursor with the given tau:
 // emits its surviving leaves into qitem_leaf after the `base` entries already
-// queued there (rescans of the previous round), counts them per leaf and
+// queued there (rescans of the previous round), counts them per leaf in
+// leaf_cnt (the work-group's LDS counts with kLds, else the global ones) and
 // advances its cursor.
+template <bool kLds>
 __device__ inline CascadeCount cascade_query(int64_t q, int N, const float *__restrict__ lbs,
                                              const int32_t *__restrict__ order, const float *__restrict__ dfo,
                                              const int32_t *__restrict__ leaf_n, int want, float tau, RoundBufs &b,
-                                             int lane, int base) {
+                                             int lane, int base, int32_t *leaf_cnt) {
   CascadeCount c;
   int pos = b.cursor[q];
   if (pos < N) {
@@ -96,7 +98,8 @@ __device__ inline CascadeCount cascade_query(int64_t q, int N, const float *__re
         if ((msurv >> lane) & 1ull) {
           const int rank = __popcll(msurv & lt);
           b.qitem_leaf[q * N + base + c.cnt + rank] = L;
-          atomicAdd(b.leaf_cnt + L, 1);
+          if (kLds) __hip_atomic_fetch_add(leaf_cnt + L, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          else atomicAdd(leaf_cnt + L, 1);
           c.series += nv[u];
         }
         c.cnt += __popcll(msurv);
@@ -124,6 +127,11 @@ __device__ inline CascadeCount cascade_query(int64_t q, int N, const float *__re
   return c;
 }
 
+// With kLds the work-group's queries count their leaves in LDS and each leaf
+// is counted globally once per work-group (several queries of a large batch
+// pick the same leaf: 3.1M items of 4,096 queries over 2,198 leaves, 415 -> 41 us;
+// a batch of 1,000 queries over 128 leaves 5.7 -> 6.0).
+template <bool kLds>
 __global__ void __launch_bounds__(64 * kListWaves) k_worklist(int64_t nq, int N, const float *__restrict__ lbs,
                                                              const int32_t *__restrict__ order,
                                                              const float *__restrict__ dfo,
@@ -131,6 +139,7 @@ __global__ void __launch_bounds__(64 * kListWaves) k_worklist(int64_t nq, int N,
                                                              Schedule sched, int32_t *qround, RoundBufs b,
                                                              int append) {
   __shared__ int64_t stat[4][kListWaves];
+  extern __shared__ int32_t s_leaf[];  // [N] with kLds
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   // the round's control words start from zero (nothing reads them during
   // this kernel), and so do the per-leaf fill counters of the placement
@@ -138,6 +147,10 @@ __global__ void __launch_bounds__(64 * kListWaves) k_worklist(int64_t nq, int N,
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < N;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x)
     b.leaf_fill[i] = 0;
+  if (kLds) {
+    for (int i = threadIdx.x; i < N; i += blockDim.x) s_leaf[i] = 0;
+    __syncthreads();
+  }
   const int64_t q = static_cast<int64_t>(blockIdx.x) * kListWaves + wave;
   CascadeCount c;
   if (q < nq) {
@@ -149,7 +162,8 @@ __global__ void __launch_bounds__(64 * kListWaves) k_worklist(int64_t nq, int N,
       if (lane == 0) qround[q] = r + 1;
     }
     // with `append`, the rescans the last merge queued stay first in the list
-    c = cascade_query(q, N, lbs, order, dfo, leaf_n, want, b.tau[q], b, lane, append ? b.qitem_cnt[q] : 0);
+    c = cascade_query<kLds>(q, N, lbs, order, dfo, leaf_n, want, b.tau[q], b, lane, append ? b.qitem_cnt[q] : 0,
+                            kLds ? s_leaf : b.leaf_cnt);
   }
   // one atomic per counter and work-group
   if (lane == 0) {
@@ -159,6 +173,9 @@ __global__ void __launch_bounds__(64 * kListWaves) k_worklist(int64_t nq, int N,
     stat[3][wave] = c.series;
   }
   __syncthreads();
+  if (kLds)
+    for (int i = threadIdx.x; i < N; i += blockDim.x)
+      if (const int n = s_leaf[i]) atomicAdd(b.leaf_cnt + i, n);
   if (threadIdx.x < 4) {
     int64_t v = 0;
     for (int w = 0; w < kListWaves; ++w) v += stat[threadIdx.x][w];
@@ -174,36 +191,80 @@ __global__ void __launch_bounds__(64 * kListWaves) k_worklist(int64_t nq, int N,
 // filter test, and no cascade reaches a position whose bound prunes it now.
 // Filter f collects its entries q * N + position in plist[f * nq + ...]; the
 // other positions ahead of the cursor within the bound get dfo = -inf.
-__global__ void __launch_bounds__(256) k_filter_pairs(int64_t nq, int N, const float *__restrict__ lbs,
-                                                      const int32_t *__restrict__ order,
-                                                      const int32_t *__restrict__ filt_of_leaf, RoundBufs b,
-                                                      const int32_t *__restrict__ qround, int64_t *plist,
-                                                      int32_t *pcnt, float *dfo) {
-  __shared__ int fe_sh[4];
-  int n_fe = 0;  // pairs this lane queued (counted once per work-group: a per-wavefront atomic on
-                 // one control word serialised on its cache line)
-  for (int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; idx < nq * N;
-       idx += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-    const int64_t q = idx / N;
-    const int pos = static_cast<int>(idx - q * N);
-    if (qround && qround[q] != 1) continue;  // serving: only queries that just finished their first round
-    if (pos < b.cursor[q] || b.pair[q] < 0) continue;
-    if (lbs[idx] > b.tau[q] * (1.0f + kLbSlack)) continue;  // pruned by its bound in every later round
-    const int f = filt_of_leaf[order[idx]];
-    if (f < 0) {
-      dfo[idx] = -__builtin_inff();
-      continue;
+//
+// One wavefront per query, 16 queries per work-group.  The bounds ascend
+// along the visit order, so a query's pairs are a prefix of what is ahead of
+// its cursor: the work-group counts its queries' pairs per filter in LDS,
+// takes one range of each filter's list for all of them (one global atomic
+// per filter and work-group, not per pair) and then writes the entries.  6.6M
+// pairs of 4,096 queries: 121 us; with an atomic per pair about 420.
+__global__ void __launch_bounds__(64 * kListWaves) k_filter_pairs(int64_t nq, int N, int F,
+                                                                 const float *__restrict__ lbs,
+                                                                 const int32_t *__restrict__ order,
+                                                                 const int32_t *__restrict__ filt_of_leaf, RoundBufs b,
+                                                                 const int32_t *__restrict__ qround, int64_t *plist,
+                                                                 int32_t *pcnt, float *dfo) {
+  extern __shared__ int32_t s_at[];  // [F] counts, then the next slots
+  __shared__ int fe_sh[kListWaves];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  for (int f = threadIdx.x; f < F; f += blockDim.x) s_at[f] = 0;
+  __syncthreads();
+  if (b.ctl[kCtlOverflow] != 0) return;  // uniform: the round was not placed, no tau is new
+  const int64_t q = static_cast<int64_t>(blockIdx.x) * kListWaves + wave;
+  constexpr int kAhead = 4;  // steps of 64 positions whose loads are in flight together
+  int n_fe = 0, cur = 0, end = 0;  // pairs this lane counted; the query's positions [cur, end)
+  // serving: only queries that just finished their first round
+  if (q < nq && b.pair[q] >= 0 && !(qround && qround[q] != 1)) {
+    cur = end = b.cursor[q];
+    const float cutoff = b.tau[q] * (1.0f + kLbSlack);
+    for (bool more = true; more && end < N;) {
+      float lv[kAhead];
+      int ov[kAhead], fv[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int pos = end + kWave * u + lane;
+        lv[u] = pos < N ? lbs[q * N + pos] : 0.0f;
+        ov[u] = pos < N ? order[q * N + pos] : 0;
+      }
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) fv[u] = filt_of_leaf[ov[u]];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        if (!more) break;
+        const int pos = end + lane;
+        const bool out = pos >= N || lv[u] > cutoff;  // pruned by its bound in every later round
+        const uint64_t mo = __ballot(out);
+        const int n = mo ? __builtin_ctzll(mo) : kWave;
+        if (lane < n) {
+          if (fv[u] < 0) {
+            dfo[q * N + pos] = -__builtin_inff();
+          } else {
+            __hip_atomic_fetch_add(s_at + fv[u], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            ++n_fe;
+          }
+        }
+        end += n;
+        more = n == kWave;
+      }
     }
-    const int slot = atomicAdd(pcnt + f, 1);
-    plist[static_cast<int64_t>(f) * nq + slot] = idx;
-    ++n_fe;
   }
   n_fe = wave_sum(n_fe);
-  if ((threadIdx.x & (kWave - 1)) == 0) fe_sh[threadIdx.x / kWave] = n_fe;
+  if (lane == 0) fe_sh[wave] = n_fe;
   __syncthreads();
+  for (int f = threadIdx.x; f < F; f += blockDim.x)
+    if (const int n = s_at[f]) s_at[f] = atomicAdd(pcnt + f, n);
   if (threadIdx.x == 0) {
-    const int e = fe_sh[0] + fe_sh[1] + fe_sh[2] + fe_sh[3];
+    int e = 0;
+    for (int w = 0; w < kListWaves; ++w) e += fe_sh[w];
     if (e) atomicAdd(reinterpret_cast<unsigned long long *>(b.ctl + kCtlFEvals), static_cast<unsigned long long>(e));
+  }
+  __syncthreads();
+#pragma unroll 4
+  for (int pos = cur + lane; pos < end; pos += kWave) {
+    const int f = filt_of_leaf[order[q * N + pos]];
+    if (f < 0) continue;
+    const int slot = __hip_atomic_fetch_add(s_at + f, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    plist[static_cast<int64_t>(f) * nq + slot] = q * N + pos;
   }
 }
 
@@ -323,12 +384,16 @@ __global__ void __launch_bounds__(1024) k_leaf_scan_scatter(int64_t nq, int N, c
 
 // The leaf scan and the item placement in one launch for up to
 // kLayoutLdsMax leaves: every work-group computes the item starts itself into
-// LDS (work-group 0 also publishes them), then places its 16 queries' items
-// as k_scatter does.  leaf_fill must be zero on entry (the prune cascade
-// zeroes it); leaf_cnt is left for the rerank to zero.
+// LDS (work-group 0 also publishes them) and places its 16 queries' items:
+// counted per leaf in LDS, one range of each leaf's slots taken for all of
+// them, then placed in it (one global atomic per leaf and work-group, not per
+// item: 3.1M items over 2,198 leaves 357 -> 95 us).  leaf_fill must be zero on
+// entry (the prune cascade zeroes it); leaf_cnt is left for the rerank to
+// zero.
 __global__ void __launch_bounds__(1024) k_layout_scatter(int64_t nq, int N, const int64_t *__restrict__ leaf_off,
                                                          int mq, int64_t row_bytes, RoundBufs b) {
-  extern __shared__ int32_t s_ist[];  // [N]
+  extern __shared__ int32_t s_ist[];  // [N] item starts, then next slots; [N] counts
+  int32_t *s_cnt = s_ist + N;
   __shared__ int64_t sh[16];
   // the wavefront's query's item list is requested before the leaf scan, so
   // its latency hides under the scan's
@@ -339,12 +404,20 @@ __global__ void __launch_bounds__(1024) k_layout_scatter(int64_t nq, int N, cons
     n = b.qitem_cnt[q];
     if (lane < n) L0 = b.qitem_leaf[q * N + lane];
   }
+  for (int i = threadIdx.x; i < N; i += blockDim.x) s_cnt[i] = 0;
   const bool over = leaf_scan_body(N, leaf_off, mq, row_bytes, b, sh, blockIdx.x == 0, false, s_ist);
   __syncthreads();
-  if (q >= nq || over) return;
+  if (over) return;  // uniform: nothing is placed
+  for (int r = lane; r < n; r += kWave)
+    __hip_atomic_fetch_add(s_cnt + (r == lane ? L0 : b.qitem_leaf[q * N + r]), 1, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+  __syncthreads();
+  for (int i = threadIdx.x; i < N; i += blockDim.x)
+    if (const int c = s_cnt[i]) s_ist[i] += atomicAdd(b.leaf_fill + i, c);
+  __syncthreads();
   for (int r = lane; r < n; r += kWave) {
     const int L = r == lane ? L0 : b.qitem_leaf[q * N + r];
-    const int slot = s_ist[L] + atomicAdd(b.leaf_fill + L, 1);
+    const int slot = __hip_atomic_fetch_add(s_ist + L, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     b.item_q[slot] = static_cast<int32_t>(q);
     b.item_leaf[slot] = L;
     b.qitem_idx[q * N + r] = slot;
@@ -440,7 +513,7 @@ __global__ void __launch_bounds__(1024) k_scatter(int64_t nq, int N, RoundBufs b
 // or that minimum, so a pass costs about as many rounds as item entries
 // enter the top k.  A row met twice (a rescan of a leaf already merged)
 // carries the same (distance, row) in both lists and is kept once.
-constexpr int kMergePreFp = 4;  // visit positions per lane whose filter-pair inputs the merge prefetches
+constexpr int kMergePreFp = kMergePairsMaxN / kWave;  // visit positions per lane whose filter-pair inputs the merge prefetches
 constexpr int kMergeSlots = 4;  // item lists per lane in one tournament pass (256 items per pass)
 
 // Non-negative doubles order like their bit patterns.
@@ -689,12 +762,11 @@ __global__ void __launch_bounds__(256) k_query_merge(int64_t nq, int N, int kmax
   for (int64_t q = static_cast<int64_t>(blockIdx.x) * 4 + wave; q < nq; q += static_cast<int64_t>(gridDim.x) * 4) {
     // Loads that do not depend on the merge are issued before it, so that
     // the query's chain of dependent global loads stays short: the filter-pair
-    // inputs of this lane's visit positions (N <= 64 kMergePreFp) and the
+    // inputs of this lane's visit positions and the
     // certificate inputs of the query's first 64 items.
     const int n_it = b.qitem_cnt[q];
     const int k = b.kq[q];
     const int have = b.res_cnt[q];
-    const bool pre_fp = fp.plist && N <= kMergePreFp * kWave;
     int cur = 0, pq = -1;
     if (fp.plist) {
       cur = b.cursor[q];
@@ -707,7 +779,7 @@ __global__ void __launch_bounds__(256) k_query_merge(int64_t nq, int N, int kmax
       pf[c] = -1;
       pl[c] = __builtin_inff();
       const int pos = lane + kWave * c;
-      if (pre_fp && pos < N) {
+      if (fp.plist && pos < N) {
         const int64_t idx = q * N + pos;
         pl[c] = fp.lbs[idx];
         pf[c] = fp.filt_of_leaf[fp.order[idx]];
@@ -816,62 +888,18 @@ __global__ void __launch_bounds__(256) k_query_merge(int64_t nq, int N, int kmax
       // selection, from the tau just merged)
       if (n_it <= 0) tau_now = b.tau[q];
       if (pq >= 0) {
-        if (pre_fp) {
 #pragma unroll
-          for (int c = 0; c < kMergePreFp; ++c) {
-            const int pos = lane + kWave * c;
-            if (pos >= cur && pos < N) {
-              const int64_t idx = q * N + pos;
-              const int f = pf[c];
-              if (f < 0 || pl[c] > tau_now * (1.0f + kLbSlack)) {
-                fp.dfo[idx] = -__builtin_inff();
-              } else {
-                fp.plist[static_cast<int64_t>(f) * nq + atomicAdd(fp.pcnt + f, 1)] = idx;
-                ++n_fe;
-              }
+        for (int c = 0; c < kMergePreFp; ++c) {
+          const int pos = lane + kWave * c;
+          if (pos >= cur && pos < N) {
+            const int64_t idx = q * N + pos;
+            const int f = pf[c];
+            if (f < 0 || pl[c] > tau_now * (1.0f + kLbSlack)) {
+              fp.dfo[idx] = -__builtin_inff();
+            } else {
+              fp.plist[static_cast<int64_t>(f) * nq + atomicAdd(fp.pcnt + f, 1)] = idx;
+              ++n_fe;
             }
-          }
-        } else {
-          // The bounds ascend along the visit order, so the positions within
-          // the cutoff are a prefix: the walk ends at the first one past it.
-          // No later cascade reaches a position past it (tau only falls), so
-          // those keep no filter value.  Four steps of 64 positions have
-          // their loads in flight together.
-          const float cutoff = tau_now * (1.0f + kLbSlack);
-          constexpr int kAhead = 4;
-          for (int pos0 = cur; pos0 < N; pos0 += kAhead * kWave) {
-            float lv[kAhead];
-            int ov[kAhead], fv[kAhead];
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-              const int pos = pos0 + kWave * u + lane;
-              const int64_t idx = q * N + pos;
-              lv[u] = pos < N ? fp.lbs[idx] : __builtin_inff();
-              ov[u] = pos < N ? fp.order[idx] : 0;
-            }
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) fv[u] = fp.filt_of_leaf[ov[u]];
-            bool end = false;
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-              const int pos = pos0 + kWave * u + lane;
-              const int64_t idx = q * N + pos;
-              const bool within = pos < N && lv[u] <= cutoff;
-              if (within) {
-                const int f = fv[u];
-                if (f < 0) {
-                  fp.dfo[idx] = -__builtin_inff();
-                } else {
-                  fp.plist[static_cast<int64_t>(f) * nq + atomicAdd(fp.pcnt + f, 1)] = idx;
-                  ++n_fe;
-                }
-              }
-              if (__ballot(!within) != 0) {  // uniform: every later position is past the cutoff
-                end = true;
-                break;
-              }
-            }
-            if (end) break;
           }
         }
       }
@@ -980,18 +1008,23 @@ void launch_worklist(int64_t nq, int N, const float *lbs, const int32_t *order, 
                      int32_t *qround, bool append) {
   Schedule sc{};
   if (sched) sc = *sched;
-  hipLaunchKernelGGL(k_worklist, dim3(ceil_div(std::max<int64_t>(nq, 1), kListWaves)), dim3(64 * kListWaves), 0, st,
-                     nq, N, lbs, order, dfo, leaf_n, want, sc, qround, b, append ? 1 : 0);
+  const dim3 grid(ceil_div(std::max<int64_t>(nq, 1), kListWaves)), block(64 * kListWaves);
+  if (N <= kLayoutLdsMax)
+    hipLaunchKernelGGL(k_worklist<true>, grid, block, static_cast<size_t>(N) * sizeof(int32_t), st, nq, N, lbs, order,
+                       dfo, leaf_n, want, sc, qround, b, append ? 1 : 0);
+  else
+    hipLaunchKernelGGL(k_worklist<false>, grid, block, 0, st, nq, N, lbs, order, dfo, leaf_n, want, sc, qround, b,
+                       append ? 1 : 0);
   LAUNCH_OK("worklist");
 }
 
-void launch_filter_pairs(int64_t nq, int N, const float *lbs, const int32_t *order, const int32_t *filt_of_leaf,
+void launch_filter_pairs(int64_t nq, int N, int F, const float *lbs, const int32_t *order, const int32_t *filt_of_leaf,
                          RoundBufs b, int64_t *plist, int32_t *pcnt, float *dfo, hipStream_t st,
                          const int32_t *qround) {
-  // a grid-stride loop over (query, visit position) with a few work-groups per CU
-  const int64_t blocks = std::min<int64_t>(std::max<int64_t>(ceil_div(nq * N, 256), 1), 4096);
-  hipLaunchKernelGGL(k_filter_pairs, dim3(static_cast<int>(blocks)), dim3(256), 0, st, nq, N, lbs, order,
-                     filt_of_leaf, b, qround, plist, pcnt, dfo);
+  const size_t lds = static_cast<size_t>(std::max(F, 1)) * sizeof(int32_t);
+  allow_lds(reinterpret_cast<const void *>(k_filter_pairs), lds);
+  hipLaunchKernelGGL(k_filter_pairs, dim3(static_cast<unsigned>(ceil_div(std::max<int64_t>(nq, 1), kListWaves))),
+                     dim3(64 * kListWaves), lds, st, nq, N, F, lbs, order, filt_of_leaf, b, qround, plist, pcnt, dfo);
   LAUNCH_OK("filter_pairs");
 }
 
@@ -1038,7 +1071,7 @@ void launch_layout_scatter(int64_t nq, int N, const int64_t *leaf_off, int mq, i
                            hipStream_t st) {
   if (N > kLayoutLdsMax) fail(LEAFI_EINTERNAL, "layout_scatter: too many leaves");
   hipLaunchKernelGGL(k_layout_scatter, dim3(ceil_div(std::max<int64_t>(nq, 1), 16)), dim3(1024),
-                     static_cast<size_t>(N) * sizeof(int32_t), st, nq, N, leaf_off, mq, row_bytes, b);
+                     2 * static_cast<size_t>(N) * sizeof(int32_t), st, nq, N, leaf_off, mq, row_bytes, b);
   LAUNCH_OK("layout_scatter");
 }
 
@@ -1054,6 +1087,7 @@ void launch_query_merge(int64_t nq, int N, int kmax, bool check_cert, bool dedup
   int64_t blocks = ceil_div(nq, 4);
   int grid = static_cast<int>(blocks < 65536 ? blocks : 65536);
   allow_lds(reinterpret_cast<const void *>(k_query_merge), lds);
+  if (fp.plist && N > kMergePairsMaxN) fail(LEAFI_EINTERNAL, "query_merge: too many leaves for its pair selection");
   (void)dedupe;  // the tournament keeps a row met twice once in every round
   hipLaunchKernelGGL(k_query_merge, dim3(grid), dim3(256), lds, st, nq, N, kmax, check_cert ? 1 : 0, b, rowid,
                      ids, dists, fp);

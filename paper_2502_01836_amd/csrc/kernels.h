@@ -193,7 +193,7 @@ void launch_worklist(int64_t nq, int N, const float *lbs, const int32_t *order, 
 // grouped by filter into plist [F, nq] (entries q * N + position) with counts
 // pcnt [F] (zeroed by the caller).  Every other position ahead of the cursor
 // gets dfo = -inf (never pruned by a filter).
-void launch_filter_pairs(int64_t nq, int N, const float *lbs, const int32_t *order, const int32_t *filt_of_leaf,
+void launch_filter_pairs(int64_t nq, int N, int F, const float *lbs, const int32_t *order, const int32_t *filt_of_leaf,
                          RoundBufs b, int64_t *plist, int32_t *pcnt, float *dfo, hipStream_t st,
                          const int32_t *qround = nullptr);
 
@@ -272,7 +272,13 @@ void scan_geometry(bool bf16, int kprime, int mq_pref, int m, int *mq, int *cap)
 // non-null (the batch's last merge) also write every query's output row, as
 // launch_finalize does.
 // With fp.plist non-null the merge also selects each query's filter pairs
-// from its new tau, as launch_filter_pairs does (no separate launch).
+// from its new tau, as launch_filter_pairs does (no separate launch), for up
+// to kMergePairsMaxN leaves: a few positions per lane, prefetched before the
+// merge.  With more, a launch of its own that takes list slots for 16 queries
+// at a time is the cheaper (4,096 queries over 2,198 leaves: the first
+// round's merge with its pairs 642 us, apart 147; 1,000 over 128 leaves: 17,
+// where a launch of its own costs 5).
+constexpr int kMergePairsMaxN = 256;
 struct FilterPairArgs {
   const float *lbs = nullptr;
   const int32_t *order = nullptr;

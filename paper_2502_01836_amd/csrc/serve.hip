@@ -160,7 +160,7 @@ void leafi_server::engine_round(int n_new, int &n_active) {
   if (use_f) {
     // slots that finished their first round get the filter pairs a later round can test
     fill_i32(w.pcnt.get(), F, 0, st);
-    launch_filter_pairs(slots, N, w.lbs.get(), w.order.get(), ix->filt.filt_of_leaf.get(), views(w), w.plist.get(),
+    launch_filter_pairs(slots, N, F, w.lbs.get(), w.order.get(), ix->filt.filt_of_leaf.get(), views(w), w.plist.get(),
                         w.pcnt.get(), w.dfo.get(), st, qround.get());
     infer_filter_pairs(ix, slots, 0, st);
   }

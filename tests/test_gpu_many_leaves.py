@@ -1,0 +1,65 @@
+"""Batches over more leaves than a wavefront's registers or LDS hold per query:
+the filter pairs selected by the merge (256 leaves) or in a launch of their
+own, the leaf counts and item slots taken per work-group of 16 queries, and
+indexes past the 4,096 leaves that the layout keeps in LDS.  Results and
+pruning counts against the FP64 oracle, and the host-driven rounds, the
+planned launches and replayed graphs against each other."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle as O
+import workloads as W
+from test_gpu_parity import assert_knn_parity
+
+pytestmark = pytest.mark.gpu
+
+M, S, H = 32, 8, 8
+
+
+@pytest.mark.parametrize("n,capacity,leaves,nq", [(2500, 10, 256, 17), (5000, 15, 512, 1), (5000, 15, 512, 33),
+                                                 (20000, 4, 7712, 18)])
+def test_counts_slots_and_pairs(n, capacity, leaves, nq):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2502_01836_amd as pkg
+    pkg.load()
+    raw = W.random_walk(n, M, seed=n + 1)
+    ix = pkg.Index().build(torch.from_numpy(raw).cuda(), leaf_capacity=capacity, n_segments=S)
+    N = ix.info()["n_leaves"]
+    assert N == leaves
+    filtered = np.arange(0, N, 3, dtype=np.int32)  # every third leaf has a filter
+    w = W.mlp_weights(len(filtered), M, H, seed=n + 2, out_bias=2.0)
+    offs = np.random.default_rng(n + 3).uniform(0.0, 1.0, len(filtered)).astype(np.float32)
+    ix.set_filters(filtered, torch.from_numpy(w).cuda(), H)
+    ix.set_offsets([1], [0.9], offs[None])
+    q, _, _ = W.noisy_queries(raw, nq, (0.3, 0.6), n + 4, n + 5)
+    xs, qs = O.znorm(raw), O.znorm(q)
+    mu, sd = O.segment_stats(xs, S)
+    t = O.build_tree(mu, sd, M, capacity, "median")
+    lb = O.lower_bound(*O.query_stats(qs, S), O.leaf_boxes(mu, sd, t), M)
+    ld, li = O.leaf_knn(xs, t.leaves, qs, 1)
+    dF = np.zeros((nq, N))
+    dF[:, filtered] = np.stack([O.mlp_forward(w[f], qs, M, H) for f in range(len(filtered))], 1) - offs[None]
+    has = np.zeros(N, dtype=bool)
+    has[filtered] = True
+    r = O.leafi_search(lb, O.visit_order(lb), ld, li, 1, has, dF, (1, 0))
+    qd = torch.from_numpy(q).cuda()
+    out = (torch.empty((nq, 1), dtype=torch.int64, device="cuda"), torch.empty((nq, 1), device="cuda"))
+    seen = []
+    for flags in (pkg.SEARCH_HOST_ROUNDS, pkg.SEARCH_NO_GRAPH, 0, 0, 0, 0):
+        ids, d, st = ix.search(qd, k=1, target=0.9, use_filters=True, schedule=(1, 0), with_stats=True, flags=flags,
+                               out=out)
+        torch.cuda.synchronize()
+        seen.append((ids.cpu().numpy().copy(), d.cpu().numpy().copy(), st))
+    ids, d, st = seen[0]
+    assert_knn_parity(ids, d, r.ids, r.dist, xs, qs)
+    if not r.near_tie.any():
+        assert st["leaves_filter_pruned"] == int(r.f_pruned.sum())
+        assert nq == 1 or r.f_pruned.any()  # the batches reach the filter test
+        assert st["leaves_scanned"] == int(r.scanned.sum())
+    for i2, d2, s2 in seen[1:]:
+        assert np.array_equal(i2, ids) and np.array_equal(d2, d)
+        for key in ("leaves_scanned", "leaves_lb_pruned", "leaves_filter_pruned", "series_scanned"):
+            assert s2[key] == st[key], key
