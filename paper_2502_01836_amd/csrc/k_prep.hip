@@ -273,10 +273,103 @@ __device__ inline void block_sort_u64(uint64_t *keys, int P) {
   }
 }
 
+// The visit order of one query by the NT threads of a work-group: the leaves
+// by ascending (bound, leaf id).  The bounds lb[0 .. N) (each written by the
+// thread that reads it here, or by an earlier kernel) are spread over
+// kOrderBuckets by a monotone map of their range, and a leaf's position is
+// its bucket's start plus its rank among the bucket's keys, a few reads of
+// LDS.  Bounds that crowd one bucket (more than kOrderBucketMax keys: mostly
+// ties) are sorted by the bitonic network instead, as is every order of up to
+// kOrderSortMax leaves, which it finishes in the time of the buckets' barriers.
+// 4,096 queries over 2,198 leaves: 490 -> 167 us with the bounds themselves
+// (the network's 78 stages over 4,096 slots were most of it).
+constexpr int kOrderBuckets = 1024, kOrderBucketMax = 128, kOrderSortMax = 256;
+
+template <int NT>
+__device__ inline void order_leaves(uint64_t *keys, int32_t *at, int N, int P, const float *lb, int32_t *order,
+                                    float *lbs) {
+  __shared__ float s_lo[NT / kWave], s_hi[NT / kWave];
+  __shared__ int32_t sh[NT / kWave];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+  bool sort = N <= kOrderSortMax;  // uniform
+  float lo = __builtin_inff(), hi = 0.0f, scale = 0.0f;
+  auto bucket = [&](float v) {
+    // bounds are not negative; one that is not finite goes to the last bucket
+    return v < __builtin_inff() ? static_cast<int>(fminf((v - lo) * scale, static_cast<float>(kOrderBuckets - 1)))
+                                : kOrderBuckets - 1;
+  };
+  if (!sort) {
+    for (int i = tid; i < kOrderBuckets; i += NT) at[i] = 0;
+    for (int i = tid; i < N; i += NT) {
+      const float v = lb[i];
+      if (v < __builtin_inff()) {
+        lo = fminf(lo, v);
+        hi = fmaxf(hi, v);
+      }
+    }
+    lo = wave_min(lo);
+    hi = wave_max(hi);
+    if (lane == 0) {
+      s_lo[w] = lo;
+      s_hi[w] = hi;
+    }
+    __syncthreads();
+    for (int i = 0; i < NT / kWave; ++i) {
+      lo = fminf(lo, s_lo[i]);
+      hi = fmaxf(hi, s_hi[i]);
+    }
+    scale = hi > lo ? fminf(kOrderBuckets / (hi - lo), 1e30f) : 0.0f;
+    for (int i = tid; i < N; i += NT)
+      __hip_atomic_fetch_add(at + bucket(lb[i]), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __syncthreads();
+    constexpr int kPer = kOrderBuckets / NT;
+    int32_t c[kPer], sum = 0, total;
+    bool crowd = false;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      c[u] = at[tid * kPer + u];
+      sum += c[u];
+      crowd |= c[u] > kOrderBucketMax;
+    }
+    int32_t run = block_scan_excl<NT>(sum, sh, total);
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      at[tid * kPer + u] = run;
+      run += c[u];
+    }
+    sort = __syncthreads_or(crowd) != 0;
+  }
+  if (sort) {
+    for (int i = tid; i < P; i += NT) keys[i] = i < N ? make_key(lb[i], static_cast<uint32_t>(i)) : kKeyMax;
+    __syncthreads();
+    block_sort_u64(keys, P);
+    for (int i = tid; i < N; i += NT) {
+      order[i] = static_cast<int32_t>(key_row(keys[i]));
+      lbs[i] = key_d2(keys[i]);  // the bound itself, in visit order
+    }
+    return;
+  }
+  for (int i = tid; i < N; i += NT) {
+    const float v = lb[i];
+    const int slot = __hip_atomic_fetch_add(at + bucket(v), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    keys[slot] = make_key(v, static_cast<uint32_t>(i));
+  }
+  __syncthreads();
+  // each bucket's counter now stands at its end, the next one's start
+  for (int i = tid; i < N; i += NT) {
+    const uint64_t key = keys[i];
+    const int bk = bucket(key_d2(key)), j0 = bk > 0 ? at[bk - 1] : 0, j1 = at[bk];
+    int r = j0;
+    for (int j = j0; j < j1; ++j) r += keys[j] < key ? 1 : 0;
+    order[r] = static_cast<int32_t>(key_row(key));
+    lbs[r] = key_d2(key);
+  }
+}
+
 // Everything a query needs before its first round, one work-group per query:
 // z-normalisation (fp32 and bf16 copies, norms, rounding error), segment
-// statistics, the summary bound of every leaf, the visit order (bitonic sort
-// of (bound, leaf id)), the calibrated (k, target) row and the search state.
+// statistics, the summary bound of every leaf, the visit order (by
+// (bound, leaf id)), the calibrated (k, target) row and the search state.
 // The same arithmetic as the separate kernels (k_qprep, k_lb, k_order,
 // select_pair_of).  Work-group 0 also zeroes the batch's control words, leaf
 // counts and filter-pair counts.
@@ -297,6 +390,25 @@ __device__ __forceinline__ float summary_lb_cols(const float *qs, const float *_
   return sqrtf(acc);
 }
 
+// summary_lb of leaf L from the boxes laid out as [S][4][N] (a wavefront's
+// lanes, one leaf each, read consecutive words), with the segment count
+// fixed at compile time: the same operations in the same order, so the same
+// value.
+template <int kS>
+__device__ __forceinline__ float summary_lb_t(const float *qs, const float *__restrict__ bt, int N, int L, int m) {
+  float acc = 0.0f;
+#pragma unroll
+  for (int s = 0; s < kS; ++s) {
+    const float *b = bt + static_cast<int64_t>(4 * s) * N + L;
+    float len = static_cast<float>(((s + 1) * m) / kS - (s * m) / kS);
+    float mq = qs[2 * s], sq = qs[2 * s + 1];
+    float gm = fmaxf(fmaxf(b[0] - mq, mq - b[N]), 0.0f);
+    float gs = fmaxf(fmaxf(b[2 * N] - sq, sq - b[3 * N]), 0.0f);
+    acc += len * (gm * gm + gs * gs);
+  }
+  return sqrtf(acc);
+}
+
 __global__ void __launch_bounds__(512) k_query_setup(const float *__restrict__ raw, int m, int S,
                                                      const float *__restrict__ boxes_t, int N, int P, float *q32,
                                                      uint16_t *q16, float *qn16, float *qeps, float *qstat, float *lb, int32_t *order, float *lbs,
@@ -307,6 +419,7 @@ __global__ void __launch_bounds__(512) k_query_setup(const float *__restrict__ r
   extern __shared__ uint64_t keys[];                    // [P]
   float *zs = reinterpret_cast<float *>(keys + P);       // [m]
   float *st = zs + m;                                    // [S][2]
+  int32_t *at = reinterpret_cast<int32_t *>(st + 2 * S);  // [kOrderBuckets]
   const int64_t q = blockIdx.x;
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
   if (blockIdx.x == 0) {
@@ -355,21 +468,9 @@ __global__ void __launch_bounds__(512) k_query_setup(const float *__restrict__ r
     }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < P; i += blockDim.x) {
-    uint64_t key = kKeyMax;
-    if (i < N) {
-      const float v = summary_lb_cols(st, boxes_t, N, i, S, m);
-      lb[q * N + i] = v;
-      key = make_key(v, static_cast<uint32_t>(i));
-    }
-    keys[i] = key;
-  }
-  __syncthreads();
-  block_sort_u64(keys, P);
-  for (int i = threadIdx.x; i < N; i += blockDim.x) {
-    order[q * N + i] = static_cast<int32_t>(key_row(keys[i]));
-    lbs[q * N + i] = key_d2(keys[i]);
-  }
+  for (int i = threadIdx.x; i < N; i += blockDim.x)
+    lb[q * N + i] = S == 16 ? summary_lb_t<16>(st, boxes_t, N, i, m) : summary_lb_cols(st, boxes_t, N, i, S, m);
+  order_leaves<512>(keys, at, N, P, lb + q * N, order + q * N, lbs + q * N);
 }
 
 // k_query_setup with one wavefront per query (four per work-group) for up to
@@ -380,25 +481,6 @@ __global__ void __launch_bounds__(512) k_query_setup(const float *__restrict__ r
 // to its sorted position.
 constexpr int kSetupWaveMaxN = 256;
 constexpr int kSetupMaxPerLane = 1024 / kWave;  // row values per lane (m <= 1024)
-
-// summary_lb of leaf L from the boxes laid out as [S][4][N] (a wavefront's
-// lanes, one leaf each, read consecutive words), with the segment count
-// fixed at compile time: the same operations in the same order, so the same
-// value.
-template <int kS>
-__device__ __forceinline__ float summary_lb_t(const float *qs, const float *__restrict__ bt, int N, int L, int m) {
-  float acc = 0.0f;
-#pragma unroll
-  for (int s = 0; s < kS; ++s) {
-    const float *b = bt + static_cast<int64_t>(4 * s) * N + L;
-    float len = static_cast<float>(((s + 1) * m) / kS - (s * m) / kS);
-    float mq = qs[2 * s], sq = qs[2 * s + 1];
-    float gm = fmaxf(fmaxf(b[0] - mq, mq - b[N]), 0.0f);
-    float gs = fmaxf(fmaxf(b[2 * N] - sq, sq - b[3 * N]), 0.0f);
-    acc += len * (gm * gm + gs * gs);
-  }
-  return sqrtf(acc);
-}
 
 template <int J>  // keys per lane: N <= 64 J
 __device__ inline void rank_and_write(const uint64_t *keys, int N, int lane, int32_t *order_q, float *lbs_q) {
@@ -542,19 +624,12 @@ __global__ void __launch_bounds__(256) k_query_setup_wave(const float *__restric
   else rank_and_write<4>(keys, N, lane, oq, lq);
 }
 
-// One work-group per query: bitonic sort of (lb bits, leaf id) keys in LDS.
+// One work-group per query: its visit order.
 __global__ void __launch_bounds__(256) k_order(const float *__restrict__ lb, int N, int P, int32_t *order,
                                                float *lbs, const int32_t *__restrict__ slots) {
-  extern __shared__ uint64_t keys[];
+  extern __shared__ uint64_t keys[];  // [P], then the bucket counts
   const int64_t q = slots ? slots[blockIdx.x] : static_cast<int64_t>(blockIdx.x);
-  for (int i = threadIdx.x; i < P; i += blockDim.x)
-    keys[i] = i < N ? make_key(lb[q * N + i], static_cast<uint32_t>(i)) : kKeyMax;
-  __syncthreads();
-  block_sort_u64(keys, P);
-  for (int i = threadIdx.x; i < N; i += blockDim.x) {
-    order[q * N + i] = static_cast<int32_t>(key_row(keys[i]));
-    lbs[q * N + i] = key_d2(keys[i]);  // the bound itself, in visit order
-  }
+  order_leaves<256>(keys, reinterpret_cast<int32_t *>(keys + P), N, P, lb + q * N, order + q * N, lbs + q * N);
 }
 
 __global__ void __launch_bounds__(256) k_make_queries(const float *__restrict__ x32, const int64_t *__restrict__ rows,
@@ -611,7 +686,8 @@ void launch_lb(const float *qstat, int64_t nq, const float *boxes, int N, int S,
 void launch_order(const float *lb, int64_t nq, int N, int32_t *order, float *lbs, hipStream_t st,
                   const int32_t *slots) {
   int P = pow2_at_least(N < 2 ? 2 : N);
-  size_t lds = static_cast<size_t>(P) * sizeof(uint64_t);  // <= 128 KiB for N <= 16384
+  // <= 132 KiB for N <= 16384
+  size_t lds = static_cast<size_t>(P) * sizeof(uint64_t) + kOrderBuckets * sizeof(int32_t);
   allow_lds(reinterpret_cast<const void *>(k_order), lds);
   hipLaunchKernelGGL(k_order, dim3(nq), dim3(256), lds, st, lb, N, P, order, lbs, slots);
   LAUNCH_OK("order");
@@ -634,7 +710,8 @@ void launch_query_setup(const float *raw, int64_t nq, int m, int S, const float 
     return;
   }
   const int P = pow2_at_least(N < 2 ? 2 : N);
-  const size_t lds = static_cast<size_t>(P) * sizeof(uint64_t) + (static_cast<size_t>(m) + 2 * S) * sizeof(float);
+  const size_t lds = static_cast<size_t>(P) * sizeof(uint64_t) + (static_cast<size_t>(m) + 2 * S) * sizeof(float) +
+                     kOrderBuckets * sizeof(int32_t);
   allow_lds(reinterpret_cast<const void *>(k_query_setup), lds);
   hipLaunchKernelGGL(k_query_setup, dim3(static_cast<unsigned>(nq)), dim3(512), lds, st, raw, m, S, boxes_t, N, P, q32,
                      q16, qn16, qeps, qstat, lb, order, lbs, k_dev, t_dev, n_pairs, pair_k, pair_t, kmax, b, F, pcnt);

@@ -1,7 +1,8 @@
 """Batches over more leaves than a wavefront's registers or LDS hold per query:
 the filter pairs selected by the merge (256 leaves) or in a launch of their
-own, the leaf counts and item slots taken per work-group of 16 queries, and
-indexes past the 4,096 leaves that the layout keeps in LDS.  Results and
+own, the leaf counts and item slots taken per work-group of 16 queries,
+indexes past the 4,096 leaves that the layout keeps in LDS, and visit orders
+by bucket and rank, with bounds that crowd one bucket as well.  Results and
 pruning counts against the FP64 oracle, and the host-driven rounds, the
 planned launches and replayed graphs against each other."""
 import numpy as np
@@ -18,14 +19,17 @@ pytestmark = pytest.mark.gpu
 M, S, H = 32, 8, 8
 
 
-@pytest.mark.parametrize("n,capacity,leaves,nq", [(2500, 10, 256, 17), (5000, 15, 512, 1), (5000, 15, 512, 33),
-                                                 (20000, 4, 7712, 18)])
-def test_counts_slots_and_pairs(n, capacity, leaves, nq):
+@pytest.mark.parametrize("n,capacity,leaves,nq,crowd", [(2500, 10, 256, 17, 0), (5000, 15, 512, 1, 0),
+                                                       (5000, 15, 512, 33, 0), (20000, 4, 7712, 18, 0),
+                                                       (6000, 15, 512, 9, 4000)])
+def test_counts_slots_and_pairs(n, capacity, leaves, nq, crowd):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import paper_2502_01836_amd as pkg
     pkg.load()
     raw = W.random_walk(n, M, seed=n + 1)
+    if crowd:  # the last rows are close copies of one series: their leaves' bounds crowd together
+        raw[n - crowd:] = raw[n - 1] + 2e-3 * np.random.default_rng(n).standard_normal((crowd, M)).astype(np.float32)
     ix = pkg.Index().build(torch.from_numpy(raw).cuda(), leaf_capacity=capacity, n_segments=S)
     N = ix.info()["n_leaves"]
     assert N == leaves
@@ -34,11 +38,14 @@ def test_counts_slots_and_pairs(n, capacity, leaves, nq):
     offs = np.random.default_rng(n + 3).uniform(0.0, 1.0, len(filtered)).astype(np.float32)
     ix.set_filters(filtered, torch.from_numpy(w).cuda(), H)
     ix.set_offsets([1], [0.9], offs[None])
-    q, _, _ = W.noisy_queries(raw, nq, (0.3, 0.6), n + 4, n + 5)
+    q, _, _ = W.noisy_queries(raw[:n - crowd], nq, (0.3, 0.6), n + 4, n + 5)
     xs, qs = O.znorm(raw), O.znorm(q)
     mu, sd = O.segment_stats(xs, S)
     t = O.build_tree(mu, sd, M, capacity, "median")
     lb = O.lower_bound(*O.query_stats(qs, S), O.leaf_boxes(mu, sd, t), M)
+    if crowd:
+        for b in lb:
+            assert np.histogram(b, bins=1024)[0].max() > 128
     ld, li = O.leaf_knn(xs, t.leaves, qs, 1)
     dF = np.zeros((nq, N))
     dF[:, filtered] = np.stack([O.mlp_forward(w[f], qs, M, H) for f in range(len(filtered))], 1) - offs[None]
