@@ -181,7 +181,7 @@ RoundBufs views(Workspace &w) {
   b.item_cnt = w.item_cnt.get();
   b.item_bound = w.item_bound.get();
   b.item_live = w.item_live.get();
-  b.taud = w.qbound.get();  // k_query_bound turns it into the rerank's bound
+  b.taud = w.qbound.get();
   b.fb_q = w.fb_q.get();
   b.fb_leaf = w.fb_leaf.get();
   b.chunk = kChunkRows;
@@ -460,10 +460,9 @@ int64_t scan_round(leafi_index *ix, int64_t nq, bool bf16, int kprime, int kmax,
   const bool bound = bf16 && ro->use_tau && !ro->one_leaf;
   if (bound) {
     launch_query_bound(s, q, b, nq, mq, kprime, kmax, ix->max_chunks_for(chunk), ix->leaf_eps_max, w.cand.get(),
-                       w.qbound.get(), st);
+                       st);
   }
-  launch_item_rerank(s, q, b, mq, kprime, kmax, bf16, w.cand.get(), grid_r, st,
-                     bound ? w.qbound.get() : nullptr);
+  launch_item_rerank(s, q, b, mq, kprime, kmax, bf16, w.cand.get(), ib, grid_r, st, bound);
   return items;
 }
 

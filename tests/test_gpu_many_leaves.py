@@ -70,3 +70,26 @@ def test_counts_slots_and_pairs(n, capacity, leaves, nq, crowd):
         assert np.array_equal(i2, ids) and np.array_equal(d2, d)
         for key in ("leaves_scanned", "leaves_lb_pruned", "leaves_filter_pruned", "series_scanned"):
             assert s2[key] == st[key], key
+
+
+@pytest.mark.parametrize("nq,k", [(1, 10), (40, 50), (40, 256), (9, 1), (330, 1)])
+def test_bounds_skip_no_result(nq, k):
+    """Exact batches on unstructured series (few leaves pruned, so every query
+    meets most of the 256): items tested against their queries' bounds one to a
+    wavefront, several to one, or listed first; bounds from the scan alone
+    (k = 1) and from the k-th of the collected keys, up to more than fit."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2502_01836_amd as pkg
+    pkg.load()
+    rng = np.random.default_rng(31)
+    raw = rng.standard_normal((8000, M)).astype(np.float32)
+    q = (raw[rng.choice(8000, nq, replace=False)] + rng.standard_normal((nq, M))).astype(np.float32)
+    ix = pkg.Index().build(torch.from_numpy(raw).cuda(), leaf_capacity=32, n_segments=S)
+    ids, d, st = ix.search(torch.from_numpy(q).cuda(), k=k, k_max=k, use_filters=False, schedule=(1, 0),
+                           with_stats=True)
+    torch.cuda.synchronize()
+    assert st["leaves_scanned"] > 128 * nq
+    xs, qs = O.znorm(raw), O.znorm(q)
+    ref_ids, ref_d = O.knn(xs, qs, k)
+    assert_knn_parity(ids.cpu().numpy(), d.cpu().numpy(), ref_ids, ref_d, xs, qs)
