@@ -7,6 +7,7 @@
 
 #include "device_util.h"
 #include "kernels.h"
+#include "wave_sort.h"
 
 namespace leafi {
 
@@ -505,61 +506,55 @@ __global__ void __launch_bounds__(1024) k_scatter(int64_t nq, int N, RoundBufs b
 // top-k (sorted by (FP64 distance, row)), refresh tau and, in a regular
 // round, queue every item whose certificate bound does not exceed the new tau
 // for a rescan (by the next round's scan, or an exact FP32 pass after the
-// last round).  Every list is already sorted (the running top-k and each
-// item's exact top-k), so the k smallest of their union are selected by a
-// tournament over the list heads (merge_pass_staged), not a sort of
-// everything: each round takes the wavefront minimum of the items' heads and
-// emits either the run of running-list entries below it (up to 64 at once)
-// or that minimum, so a pass costs about as many rounds as item entries
-// enter the top k.  A row met twice (a rescan of a leaf already merged)
-// carries the same (distance, row) in both lists and is kept once.
+// last round).  The top-k is held in registers, R entries per lane; the items'
+// entries are read 64 R at a time, all loads in flight together, those that
+// cannot enter are dropped, the rest sorted and merged in registers.  A row
+// can be met twice only when a leaf merged in an earlier round is rescanned
+// (`dedupe`): its new entry is dropped.  What bounds it is one query's chain
+// of loads and sorts: 1,024 queries of k <= 100 over 10M series take 35 us in
+// their second round and 15 after their rescans; a tournament that emitted the
+// entries one by one from staged lists in LDS took 141 and 139.
 constexpr int kMergePreFp = kMergePairsMaxN / kWave;  // visit positions per lane whose filter-pair inputs the merge prefetches
-constexpr int kMergeSlots = 4;  // item lists per lane in one tournament pass (256 items per pass)
+constexpr int kMergeSlots = 4;  // item lists per lane in one pass (256 items per pass)
 
-// Non-negative doubles order like their bit patterns.
-__device__ __forceinline__ uint64_t dbl_bits(double v) { return static_cast<uint64_t>(__double_as_longlong(v)); }
+// LDS of one merge wavefront: the item lists' offsets among the pass's
+// entries and their items, the rows of the top-k.
+__host__ __device__ constexpr int merge_slice_words(int R) { return 2 * kWave * kMergeSlots + 4 + kWave * R; }
 
-// One pass of the tournament: the k smallest distinct (distance, row)
-// entries of the sorted list in (in_v, in_t) (n_in entries, LDS) and of the
-// item lists qitem_idx[q N + it0 ..] go to (out_v, out_t) in ascending order;
-// returns how many.  The pass's lists are staged in LDS first: every entry of
-// the (at most 64 kMergeSlots) lists, each cut to k, is loaded at once (all
-// loads in flight together, not one dependent load per round), so the
-// tournament's rounds read LDS only.  Takes the leading items whose entries
-// fit kMergeStage (at least one: an item has at most k <= 256 entries) and
-// sets *consumed to their number; the caller passes the rest again.
-// stage_v / stage_t hold kMergeStage entries, soff and sidx 64 kMergeSlots + 1
-// ints.
-constexpr int kMergeStage = 1024;
-
-// LDS of one merge wavefront: the two kmax-entry lists (16-byte multiple),
-// the staged entries, their slot offsets and item indexes.
-__host__ __device__ inline size_t merge_lists_bytes(int kmax) {
-  return (2 * static_cast<size_t>(kmax) * (sizeof(double) + sizeof(uint32_t)) + 15) / 16 * 16;
-}
-__host__ __device__ inline size_t merge_slice_bytes(int kmax) {
-  const size_t stage = static_cast<size_t>(kMergeStage) * (sizeof(double) + sizeof(uint32_t)) +
-                       (2 * kWave * kMergeSlots + 1) * sizeof(int);
-  return merge_lists_bytes(kmax) + (stage + 15) / 16 * 16;
+// Entry i (lane i / R, register i mod R) of a wavefront's sorted keys.
+template <int R>
+__device__ __forceinline__ ExactKey entry_of(const ExactKey (&v)[R], int i) {
+  ExactKey x = v[0];
+#pragma unroll
+  for (int r = 1; r < R; ++r) x = pick(i % R == r, v[r], x);
+  const int l = i / R;
+  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(x.d)), l);
+  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(x.d >> 32)), l);
+  return ExactKey{static_cast<uint64_t>(hi) << 32 | lo,
+                  static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(x.row), l))};
 }
 
-__device__ inline int merge_pass_staged(int64_t q, int N, int kmax, int k, const RoundBufs &b, int it0, int nb,
-                                        const double *in_v, const uint32_t *in_t, int n_in, double *out_v,
-                                        uint32_t *out_t, int lane, double *stage_v, uint32_t *stage_t, int *soff,
-                                        int *sidx, int *consumed) {
-  constexpr double kInf = __builtin_inf();
+constexpr uint32_t kNoRow = 0xffffffffu;
+__device__ __forceinline__ ExactKey no_entry() { return ExactKey{0x7ff0000000000000ull, kNoRow}; }
+
+// Merges the lists of items qitem_idx[q N + it0 ..  + nb) (nb <= 256), each
+// cut to k, into the k entries of `best`.
+template <int R>
+__device__ inline void merge_pass(int64_t q, int N, int kmax, int k, const RoundBufs &b, int it0, int nb, bool dedupe,
+                                  ExactKey (&best)[R], int lane, int *soff, int *sidx, uint32_t *rows) {
   constexpr int kSlots = kWave * kMergeSlots;
-  int cnt[kMergeSlots], off[kMergeSlots];
+  int idx[kMergeSlots], cnt[kMergeSlots];
+#pragma unroll
+  for (int i = 0; i < kMergeSlots; ++i) {
+    const int j = lane + kWave * i;
+    idx[i] = j < nb ? b.qitem_idx[q * N + it0 + j] : 0;
+    cnt[i] = j < nb ? b.item_cnt[idx[i]] : 0;
+  }
   int total = 0;
 #pragma unroll
   for (int i = 0; i < kMergeSlots; ++i) {
     const int j = lane + kWave * i;
-    int idx = 0, c = 0;
-    if (j < nb) {
-      idx = b.qitem_idx[q * N + it0 + j];
-      c = b.item_cnt[idx];
-      c = c < k ? c : k;
-    }
+    const int c = cnt[i] < k ? cnt[i] : k;
     // slot 64 i + lane starts after every slot before it
     int x = c;
 #pragma unroll
@@ -567,193 +562,70 @@ __device__ inline int merge_pass_staged(int64_t q, int N, int kmax, int k, const
       const int y = __shfl_up(x, o, kWave);
       if (lane >= o) x += y;
     }
-    off[i] = total + x - c;
+    soff[j] = total + x - c;
+    sidx[j] = idx[i];
     total += __shfl(x, kWave - 1, kWave);
-    cnt[i] = c;
-    sidx[j] = idx;
   }
-  // the leading items whose entries fit the staging area (slot order
-  // follows item order, so they are a prefix); the rest wait for the next call
-  int used = 0, staged = 0;
-#pragma unroll
-  for (int i = 0; i < kMergeSlots; ++i) {
-    const bool fit = lane + kWave * i < nb && off[i] + cnt[i] <= kMergeStage;
-    used += __popcll(__ballot(fit));
-    if (!fit) cnt[i] = 0;
-    staged = max(staged, wave_max(fit ? off[i] + cnt[i] : 0));
-  }
-  *consumed = used;
-  total = staged;
-#pragma unroll
-  for (int i = 0; i < kMergeSlots; ++i) soff[lane + kWave * i] = cnt[i] > 0 ? off[i] : min(off[i], total);
   if (lane == 0) soff[kSlots] = total;
   wave_lds_sync();
-  // entry e of the staged lists belongs to the last slot s with soff[s] <= e
-  // (slots with no entries share their successor's offset)
-  constexpr int kU = 4;  // entries per lane in flight together
-  for (int e0 = 0; e0 < total; e0 += kWave * kU) {
-    double v[kU];
-    uint32_t t[kU];
+  for (int e0 = 0; e0 < total; e0 += kWave * R) {
+    // entry e belongs to the last slot s with soff[s] <= e (slots with no
+    // entries share their successor's offset)
+    int slot[R];
 #pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int e = e0 + lane + kWave * u;
-      int sl = 0;
-      if (e < total) {
-        int lo = 0, hi = kSlots;  // soff[lo] <= e < soff[hi]
-        while (hi - lo > 1) {
-          const int mid = (lo + hi) >> 1;
-          if (soff[mid] <= e) lo = mid;
-          else hi = mid;
-        }
-        sl = lo;
-      }
-      const int64_t at = static_cast<int64_t>(sidx[sl]) * kmax + (e < total ? e - soff[sl] : 0);
-      v[u] = b.item_d2[at];
-      t[u] = static_cast<uint32_t>(b.item_row[at]);
-    }
+    for (int r = 0; r < R; ++r) slot[r] = 0;
 #pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int e = e0 + lane + kWave * u;
-      if (e < total) {
-        stage_v[e] = v[u];
-        stage_t[e] = t[u];
-      }
+    for (int step = kSlots / 2; step >= 1; step /= 2)
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (soff[slot[r] + step] <= e0 + lane * R + r) slot[r] += step;
+    ExactKey x[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int e = e0 + lane * R + r;
+      const int64_t at = static_cast<int64_t>(sidx[slot[r]]) * kmax + (e < total ? e - soff[slot[r]] : 0);
+      x[r].d = static_cast<uint64_t>(__double_as_longlong(b.item_d2[at]));
+      x[r].row = static_cast<uint32_t>(b.item_row[at]);
     }
+    const ExactKey last = entry_of(best, k - 1);
+    bool any = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const bool in = e0 + lane * R + r < total && x[r] < last;
+      x[r] = pick(in, x[r], no_entry());
+      any |= in;
+    }
+    if (__ballot(any) == 0) continue;
+    if (dedupe) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) rows[lane * R + r] = best[r].row;
+      wave_lds_sync();
+      for (int i = 0; i < k; ++i) {
+        const uint32_t row = rows[i];
+#pragma unroll
+        for (int r = 0; r < R; ++r) x[r] = pick(x[r].row == row, no_entry(), x[r]);
+      }
+      wave_lds_sync();
+    }
+    if (total - e0 <= 16 * R) wave_sort_regs<16>(x, lane);
+    else wave_sort_regs<kWave>(x, lane);
+    ExactKey y[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) y[r] = lane_xor<kWave - 1>(x[R - 1 - r], lane);
+    wave_merge_low(best, y, lane);
   }
   wave_lds_sync();
-  double hv[kMergeSlots];
-  uint32_t ht[kMergeSlots];
-  int pos[kMergeSlots];
-#pragma unroll
-  for (int i = 0; i < kMergeSlots; ++i) {
-    pos[i] = 0;
-    hv[i] = cnt[i] > 0 ? stage_v[off[i]] : kInf;
-    ht[i] = cnt[i] > 0 ? stage_t[off[i]] : 0xffffffffu;
-  }
-  int out = 0, rp = 0;
-  while (out < k) {
-    // smallest head of the staged lists
-    double lv = kInf;
-    uint32_t lt = 0xffffffffu;
-#pragma unroll
-    for (int i = 0; i < kMergeSlots; ++i)
-      if (hv[i] < lv || (hv[i] == lv && ht[i] < lt)) {
-        lv = hv[i];
-        lt = ht[i];
-      }
-    const uint64_t mvb = wave_min_u64(dbl_bits(lv));
-    const uint64_t mtb = wave_min_u64(dbl_bits(lv) == mvb ? static_cast<uint64_t>(lt) : ~0ull);
-    const double gv = __longlong_as_double(static_cast<long long>(mvb));
-    const uint32_t gt = static_cast<uint32_t>(mtb);
-    // the running list's entries below it come next, as one run (up to a
-    // wavefront's worth per round; lane j checks entry rp + j)
-    bool below = false;
-    if (rp + lane < n_in && out + lane < k) {
-      const double v = in_v[rp + lane];
-      const uint32_t t = in_t[rp + lane];
-      below = v < gv || (v == gv && t < gt);
-    }
-    const uint64_t bm = __ballot(below);
-    const int run = ~bm == 0 ? kWave : __builtin_ctzll(~bm);
-    if (run > 0) {
-      if (lane < run) {
-        out_v[out + lane] = in_v[rp + lane];
-        out_t[out + lane] = in_t[rp + lane];
-      }
-      out += run;
-      rp += run;
-      continue;
-    }
-    if (gt == 0xffffffffu) break;  // every list is exhausted
-    // With one staged list left (a query's first round has one item), its
-    // entries below the running head come next, as one run likewise.
-    int live = 0, owner = 0, oslot = 0;
-#pragma unroll
-    for (int i = 0; i < kMergeSlots; ++i) {
-      const uint64_t bl = __ballot(pos[i] < cnt[i]);
-      if (bl != 0 && live == 0) {
-        owner = __builtin_ctzll(bl);
-        oslot = i;
-      }
-      live += __popcll(bl);
-    }
-    if (live == 1) {
-      int po = 0, oo = 0, co = 0;
-#pragma unroll
-      for (int i = 0; i < kMergeSlots; ++i)
-        if (i == oslot) {
-          po = pos[i];
-          oo = off[i];
-          co = cnt[i];
-        }
-      po = __shfl(po, owner, kWave);
-      oo = __shfl(oo, owner, kWave);
-      co = __shfl(co, owner, kWave);
-      const double rv = rp < n_in ? in_v[rp] : kInf;
-      const uint32_t rt = rp < n_in ? in_t[rp] : 0xffffffffu;
-      bool take = false;
-      if (po + lane < co && out + lane < k) {
-        const double v = stage_v[oo + po + lane];
-        const uint32_t t = stage_t[oo + po + lane];
-        take = v < rv || (v == rv && t < rt);
-      }
-      const uint64_t tm = __ballot(take);
-      const int run2 = ~tm == 0 ? kWave : __builtin_ctzll(~tm);
-      if (run2 > 0) {
-        if (lane < run2) {
-          out_v[out + lane] = stage_v[oo + po + lane];
-          out_t[out + lane] = stage_t[oo + po + lane];
-        }
-        out += run2;
-        if (lane == owner) {
-#pragma unroll
-          for (int i = 0; i < kMergeSlots; ++i)
-            if (i == oslot) {
-              pos[i] += run2;
-              const bool more = pos[i] < cnt[i];
-              hv[i] = more ? stage_v[off[i] + pos[i]] : kInf;
-              ht[i] = more ? stage_t[off[i] + pos[i]] : 0xffffffffu;
-            }
-        }
-        continue;
-      }
-    }
-    // else the staged minimum (the running head too when it is the same row)
-    if (lane == 0) {
-      out_v[out] = gv;
-      out_t[out] = gt;
-    }
-    ++out;
-    if (rp < n_in && in_v[rp] == gv && in_t[rp] == gt) ++rp;
-#pragma unroll
-    for (int i = 0; i < kMergeSlots; ++i) {
-      if (hv[i] == gv && ht[i] == gt) {
-        ++pos[i];
-        const bool more = pos[i] < cnt[i];
-        hv[i] = more ? stage_v[off[i] + pos[i]] : kInf;
-        ht[i] = more ? stage_t[off[i] + pos[i]] : 0xffffffffu;
-      }
-    }
-  }
-  wave_lds_sync();
-  return out;
 }
 
+template <int R>
 __global__ void __launch_bounds__(256) k_query_merge(int64_t nq, int N, int kmax, int check_cert,
-                                                     RoundBufs b, const int64_t *__restrict__ rowid,
+                                                     int dedupe, RoundBufs b, const int64_t *__restrict__ rowid,
                                                      int64_t *out_ids, float *out_d, FilterPairArgs fp) {
-  extern __shared__ unsigned char smem_raw[];
-  // four wavefronts per work-group, each with its own LDS slice and query:
-  // two lists of kmax entries (the tournament's input and output), then the
-  // staging area of merge_pass_staged
+  // four wavefronts per work-group, each with its own LDS slice and query
+  __shared__ int smem[4 * merge_slice_words(R)];
   const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
-  unsigned char *mine = smem_raw + static_cast<size_t>(wave) * merge_slice_bytes(kmax);
-  double *buf_v = reinterpret_cast<double *>(mine);
-  uint32_t *buf_t = reinterpret_cast<uint32_t *>(mine + sizeof(double) * 2 * kmax);
-  double *stage_v = reinterpret_cast<double *>(mine + merge_lists_bytes(kmax));
-  uint32_t *stage_t = reinterpret_cast<uint32_t *>(stage_v + kMergeStage);
-  int *soff = reinterpret_cast<int *>(stage_t + kMergeStage);
-  int *sidx = soff + kWave * kMergeSlots + 1;
+  int *soff = smem + wave * merge_slice_words(R), *sidx = soff + kWave * kMergeSlots + 4;
+  uint32_t *rows = reinterpret_cast<uint32_t *>(sidx + kWave * kMergeSlots);
   const uint64_t lt = (1ull << lane) - 1ull;
   __shared__ int active_sh[4], fb_sh[4], fe_sh[4];
   // after a capacity overflow the item lists were never placed: nothing to merge
@@ -794,43 +666,34 @@ __global__ void __launch_bounds__(256) k_query_merge(int64_t nq, int N, int kmax
     }
     float tau_now = __builtin_inff();  // the query's tau after this merge (filter pairs below)
     if (n_it > 0) {
-      double *vals = buf_v, *ov = buf_v + kmax;
-      uint32_t *tags = buf_t, *ot = buf_t + kmax;
-      for (int i = lane; i < kmax; i += kWave) {
-        const double v = b.res_d2[q * kmax + i];  // loaded unconditionally, kept below `have`
-        const uint32_t t = static_cast<uint32_t>(b.res_row[q * kmax + i]);
-        vals[i] = i < have ? v : __builtin_inf();
-        tags[i] = i < have ? t : 0xffffffffu;
+      ExactKey best[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int i = lane * R + r;
+        const int64_t at = q * kmax + (i < kmax ? i : 0);  // loaded unconditionally, kept below `have`
+        const double v = b.res_d2[at];
+        const uint32_t t = static_cast<uint32_t>(b.res_row[at]);
+        best[r].d = static_cast<uint64_t>(__double_as_longlong(v));
+        best[r].row = t;
+        best[r] = pick(i < have && i < k, best[r], no_entry());
       }
-      wave_lds_sync();
-      int n_in = have < k ? have : k;
-      for (int it0 = 0; it0 < n_it;) {
+      for (int it0 = 0; it0 < n_it; it0 += kWave * kMergeSlots) {
         const int nb = n_it - it0 < kWave * kMergeSlots ? n_it - it0 : kWave * kMergeSlots;
-        int used = 0;
-        n_in = merge_pass_staged(q, N, kmax, k, b, it0, nb, vals, tags, n_in, ov, ot, lane, stage_v, stage_t, soff,
-                                 sidx, &used);
-        it0 += used;
-        double *sv = vals;
-        vals = ov;
-        ov = sv;
-        uint32_t *st = tags;
-        tags = ot;
-        ot = st;
+        merge_pass<R>(q, N, kmax, k, b, it0, nb, dedupe != 0, best, lane, soff, sidx, rows);
       }
-      for (int i = n_in + lane; i < kmax; i += kWave) {
-        vals[i] = __builtin_inf();
-        tags[i] = 0xffffffffu;
-      }
-      wave_lds_sync();
       int cnt = 0;
-      for (int i = 0; i < k; ++i) cnt += tags[i] != 0xffffffffu ? 1 : 0;
-      for (int i = lane; i < k; i += kWave) {
-        b.res_d2[q * kmax + i] = vals[i];
-        b.res_row[q * kmax + i] = static_cast<int32_t>(tags[i]);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int i = lane * R + r;
+        cnt += __popcll(__ballot(i < k && best[r].row != kNoRow));
+        if (i < k) {
+          b.res_d2[q * kmax + i] = __longlong_as_double(static_cast<long long>(best[r].d));
+          b.res_row[q * kmax + i] = static_cast<int32_t>(best[r].row);
+        }
       }
       float tau = __builtin_inff();
       if (cnt == k) {
-        double d = sqrt(vals[k - 1]);
+        const double d = sqrt(__longlong_as_double(static_cast<long long>(entry_of(best, k - 1).d)));
         tau = static_cast<float>(d);
         if (static_cast<double>(tau) < d) tau = nextafterf(tau, __builtin_inff());
       }
@@ -867,13 +730,17 @@ __global__ void __launch_bounds__(256) k_query_merge(int64_t nq, int N, int kmax
         n_fb += nr;
       }
       if (out_ids) {  // the batch's last merge: write the query's output row
-        for (int i = lane; i < kmax; i += kWave) {
-          const bool hit = i < cnt;
-          out_ids[q * kmax + i] = hit ? rowid[tags[i]] : -1;
-          out_d[q * kmax + i] = hit ? static_cast<float>(sqrt(vals[i])) : __builtin_inff();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const int i = lane * R + r;
+          if (i < kmax) {
+            const bool hit = i < cnt;
+            out_ids[q * kmax + i] = hit ? rowid[best[r].row] : -1;
+            out_d[q * kmax + i] = hit ? static_cast<float>(sqrt(__longlong_as_double(static_cast<long long>(best[r].d))))
+                                      : __builtin_inff();
+          }
         }
       }
-      wave_lds_sync();
       if (lane == 0) b.qitem_cnt[q] = nr;  // the rescan pass's items of this query (usually none)
     } else if (out_ids) {
       const int cnt = b.res_cnt[q];
@@ -1082,15 +949,16 @@ void launch_scatter(int64_t nq, int N, RoundBufs b, hipStream_t st) {
 
 void launch_query_merge(int64_t nq, int N, int kmax, bool check_cert, bool dedupe, RoundBufs b, hipStream_t st,
                         const int64_t *rowid, int64_t *ids, float *dists, const FilterPairArgs &fp) {
-  // LDS slice per wavefront: two lists of kmax entries and the staging area
-  size_t lds = 4 * merge_slice_bytes(kmax);
-  int64_t blocks = ceil_div(nq, 4);
-  int grid = static_cast<int>(blocks < 65536 ? blocks : 65536);
-  allow_lds(reinterpret_cast<const void *>(k_query_merge), lds);
+  const int64_t blocks = ceil_div(nq, 4);
+  const int grid = static_cast<int>(blocks < 65536 ? blocks : 65536);
   if (fp.plist && N > kMergePairsMaxN) fail(LEAFI_EINTERNAL, "query_merge: too many leaves for its pair selection");
-  (void)dedupe;  // the tournament keeps a row met twice once in every round
-  hipLaunchKernelGGL(k_query_merge, dim3(grid), dim3(256), lds, st, nq, N, kmax, check_cert ? 1 : 0, b, rowid,
-                     ids, dists, fp);
+  auto launch = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, nq, N, kmax, check_cert ? 1 : 0, dedupe ? 1 : 0, b, rowid,
+                       ids, dists, fp);
+  };
+  if (kmax <= kWave) launch(k_query_merge<1>);
+  else if (kmax <= 2 * kWave) launch(k_query_merge<2>);
+  else launch(k_query_merge<4>);
   LAUNCH_OK("query_merge");
 }
 
