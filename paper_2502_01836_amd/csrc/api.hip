@@ -319,6 +319,9 @@ constexpr double kPreallocLimit = 1.0 * (1 << 30);
 // exceed kMaxRerankKeys.
 constexpr int kMaxRerankKeys = 4096;
 constexpr int kFp32ChunkRows = 128;  // the FP32 scan streams 4 m bytes per row: finer tiles
+// Tiles that an all-pairs rescan should have before they grow longer (73 items
+// of 500 queries x 128 leaves of 7,800 rows: 128 rows 257 us, 256 202, 512 214).
+constexpr int kFp32ShapeTiles = 2048;
 int pick_chunk(const leafi_index *ix, int kprime, int pref) {
   int chunk = pref;
   while (chunk < (kRowAlign << (kChunkSizes - 1)) &&
@@ -353,6 +356,10 @@ PassShape pass_shape(const leafi_index *ix, bool bf16, int kprime, const ItemsEs
       if (groups * ix->total_chunks_for(c) >= static_cast<int64_t>(kShapeTiles) * ix->N) chunk = c;
   } else if (bf16 && one_leaf) {
     mq = 16;
+  } else if (!bf16 && est.all_pairs) {
+    const int64_t groups = std::max(ceil_div(est.items, mq), std::min<int64_t>(est.items, ix->N));
+    for (int c = chunk; c <= kChunkRows; c *= 2)
+      if (groups * ix->total_chunks_for(c) >= static_cast<int64_t>(kFp32ShapeTiles) * ix->N) chunk = c;
   }
   s.chunk = pick_chunk(ix, kprime, chunk);
   scan_geometry(bf16, kprime, mq, ix->m, &s.mq, &s.cap);
@@ -1018,7 +1025,9 @@ void allpairs_items(leafi_index *ix, int64_t nq, int k, int64_t n_items, hipStre
   if (n_fb > 0) {
     reset_for_fallback(ix, nq, st);
     launch_emit_fallback(n_fb, ix->N, views(w), st);
-    int64_t it2 = scan_round(ix, nq, false, default_kprime(k, false), k, st, nullptr);
+    RoundOpts rf;
+    rf.est = ItemsEst{n_fb, true};
+    int64_t it2 = scan_round(ix, nq, false, default_kprime(k, false), k, st, nullptr, -1, &rf);
     if (it2 > 0) consume(it2);
   }
 }

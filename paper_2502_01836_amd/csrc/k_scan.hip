@@ -475,8 +475,15 @@ __global__ void __launch_bounds__(256, QB >= 3 ? 2 : 4) k_scan_bf16(StoreView s,
   }
 }
 
+// The FP32 scan (rescans of what the BF16 scan could not certify, and searches
+// that ask for FP32): 64 rows a step, 16 lanes per row, direct differences.
+// Few items, so what bounds it is a tile's chain: rows are read a step
+// ahead of their use, in whole 128-byte lines, and the four rows of a lane
+// group are summed across it side by side by DPP.  73 items of an all-pairs
+// pass over 7,800-row leaves of 256: 480 -> 202 us with
+// tiles of 256 rows, the rescans of 1,024 queries over 10M series 44 -> 34.
 template <int EPL>
-__global__ void __launch_bounds__(256) k_scan_fp32(StoreView s, QueryView qv, RoundBufs b, int mq, int kprime,
+__global__ void __launch_bounds__(256, 2) k_scan_fp32(StoreView s, QueryView qv, RoundBufs b, int mq, int kprime,
                                                    int cap, uint64_t *cand) {
   constexpr int kWaves = 4;
   extern __shared__ uint64_t smem[];
@@ -501,6 +508,20 @@ __global__ void __launch_bounds__(256) k_scan_fp32(StoreView s, QueryView qv, Ro
     if (tt >= n_tiles) continue;
     const int t = static_cast<int>(tt);
     TileInfo ti = decode_tile(t, s, b, mq, s_leaf);
+    // Lane (rsel, sub) holds elements 32 i + 2 sub and + 1 of row 4 st + rsel:
+    // 16 lanes read 128 consecutive bytes of a row (and of a query in LDS) at
+    // once.  The next 64 rows are on their way while these are compared.
+    constexpr int kBufs = EPL <= 16 ? 2 : 1;  // (past m = 256 two would not fit the registers)
+    float2 x[kBufs][4][EPL / 2];
+    auto load = [&](float2(&v)[4][EPL / 2], int64_t base) {
+#pragma unroll
+      for (int st = 0; st < 4; ++st) {
+        const float2 *xp = reinterpret_cast<const float2 *>(s.x32 + (base + 16 * wave + 4 * st + rsel) * m) + sub;
+#pragma unroll
+        for (int i = 0; i < EPL / 2; ++i) v[st][i] = xp[16 * i];
+      }
+    };
+    load(x[0], ti.r0);
     if (threadIdx.x < mq) {
       const int j = threadIdx.x;
       cnt[j] = 0;
@@ -512,36 +533,34 @@ __global__ void __launch_bounds__(256) k_scan_fp32(StoreView s, QueryView qv, Ro
       qs[e] = qv.q32[static_cast<int64_t>(b.item_q[ti.p0 + j]) * m + (e - j * m)];
     }
     __syncthreads();
-    for (int64_t base = ti.r0; base < ti.r1; base += 64) {
-      float x[4][EPL];
+    auto compare = [&](const float2(&v)[4][EPL / 2], int64_t base) {
+      for (int j = 0; j < ti.nqt; ++j) {
+        const float2 *qp = reinterpret_cast<const float2 *>(qs + j * m) + sub;
+        float p[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-      for (int st = 0; st < 4; ++st) {
-        const float *xp = s.x32 + (base + 16 * wave + 4 * st + rsel) * m + sub * EPL;
+        for (int i = 0; i < EPL / 2; ++i) {
+          const float2 y = qp[16 * i];
 #pragma unroll
-        for (int e = 0; e < EPL; e += 2) {
-          float2 v = *reinterpret_cast<const float2 *>(xp + e);
-          x[st][e] = v.x;
-          x[st][e + 1] = v.y;
-        }
-      }
-#pragma unroll
-      for (int st = 0; st < 4; ++st) {
-        int64_t row = base + 16 * wave + 4 * st + rsel;
-        for (int j = 0; j < ti.nqt; ++j) {
-          const float *qp = qs + j * m + sub * EPL;
-          float p = 0.0f;
-#pragma unroll
-          for (int e = 0; e < EPL; ++e) {
-            float d = qp[e] - x[st][e];
-            p = fmaf(d, d, p);
+          for (int st = 0; st < 4; ++st) {
+            const float d0 = y.x - v[st][i].x, d1 = y.y - v[st][i].y;
+            p[st] = fmaf(d0, d0, p[st]);
+            p[st] = fmaf(d1, d1, p[st]);
           }
-          p += __shfl_xor(p, 8, 16);
-          p += __shfl_xor(p, 4, 16);
-          p += __shfl_xor(p, 2, 16);
-          p += __shfl_xor(p, 1, 16);
-          if (sub == 0 && row < ti.real_end) append_key(keys, cnt, thr, j, cap, make_key(p, static_cast<uint32_t>(row)));
         }
+#pragma unroll
+        for (int st = 0; st < 4; ++st) {
+          p[st] += u2f(lane_xor<8>(f2u(p[st]), lane));
+          p[st] += u2f(lane_xor<4>(f2u(p[st]), lane));
+          p[st] += u2f(lane_xor<2>(f2u(p[st]), lane));
+          p[st] += u2f(lane_xor<1>(f2u(p[st]), lane));
+        }
+        // lane `sub` = 0 .. 3 of a row group keeps its row st = sub
+        const float d2 = sub == 0 ? p[0] : sub == 1 ? p[1] : sub == 2 ? p[2] : p[3];
+        const int64_t row = base + 16 * wave + 4 * sub + rsel;
+        if (sub < 4 && row < ti.real_end) append_key(keys, cnt, thr, j, cap, make_key(d2, static_cast<uint32_t>(row)));
       }
+    };
+    auto cut = [&]() {
       __syncthreads();
       // every count read at once (mq <= 64), then this wavefront's lists
       uint64_t over =
@@ -552,6 +571,17 @@ __global__ void __launch_bounds__(256) k_scan_fp32(StoreView s, QueryView qv, Ro
         compact_list(keys, cnt, thr, j, cap, kpl[j], lane);
       }
       __syncthreads();
+    };
+    for (int64_t base = ti.r0; base < ti.r1; base += 64 * kBufs) {
+#pragma unroll
+      for (int u = 0; u < kBufs; ++u) {
+        const int64_t at = base + 64 * u;
+        if (at >= ti.r1) break;  // uniform
+        if (kBufs > 1 && at + 64 < ti.r1) load(x[(u + 1) % kBufs], at + 64);
+        compare(x[u], at);
+        if (kBufs == 1 && at + 64 < ti.r1) load(x[0], at + 64);
+        cut();
+      }
     }
     finish_tile(keys, cnt, thr, kpl, t, mq, ti.nqt, cap, kprime, ti.r0, wave, kWaves, lane, cand);
     __syncthreads();
