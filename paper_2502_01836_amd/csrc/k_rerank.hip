@@ -23,7 +23,7 @@ namespace {
 
 // Selection instead of a full sort when at most kSelectMax of at most
 // 64 * kSelectPerLane chunk candidates are wanted.
-constexpr int kSelectMax = 16;
+constexpr int kSelectMax = kCandFill;
 constexpr int kSelectPerLane = 16;
 
 // One wavefront per item.  LDS: merged keys [P], then per candidate the fp32
@@ -32,7 +32,8 @@ constexpr int kSelectPerLane = 16;
 // into buf (ascending, kKeyMax past the last real key): kp rounds of a
 // the keys above the previous one (keys are unique), U per lane in registers
 // (unconditional loads of clamped entries, so all of a lane's loads are in
-// flight together; n >= kprime >= kp >= 1, so entry 0 exists; n <= 64 U).
+// flight together; the first kp <= kCandFill slots of each list, n = lists x
+// kp >= 1 in all, so entry 0 exists; n <= 64 U).
 template <int U>
 __device__ inline void select_keys(const uint64_t *__restrict__ cand, int64_t t0, int G, int g, int mq, int j,
                                    int kprime, int kp, int n, int lane, uint64_t *buf) {
@@ -41,8 +42,8 @@ __device__ inline void select_keys(const uint64_t *__restrict__ cand, int64_t t0
   for (int u = 0; u < U; ++u) {
     const int e = lane + u * kWave;
     const int ec = e < n ? e : 0;
-    const int c = ec / kprime;
-    const uint64_t v = cand[((t0 + static_cast<int64_t>(c) * G + g) * mq + j) * kprime + (ec - c * kprime)];
+    const int c = ec / kp;
+    const uint64_t v = cand[((t0 + static_cast<int64_t>(c) * G + g) * mq + j) * kprime + (ec - c * kp)];
     mine[u] = e < n ? v : kKeyMax;
   }
   uint64_t prev = 0;
@@ -127,8 +128,12 @@ __global__ void __launch_bounds__(256) k_query_bound(StoreView s, QueryView qv, 
 #pragma unroll
         for (int u = 0; u < kStep; ++u) v[u] = static_cast<uint32_t>(list[e0 + u < kp ? e0 + u : kp - 1] >> 32);
         int n = 0;
+        bool below = true;  // (past the list's end its slots hold anything)
 #pragma unroll
-        for (int u = 0; u < kStep; ++u) n += e0 + u < kp && v[u] < top && v[u] < f2u(__builtin_inff()) ? 1 : 0;
+        for (int u = 0; u < kStep; ++u) {
+          below = below && e0 + u < kp && v[u] < top && v[u] < f2u(__builtin_inff());
+          n += below ? 1 : 0;
+        }
         if (n == 0) break;
         const int at = __hip_atomic_fetch_add(&s_n, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 #pragma unroll
@@ -349,7 +354,7 @@ __global__ void __launch_bounds__(256, 3) k_item_rerank(StoreView s, QueryView q
       // the query's own candidate count (its lists hold kp keys in kprime slots)
       const int kp = item_kprime(b.kp_query, kprime, k, bf16 != 0);
       const int PKi = pow2_at_least(kp < 2 ? 2 : kp);
-      const int n = C * kprime;
+      const int n = C * kp;
       const double dq = bf16_delta(static_cast<double>(qn_q), m);
       uint64_t best[R];  // key e in lane e / R, register e mod R
       if (kp <= kSelectMax && n <= kWave * kSelectPerLane) {
@@ -389,6 +394,25 @@ __global__ void __launch_bounds__(256, 3) k_item_rerank(StoreView s, QueryView q
               const uint64_t x = cand[((t0 + static_cast<int64_t>(c) * G + g) * mq + j) * kprime + (e < kp ? e : 0)];
               w[v][r] = in ? x : kKeyMax;
             }
+#pragma unroll
+          for (int v = 0; v < kLists; ++v) {
+            // nothing past a list's end: a slot is before it if neither it
+            // nor any lower slot (a higher register or lane) holds kKeyMax
+            bool end = false;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+              const int e = kCap - 1 - (lane * R + r);
+              end |= e < kp && w[v][r] == kKeyMax;
+            }
+            const uint64_t ends = __ballot(end);
+            bool past = lane < kWave - 1 && (ends >> (lane + 1)) != 0;
+#pragma unroll
+            for (int r = R - 1; r >= 0; --r) {
+              const int e = kCap - 1 - (lane * R + r);
+              past |= e < kp && w[v][r] == kKeyMax;
+              if (past) w[v][r] = kKeyMax;
+            }
+          }
 #pragma unroll
           for (int v = 0; v < kLists; ++v) {
             const uint32_t head =

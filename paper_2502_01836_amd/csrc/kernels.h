@@ -239,7 +239,10 @@ void launch_leaf_scan_scatter(int64_t nq, int N, const int64_t *leaf_off, int mq
                               hipStream_t st);
 
 // Leaf scan over all tiles; keeps the kprime best (key = dist^2 bits, row)
-// per (tile, query slot) in cand.
+// per (tile, query slot) in cand: ascending, ended by kKeyMax unless all
+// kprime slots are taken.  Past that end the first kCandFill slots hold
+// kKeyMax, the rest nothing in particular.
+constexpr int kCandFill = 16;
 void launch_scan_bf16(StoreView s, QueryView q, RoundBufs b, int mq, int kprime, uint64_t *cand, int grid,
                       hipStream_t st, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 void launch_scan_fp32(StoreView s, QueryView q, RoundBufs b, int mq, int kprime, uint64_t *cand, int grid,

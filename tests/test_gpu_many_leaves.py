@@ -93,3 +93,30 @@ def test_bounds_skip_no_result(nq, k):
     xs, qs = O.znorm(raw), O.znorm(q)
     ref_ids, ref_d = O.knn(xs, qs, k)
     assert_knn_parity(ids.cpu().numpy(), d.cpu().numpy(), ref_ids, ref_d, xs, qs)
+
+
+@pytest.mark.parametrize("k,nq", [(40, 3), (256, 3), (5, 20)])
+def test_lists_end_where_their_keys_do(k, nq):
+    """Lists of far fewer keys than their slots, over a workspace whose slots
+    hold an earlier batch's full lists: nothing past a list's end is read."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2502_01836_amd as pkg
+    pkg.load()
+    raw = W.random_walk(9000, 64, seed=77)
+    q, _, _ = W.noisy_queries(raw, 40, 0.4, 78, 79)
+    ix = pkg.Index().build(torch.from_numpy(raw).cuda(), leaf_capacity=100, n_segments=S)
+    qd = torch.from_numpy(q).cuda()
+    xs, qs = O.znorm(raw), O.znorm(q)
+    want_ids, want_d = O.knn(xs, qs, 256)
+    ix.search(qd, k=256, k_max=256, use_filters=False, schedule=(0,))  # tau +inf: full lists everywhere
+    for schedule in ((1, 0), (2, 5, 0)):
+        ids, d = ix.search(qd[:nq], k=k, k_max=k, use_filters=False, schedule=schedule)
+        torch.cuda.synchronize()
+        assert_knn_parity(ids.cpu().numpy(), d.cpu().numpy(), want_ids[:nq, :k], want_d[:nq, :k], xs, qs[:nq])
+    ks = torch.from_numpy(np.resize([1, 40, 256], 40).astype(np.int32)).cuda()
+    ids, d = ix.search(qd, k=ks, k_max=256, use_filters=False, schedule=(1, 0))
+    torch.cuda.synchronize()
+    for i, kk in enumerate(ks.cpu().tolist()):
+        assert_knn_parity(ids[i:i + 1, :kk].cpu().numpy(), d[i:i + 1, :kk].cpu().numpy(), want_ids[i:i + 1, :kk],
+                          want_d[i:i + 1, :kk], xs, qs[i:i + 1])
