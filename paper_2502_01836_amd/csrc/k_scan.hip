@@ -245,10 +245,22 @@ __device__ inline void append_key(uint64_t *keys, int *cnt, const uint64_t *thr,
 // 1,024 queries over 10M series 1.37 -> 1.23.
 // Slots of lists past the tile's queries (j >= nqt) belong to no item and
 // are never read: they are not written.
-template <typename K>
+// With kRare the empty lists' slots are written by the whole work-group at
+// once.
+template <bool kRare, typename K>
 __device__ inline void finish_tile(K *keys, int *cnt, K *thr, const int *kpl, int t, int mq, int nqt, int cap,
                                    int kprime, int64_t r0, int wave, int nwaves, int lane, uint64_t *cand) {
+  uint64_t some = ~0ull;
+  if constexpr (kRare) {
+    const int fill = min(kprime, kCandFill);
+    for (int i = threadIdx.x; i < nqt * kCandFill; i += nwaves * kWave) {
+      const int j = i / kCandFill, slot = i % kCandFill;
+      if (cnt[j] == 0 && slot < fill) cand[(static_cast<int64_t>(t) * mq + j) * kprime + slot] = kKeyMax;
+    }
+    some = __ballot(lane < nqt && cnt[lane < nqt ? lane : 0] > 0);
+  }
   for (int j = wave; j < nqt; j += nwaves) {
+    if (kRare && ((some >> j) & 1) == 0) continue;
     uint64_t *out = cand + (static_cast<int64_t>(t) * mq + j) * kprime;
     compact_list(keys, cnt, thr, j, cap, kpl[j], lane);
     // only the first cnt[j] entries are candidates; the list may hold fewer
@@ -273,7 +285,13 @@ __device__ __forceinline__ void load_rows(const uint16_t *x16, int64_t base, int
 
 // One 64-row block: its squared norms, the prefetch of the next block into
 // `nxt`, MFMAs on `cur`, candidate appends, then list maintenance.
-template <int KS, int QB>
+// With kRare (rounds whose tiles share a falling bound: few rows are
+// candidates, and 16 rows x 16 queries mostly hold none) a least distance
+// above every threshold ends the epilogue; where candidates are common that
+// test only adds to it (an all-pairs pass 706 -> 731 us with it).  The second
+// round of 4,096 queries over ragged leaves of 96, bound by these
+// instructions: 3.60 -> 2.65 ms; of 1,024 over 10M x 256: 1.23 -> 1.20.
+template <int KS, int QB, bool kRare>
 __device__ __forceinline__ void scan_block(const StoreView &s, const TileInfo &ti, int64_t base, bf16x8 (&cur)[KS],
                                            bf16x8 (&nxt)[KS], int64_t pre, const uint16_t *qs, int qstride,
                                            const float (&qn)[QB], uint32_t *keys, int *cnt, uint32_t *thr, int cap,
@@ -299,30 +317,37 @@ __device__ __forceinline__ void scan_block(const StoreView &s, const TileInfo &t
       acc[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur[k], bq, acc[qb], 0, 0, 0);
     }
   // epilogue: lane holds rows rowc..rowc+3 for query column (lane & 15)
+  const int row0 = static_cast<int>(rowc - ti.r0), rows = static_cast<int>(ti.real_end - ti.r0);  // within the tile
   const float xr[4] = {xn.x, xn.y, xn.z, xn.w};
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     const int j = 16 * qb + (lane & 15);
-    if (j < ti.nqt) {
-      // the lane's (up to 4) appends take one LDS atomic: one round trip per
-      // block instead of one per row
-      const uint32_t tj = thr[j];
-      uint32_t kk[4];
-      int n = 0;
+    if constexpr (kRare) {
+      // (lists past the tile's queries have threshold 0; a key below the
+      // threshold is below its distance step or shares it)
+      float least = __builtin_inff();
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t row = rowc + r;
-        const float d2 = fmaxf(qn[qb] + xr[r] - 2.0f * acc[qb][r], 0.0f);
-        kk[r] = make_key32(d2, static_cast<uint32_t>(row - ti.r0));
-        if (!(row < ti.real_end && kk[r] < tj)) kk[r] = kKey32Max;
-        n += kk[r] != kKey32Max;
-      }
-      if (n > 0) {
-        uint32_t *dst = keys + static_cast<int64_t>(j) * (cap + 1) + atomicAdd(cnt + j, n);
+      for (int r = 0; r < 4; ++r) least = fminf(least, qn[qb] + xr[r] - 2.0f * acc[qb][r]);
+      if (__ballot(f2u(fmaxf(least, 0.0f)) >> kDropBits <= thr[j] >> kLocalBits) == 0) continue;
+    }
+    if (j >= ti.nqt) continue;
+    const uint32_t tj = thr[j];
+    // the lane's (up to 4) appends take one LDS atomic: one round trip per
+    // block instead of one per row
+    uint32_t kk[4];
+    int n = 0;
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (kk[r] != kKey32Max) *dst++ = kk[r];
-      }
+    for (int r = 0; r < 4; ++r) {
+      const float d2 = fmaxf(qn[qb] + xr[r] - 2.0f * acc[qb][r], 0.0f);
+      kk[r] = make_key32(d2, static_cast<uint32_t>(row0 + r));
+      if (!(row0 + r < rows && kk[r] < tj)) kk[r] = kKey32Max;
+      n += kk[r] != kKey32Max;
+    }
+    if (n > 0) {
+      uint32_t *dst = keys + static_cast<int64_t>(j) * (cap + 1) + atomicAdd(cnt + j, n);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (kk[r] != kKey32Max) *dst++ = kk[r];
     }
   }
   // Lists are checked after every block, or with room for two blocks of
@@ -342,7 +367,7 @@ __device__ __forceinline__ void scan_block(const StoreView &s, const TileInfo &t
   lds_barrier();
 }
 
-template <int KS, int QB>
+template <int KS, int QB, bool kRare>
 __global__ void __launch_bounds__(256, QB >= 3 ? 2 : 4) k_scan_bf16(StoreView s, QueryView qv, RoundBufs b,
                                                                    int kprime, int cap, uint64_t *cand) {
   constexpr int MQ = 16 * QB;
@@ -389,7 +414,7 @@ __global__ void __launch_bounds__(256, QB >= 3 ? 2 : 4) k_scan_bf16(StoreView s,
     if (threadIdx.x < MQ) {
       const int j = threadIdx.x;
       cnt[j] = 0;
-      uint32_t t0 = kKey32Max;
+      uint32_t t0 = j < ti.nqt ? kKey32Max : 0u;
       int kp = kprime;
       if (j < ti.nqt) {
         const int64_t qq = b.item_q[ti.p0 + j];
@@ -433,9 +458,9 @@ __global__ void __launch_bounds__(256, QB >= 3 ? 2 : 4) k_scan_bf16(StoreView s,
     const int room = pair ? 128 : 64;
     if constexpr (kBufs == 2) {
       for (int64_t base = ti.r0; base < ti.r1; base += 128) {
-        scan_block<KS, QB>(s, ti, base, a0, a1, base + 64, qs, qstride, qn, keys, cnt, thr, cap, kpl, !pair, room,
+        scan_block<KS, QB, kRare>(s, ti, base, a0, a1, base + 64, qs, qstride, qn, keys, cnt, thr, cap, kpl, !pair, room,
                            wave, lane);
-        scan_block<KS, QB>(s, ti, base + 64, a1, a0, base + 128 < ti.r1 ? base + 128 : base + 64, qs, qstride, qn,
+        scan_block<KS, QB, kRare>(s, ti, base + 64, a1, a0, base + 128 < ti.r1 ? base + 128 : base + 64, qs, qstride, qn,
                            keys, cnt, thr, cap, kpl, true, room, wave, lane);
       }
     } else {
@@ -444,19 +469,19 @@ __global__ void __launch_bounds__(256, QB >= 3 ? 2 : 4) k_scan_bf16(StoreView s,
       // group of four may end after its second
       auto pre = [&](int64_t row) { return row < ti.r1 ? row : ti.r0; };
       for (int64_t base = ti.r0; base < ti.r1; base += 256) {
-        scan_block<KS, QB>(s, ti, base, a0, a3, pre(base + 192), qs, qstride, qn, keys, cnt, thr, cap, kpl, !pair,
+        scan_block<KS, QB, kRare>(s, ti, base, a0, a3, pre(base + 192), qs, qstride, qn, keys, cnt, thr, cap, kpl, !pair,
                            room, wave, lane);
-        scan_block<KS, QB>(s, ti, base + 64, a1, a0, pre(base + 256), qs, qstride, qn, keys, cnt, thr, cap, kpl, true,
+        scan_block<KS, QB, kRare>(s, ti, base + 64, a1, a0, pre(base + 256), qs, qstride, qn, keys, cnt, thr, cap, kpl, true,
                            room, wave, lane);
         if (base + 128 < ti.r1) {  // uniform
-          scan_block<KS, QB>(s, ti, base + 128, a2, a1, pre(base + 320), qs, qstride, qn, keys, cnt, thr, cap, kpl,
+          scan_block<KS, QB, kRare>(s, ti, base + 128, a2, a1, pre(base + 320), qs, qstride, qn, keys, cnt, thr, cap, kpl,
                              !pair, room, wave, lane);
-          scan_block<KS, QB>(s, ti, base + 192, a3, a2, pre(base + 384), qs, qstride, qn, keys, cnt, thr, cap, kpl,
+          scan_block<KS, QB, kRare>(s, ti, base + 192, a3, a2, pre(base + 384), qs, qstride, qn, keys, cnt, thr, cap, kpl,
                              true, room, wave, lane);
         }
       }
     }
-    finish_tile(keys, cnt, thr, kpl, t, MQ, ti.nqt, cap, kprime, ti.r0, wave, kWaves, lane, cand);
+    finish_tile<kRare>(keys, cnt, thr, kpl, t, MQ, ti.nqt, cap, kprime, ti.r0, wave, kWaves, lane, cand);
     __syncthreads();
     // A list of k keys or more bounds its query's k-th distance: k distinct
     // rows lie within the k-th key's distance (the key's step rounded up).
@@ -587,7 +612,7 @@ __global__ void __launch_bounds__(256, 2) k_scan_fp32(StoreView s, QueryView qv,
         cut();
       }
     }
-    finish_tile(keys, cnt, thr, kpl, t, mq, ti.nqt, cap, kprime, ti.r0, wave, kWaves, lane, cand);
+    finish_tile<false>(keys, cnt, thr, kpl, t, mq, ti.nqt, cap, kprime, ti.r0, wave, kWaves, lane, cand);
     __syncthreads();
   }
 }
@@ -632,12 +657,12 @@ size_t scan_bf16_lds(int mq, int cap, int m) {
          static_cast<size_t>(mq) * (m + 8) * 2 + 16;
 }
 
-template <int KS, int QB>
+template <int KS, int QB, bool kRare>
 void scan_bf16_inst(StoreView s, QueryView q, RoundBufs b, int kprime, int cap, uint64_t *cand, int grid,
                     hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   constexpr int MQ = 16 * QB;
   const size_t lds = scan_bf16_lds(MQ, cap, 32 * KS);
-  auto kern = k_scan_bf16<KS, QB>;
+  auto kern = k_scan_bf16<KS, QB, kRare>;
   allow_lds(reinterpret_cast<const void *>(kern), lds);
   grid = resident_grid(kern, lds, grid);
   if (e0 || e1)  // start / stop timestamps of this dispatch itself
@@ -647,18 +672,18 @@ void scan_bf16_inst(StoreView s, QueryView q, RoundBufs b, int kprime, int cap, 
   LAUNCH_OK("scan_bf16");
 }
 
-template <int QB>
+template <int QB, bool kRare>
 void scan_bf16_ks(int ks, StoreView s, QueryView q, RoundBufs b, int kprime, int cap, uint64_t *cand, int grid,
                   hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   switch (ks) {
-    case 1: scan_bf16_inst<1, QB>(s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
-    case 2: scan_bf16_inst<2, QB>(s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
-    case 3: scan_bf16_inst<3, QB>(s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
-    case 4: scan_bf16_inst<4, QB>(s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
-    case 5: scan_bf16_inst<5, QB>(s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
-    case 6: scan_bf16_inst<6, QB>(s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
-    case 7: scan_bf16_inst<7, QB>(s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
-    case 8: scan_bf16_inst<8, QB>(s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
+    case 1: scan_bf16_inst<1, QB, kRare>(s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
+    case 2: scan_bf16_inst<2, QB, kRare>(s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
+    case 3: scan_bf16_inst<3, QB, kRare>(s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
+    case 4: scan_bf16_inst<4, QB, kRare>(s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
+    case 5: scan_bf16_inst<5, QB, kRare>(s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
+    case 6: scan_bf16_inst<6, QB, kRare>(s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
+    case 7: scan_bf16_inst<7, QB, kRare>(s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
+    case 8: scan_bf16_inst<8, QB, kRare>(s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
     default: fail(LEAFI_EINVAL, "bf16 scan supports m <= 256");
   }
 }
@@ -714,12 +739,14 @@ void launch_scan_bf16(StoreView s, QueryView q, RoundBufs b, int mq, int kprime,
   scan_geometry(true, kprime, mq, s.m, &mq2, &cap);
   if (mq != mq2) fail(LEAFI_EINTERNAL, "scan_bf16: tile geometry mismatch");
   if (b.chunk > (1 << kLocalBits)) fail(LEAFI_EINTERNAL, "scan_bf16: tiles of at most 4096 rows");
-  int ks = s.m / 32;
+  const int ks = s.m / 32;
+  const bool rare = b.use_tau == 2;  // (the smaller tiles' registers are full without the test)
+  auto launch = [&](auto scan) { scan(ks, s, q, b, kprime, cap, cand, grid, st, e0, e1); };
   switch (mq) {
-    case 16: scan_bf16_ks<1>(ks, s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
-    case 32: scan_bf16_ks<2>(ks, s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
-    case 48: scan_bf16_ks<3>(ks, s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
-    default: scan_bf16_ks<4>(ks, s, q, b, kprime, cap, cand, grid, st, e0, e1); break;
+    case 16: launch(scan_bf16_ks<1, false>); break;
+    case 32: launch(scan_bf16_ks<2, false>); break;
+    case 48: launch(rare ? scan_bf16_ks<3, true> : scan_bf16_ks<3, false>); break;
+    default: launch(rare ? scan_bf16_ks<4, true> : scan_bf16_ks<4, false>); break;
   }
 }
 
