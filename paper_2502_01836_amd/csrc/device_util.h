@@ -114,6 +114,11 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
 __device__ __forceinline__ uint64_t wave_min_key(uint64_t v) { return wave_min_u64(v); }
 __device__ __forceinline__ uint32_t wave_min_key(uint32_t v) { return wave_min_u32(v); }
 
+// Work-group barrier for LDS traffic only: waits for this wave's LDS
+// operations, then s_barrier.  Unlike __syncthreads it does not drain
+// outstanding global loads and stores, which stay in flight across it.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // Exclusive prefix sum over a work-group of NT threads (NT / 64 <= 64
 // wavefronts): wavefront scans by shuffles, then one scan of the wavefront
 // totals.  `sh` holds NT / 64 values of LDS; `total` receives the sum.  Every

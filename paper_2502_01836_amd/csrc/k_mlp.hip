@@ -699,10 +699,11 @@ __device__ inline void train_store(float *wf, int m, int h, const float (&W)[kTr
 // the mean squared error with learning rate lr.  Returns the sum of squared
 // errors (valid in thread 0).  Every thread of the work-group calls it.
 // Hidden units >= h have zero weights, b1 and w2 and are never updated
-// (their Delta is zero), so they add nothing.
-template <int MT, bool update>
+// (their Delta is zero), so they add nothing.  done(ti) is called once input
+// tile ti of W is updated.
+template <int MT, bool update, typename Done>
 __device__ inline float train_step(float (&W)[kTrainHT][MT][4], float (&b1r)[kTrainHT], float (&w2r)[kTrainHT], int h,
-                                   int nb, float lr, const TrainLds &t) {
+                                   int nb, float lr, const TrainLds &t, Done done) {
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int q = lane >> 4, col = lane & 15;
   const bool act = 16 * kTrainHT * wave < h;  // any hidden unit of this wavefront in use
@@ -739,7 +740,7 @@ __device__ inline float train_step(float (&W)[kTrainHT][MT][4], float (&b1r)[kTr
       for (int o = 8; o > 0; o >>= 1) p += __shfl_xor(p, o, kWave);
       if (col == 0) t.red[wave * kTrainB + 16 * tb + 4 * q + r] = p;
     }
-  __syncthreads();
+  lds_barrier();
   if (threadIdx.x < kTrainB) {
     const int c = threadIdx.x;
     float yh = t.scal[0];
@@ -748,10 +749,8 @@ __device__ inline float train_step(float (&W)[kTrainHT][MT][4], float (&b1r)[kTr
     t.gy[c] = 2.0f * e / static_cast<float>(nb);
     t.sq[c] = e * e;
   }
-  __syncthreads();
-  float loss = 0.0f;
-  if (threadIdx.x == 0)
-    for (int c = 0; c < nb; ++c) loss += t.sq[c];
+  lds_barrier();
+  const float loss = wave == 0 ? wave_sum(t.sq[lane]) : 0.0f;  // (rows past nb have none)
   if (!update) return loss;
   // Delta = dL/dZ into the forward tiles; gradients of w2 and b1
   float gw2[kTrainHT], gb1[kTrainHT];
@@ -798,6 +797,7 @@ __device__ inline float train_step(float (&W)[kTrainHT][MT][4], float (&b1r)[kTr
       for (int i = 0; i < kTrainHT; ++i)
 #pragma unroll
         for (int r = 0; r < 4; ++r) W[i][ti][r] = fmaf(-lr, G[i][r], W[i][ti][r]);
+      done(ti);
     }
   }
   __builtin_amdgcn_sched_barrier(0);
@@ -806,11 +806,10 @@ __device__ inline float train_step(float (&W)[kTrainHT][MT][4], float (&b1r)[kTr
     b1r[i] = fmaf(-lr, gb1[i], b1r[i]);
     w2r[i] = fmaf(-lr, gw2[i], w2r[i]);
   }
-  __syncthreads();  // every thread has read b2 and gy
-  if (threadIdx.x == 0) {
-    float gs = 0.0f;
-    for (int c = 0; c < nb; ++c) gs += t.gy[c];
-    t.scal[0] = fmaf(-lr, gs, t.scal[0]);
+  lds_barrier();  // every thread has read b2 and gy
+  if (wave == 0) {
+    const float gs = wave_sum(t.gy[lane]);
+    if (lane == 0) t.scal[0] = fmaf(-lr, gs, t.scal[0]);
   }
   return loss;
 }
@@ -829,6 +828,12 @@ __device__ inline void train_stage(const float *xq, const int32_t *qidx, const f
   __syncthreads();
 }
 
+// One SGD step per filter.  What bounds it is the weights' way to the
+// registers and back (270 MB each way for 1,024 filters 256 -> 256 -> 1) and
+// the matrix products (half that time), one work-group per CU: so the rows
+// and all of W1 are requested at once, the forward pass starts on the input
+// tiles that have arrived, and each tile is stored as soon as the backward
+// pass has updated it: 227 us, with the four phases one after the other 374.
 template <int MT>
 __global__ void __launch_bounds__(kTrainThreads, 1) k_mlp_sgd_step_mfma(float *w, int m, int h, const float *x,
                                                                         const float *y, int batch, float lr,
@@ -838,13 +843,76 @@ __global__ void __launch_bounds__(kTrainThreads, 1) k_mlp_sgd_step_mfma(float *w
   const int f = blockIdx.x;
   const int64_t P = static_cast<int64_t>(h) * m + 2 * h + 1;
   float *wf = w + f * P;
+  const float *xf = x + static_cast<int64_t>(f) * batch * m, *yf = y + static_cast<int64_t>(f) * batch;
+  const int q = (threadIdx.x & (kWave - 1)) >> 4;
+  // the batch's rows, 16 bytes per thread and piece (rows past it zero)
+  constexpr int kRow4 = 4 * MT, kPieces = (kTrainB * kRow4 + kTrainThreads - 1) / kTrainThreads;
+  const bool wide = reinterpret_cast<uintptr_t>(xf) % 16 == 0;  // uniform
+  float4 xv[kPieces];
+  if (wide) {
+#pragma unroll
+    for (int u = 0; u < kPieces; ++u) {
+      const int e = threadIdx.x + u * kTrainThreads;
+      const bool in = e < batch * kRow4;
+      const float4 v = reinterpret_cast<const float4 *>(xf)[in ? e : 0];
+      xv[u] = in ? v : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
+  }
+  const float yv = threadIdx.x < batch ? yf[threadIdx.x] : 0.0f;
+  const float b2 = wf[P - 1];
   float W[kTrainHT][MT][4], b1r[kTrainHT], w2r[kTrainHT];
-  train_load<MT>(wf, m, h, W, b1r, w2r);
-  if (threadIdx.x == 0) t.scal[0] = wf[P - 1];
-  train_stage(x + static_cast<int64_t>(f) * batch * m, nullptr, y + static_cast<int64_t>(f) * batch, batch, m, t);
-  const float sse = train_step<MT, true>(W, b1r, w2r, h, batch, lr, t);
-  __syncthreads();
-  train_store<MT>(wf, m, h, W, b1r, w2r);
+  uint32_t at[kTrainHT];  // this lane's byte offset in W1, past its end for units >= h: those read 0
+  const __amdgpu_buffer_rsrc_t w1 = __builtin_amdgcn_make_buffer_rsrc(wf, 0, 4 * m * h, 0x00027000);
+#pragma unroll
+  for (int i = 0; i < kTrainHT; ++i) {
+    const int j = train_unit(i);
+    at[i] = j < h ? 4u * (4 * q * h + j) : 0x7f000000u;
+    b1r[i] = j < h ? wf[static_cast<int64_t>(h) * m + j] : 0.0f;
+    w2r[i] = j < h ? wf[static_cast<int64_t>(h) * m + h + j] : 0.0f;
+  }
+#pragma unroll
+  for (int ti = 0; ti < MT; ++ti)
+#pragma unroll
+    for (int i = 0; i < kTrainHT; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        W[i][ti][r] = __builtin_bit_cast(
+            float, __builtin_amdgcn_raw_buffer_load_b32(w1, at[i], 4 * (16 * ti + r) * h, 0));
+  __builtin_amdgcn_sched_barrier(0);
+  if (wide) {
+#pragma unroll
+    for (int u = 0; u < kPieces; ++u) {
+      const int e = threadIdx.x + u * kTrainThreads, c = e / kRow4, i4 = e - c * kRow4;
+      if (c < kTrainB) {
+        float *d = t.xb + c * t.ldx + 4 * i4;
+        d[0] = xv[u].x;
+        d[1] = xv[u].y;
+        d[2] = xv[u].z;
+        d[3] = xv[u].w;
+      }
+    }
+    if (threadIdx.x < kTrainB) t.yt[threadIdx.x] = yv;
+  } else {
+    train_stage(xf, nullptr, yf, batch, m, t);
+  }
+  if (threadIdx.x == 0) t.scal[0] = b2;
+  lds_barrier();
+  const float sse = train_step<MT, true>(W, b1r, w2r, h, batch, lr, t, [&](int ti) {
+#pragma unroll
+    for (int i = 0; i < kTrainHT; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, W[i][ti][r]), w1, at[i],
+                                              4 * (16 * ti + r) * h, 0);
+  });
+#pragma unroll
+  for (int i = 0; i < kTrainHT; ++i) {
+    const int j = train_unit(i);
+    if (j < h && q == 0) {
+      wf[static_cast<int64_t>(h) * m + j] = b1r[i];
+      wf[static_cast<int64_t>(h) * m + h + j] = w2r[i];
+    }
+  }
   if (threadIdx.x == 0) {
     wf[P - 1] = t.scal[0];
     if (loss_out) loss_out[f] = sse / static_cast<float>(batch);
@@ -905,7 +973,7 @@ __global__ void __launch_bounds__(kTrainThreads, 1) k_mlp_train_mfma(TrainArgs a
       }
       __syncthreads();
       train_stage(a.xq, bq, by, nb, m, t);
-      train_step<MT, true>(W, b1r, w2r, h, nb, lr, t);
+      train_step<MT, true>(W, b1r, w2r, h, nb, lr, t, [](int) {});
       __syncthreads();
     }
     // validation error (forward passes only)
@@ -913,7 +981,7 @@ __global__ void __launch_bounds__(kTrainThreads, 1) k_mlp_train_mfma(TrainArgs a
     for (int s0 = 0; s0 < n_val; s0 += kTrainB) {
       const int nb = n_val - s0 < kTrainB ? n_val - s0 : kTrainB;
       train_stage(a.xq, exq + a.n_train + s0, exy + a.n_train + s0, nb, m, t);
-      vsum += train_step<MT, false>(W, b1r, w2r, h, nb, 0.0f, t);
+      vsum += train_step<MT, false>(W, b1r, w2r, h, nb, 0.0f, t, [](int) {});
       __syncthreads();
     }
     if (threadIdx.x == 0) {

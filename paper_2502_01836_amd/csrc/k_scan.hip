@@ -102,11 +102,6 @@ __device__ inline int64_t xcd_tile(int64_t j, int x, int lg) {
   return (((j >> lg) * kXcds + x) << lg) + (j & ((1 << lg) - 1));
 }
 
-// Work-group barrier for LDS traffic only: waits for this wave's LDS
-// operations, then s_barrier.  Unlike __syncthreads it does not drain
-// outstanding global loads, so prefetched rows stay in flight across it.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // Leaf of tile t, found by the whole work-group: the L with
 // tile_start[L] <= t < tile_start[L + 1] (tile_start is non-decreasing and
 // tile_start[N] is the tile count, so exactly one L qualifies, and exactly
