@@ -1125,6 +1125,9 @@ int leafi_create(leafi_alloc_fn alloc, leafi_free_fn free_fn, void *alloc_ctx, l
 
 void leafi_destroy(leafi_index *index) { delete index; }
 
+// Series from which a binary tree is built on the device.
+constexpr int64_t kDeviceTreeMin = 16384;
+
 int leafi_build_index(leafi_index *ix, const float *series, int64_t n, int32_t m, const leafi_build_opts *opts,
                       void *stream) {
   return guarded([&] {
@@ -1150,31 +1153,58 @@ int leafi_build_index(leafi_index *ix, const float *series, int64_t n, int32_t m
     DevBuf<double> mean(n), sd(n);
     DevBuf<float> smu(static_cast<size_t>(n) * S), ssd(static_cast<size_t>(n) * S);
     launch_series_stats(series, n, m, S, mean.get(), sd.get(), smu.get(), ssd.get(), st);
-    std::vector<float> hmu(static_cast<size_t>(n) * S), hsd(static_cast<size_t>(n) * S);
-    d2h(hmu.data(), smu.get(), hmu.size(), st);
-    d2h(hsd.data(), ssd.get(), hsd.size(), st);
-    HIP_OK(hipStreamSynchronize(st));
+    // 2. tree
+    constexpr int kMaxLeaves = 16384;
+    const bool on_device = opts->split_rule != 2 && n >= kDeviceTreeMin;
+    DevBuf<int32_t> ids;  // the members in tree order
+    TreeResult tree;
+    std::vector<int64_t> lsz;
+    std::vector<float> boxes;
+    if (on_device) {
+      device_tree(smu.get(), ssd.get(), n, S, m, opts->leaf_capacity, opts->split_rule, kMaxLeaves, ids, lsz, boxes, st);
+    } else {
+      std::vector<float> hmu(static_cast<size_t>(n) * S), hsd(static_cast<size_t>(n) * S);
+      d2h(hmu.data(), smu.get(), hmu.size(), st);
+      d2h(hsd.data(), ssd.get(), hsd.size(), st);
+      HIP_OK(hipStreamSynchronize(st));
+      tree = build_tree(hmu, hsd, n, S, m, opts->leaf_capacity, opts->split_rule);
+      for (const auto &l : tree.leaves) lsz.push_back(static_cast<int64_t>(l.size()));
+      if (tree.leaves.size() <= kMaxLeaves) boxes = leaf_boxes(hmu, hsd, S, tree);
+    }
     smu.release();
     ssd.release();
-    // 2. tree
-    TreeResult tree = build_tree(hmu, hsd, n, S, m, opts->leaf_capacity, opts->split_rule);
-    const int N = static_cast<int>(tree.leaves.size());
-    LEAFI_CHECK_ARG(N <= 16384, "more than 16384 leaves; raise leaf_capacity");
+    const int N = static_cast<int>(lsz.size());
+    LEAFI_CHECK_ARG(N <= kMaxLeaves, "more than 16384 leaves; raise leaf_capacity");
     // 3. padded leaf-contiguous layout
-    std::vector<int64_t> off(N + 1, 0), lsz(N);
+    std::vector<int64_t> off(N + 1, 0), first(N + 1, 0);
     for (int L = 0; L < N; ++L) {
-      lsz[L] = static_cast<int64_t>(tree.leaves[L].size());
       off[L + 1] = off[L] + round_up(lsz[L], kRowAlign);
+      first[L + 1] = first[L] + lsz[L];
     }
     const int64_t rows = off[N];
-    std::vector<int64_t> src(rows, -1);
-    std::vector<int32_t> leaf_of_row(rows);
-    std::vector<int64_t> members;
-    members.reserve(n);
-    for (int L = 0; L < N; ++L) {
-      for (int64_t r = off[L]; r < off[L + 1]; ++r) leaf_of_row[r] = L;
-      for (size_t i = 0; i < tree.leaves[L].size(); ++i) src[off[L] + i] = tree.leaves[L][i];
-      members.insert(members.end(), tree.leaves[L].begin(), tree.leaves[L].end());
+    std::vector<int64_t> members(n);
+    DevBuf<int64_t> dsrc(rows);
+    DevBuf<int32_t> dleaf(rows);
+    ix->leaf_off.alloc(N + 1);
+    h2d(ix->leaf_off.get(), off.data(), N + 1, st);
+    if (on_device) {
+      DevBuf<int64_t> dfirst(N + 1), dmembers(n);
+      h2d(dfirst.get(), first.data(), N + 1, st);
+      launch_tree_rows(rows, N, ix->leaf_off.get(), dfirst.get(), ids.get(), dsrc.get(), dleaf.get(), dmembers.get(), st);
+      d2h(members.data(), dmembers.get(), n, st);
+      HIP_OK(hipStreamSynchronize(st));
+      ids.release();
+    } else {
+      std::vector<int64_t> src(rows, -1);
+      std::vector<int32_t> leaf_of_row(rows);
+      for (int L = 0; L < N; ++L) {
+        std::fill(leaf_of_row.begin() + off[L], leaf_of_row.begin() + off[L + 1], L);
+        std::copy(tree.leaves[L].begin(), tree.leaves[L].end(), src.begin() + off[L]);
+        std::copy(tree.leaves[L].begin(), tree.leaves[L].end(), members.begin() + first[L]);
+      }
+      h2d(dsrc.get(), src.data(), rows, st);
+      h2d(dleaf.get(), leaf_of_row.data(), rows, st);
+      HIP_OK(hipStreamSynchronize(st));
     }
     int max_chunks[kChunkSizes];
     int64_t total_chunks[kChunkSizes];
@@ -1187,21 +1217,15 @@ int leafi_build_index(leafi_index *ix, const float *series, int64_t n, int32_t m
         total_chunks[j] += c;
       }
     }
-    std::vector<float> boxes = leaf_boxes(hmu, hsd, S, tree);
     // 4. device leaf store
     ix->x32.alloc(static_cast<size_t>(rows) * m);
     ix->x16.alloc(static_cast<size_t>(rows) * m);
     ix->xn16.alloc(rows);
     ix->rowid.alloc(rows);
-    ix->leaf_off.alloc(N + 1);
     ix->leaf_n.alloc(N);
     ix->boxes.alloc(boxes.size());
     ix->boxes_t.alloc(boxes.size());
     ix->leaf_eps.alloc(N);
-    DevBuf<int64_t> dsrc(rows);
-    DevBuf<int32_t> dleaf(rows);
-    h2d(dsrc.get(), src.data(), rows, st);
-    h2d(dleaf.get(), leaf_of_row.data(), rows, st);
     HIP_OK(hipMemsetAsync(ix->leaf_eps.get(), 0, N * sizeof(float), st));
     launch_pack(series, dsrc.get(), dleaf.get(), rows, m, mean.get(), sd.get(), ix->x32.get(), ix->x16.get(),
                 ix->xn16.get(), ix->rowid.get(), ix->leaf_eps.get(), st);
@@ -1213,7 +1237,6 @@ int leafi_build_index(leafi_index *ix, const float *series, int64_t n, int32_t m
     }
     std::vector<int32_t> ln32(N);
     for (int L = 0; L < N; ++L) ln32[L] = static_cast<int32_t>(lsz[L]);
-    h2d(ix->leaf_off.get(), off.data(), N + 1, st);
     h2d(ix->leaf_n.get(), ln32.data(), N, st);
     h2d(ix->boxes.get(), boxes.data(), boxes.size(), st);
     std::vector<float> boxes_t(boxes.size());

@@ -39,6 +39,17 @@ TreeResult build_isax_tree(const std::vector<float> &seg_mu, int64_t n, int S, i
 std::vector<float> leaf_boxes(const std::vector<float> &seg_mu, const std::vector<float> &seg_sd, int S,
                               const TreeResult &t);
 
+// The binary trees built on the device (k_tree.hip), from the summaries there:
+// the leaves' members in tree order (`ids`, ascending within a leaf), their
+// sizes and boxes.  With more than max_leaves leaves it stops; sizes then
+// holds more than that.
+void device_tree(const float *mu, const float *sd, int64_t n, int S, int m, int capacity, int rule, int max_leaves,
+                 DevBuf<int32_t> &ids, std::vector<int64_t> &sizes, std::vector<float> &boxes, hipStream_t st);
+// The store's rows (padded leaf by leaf, off [N + 1]; -1: padding), their
+// leaves, and the members as 64-bit ids; first [N + 1] counts the members before each leaf.
+void launch_tree_rows(int64_t rows, int N, const int64_t *off, const int64_t *first, const int32_t *ids, int64_t *src,
+                      int32_t *leaf, int64_t *members, hipStream_t st);
+
 // ---- leaf selection (tree.cpp) -----------------------------------------------
 
 // Algorithm 3: leaves by size (largest first, ties by id) with size >= th

@@ -115,8 +115,12 @@ __global__ void __launch_bounds__(256) k_pack(const float *__restrict__ raw, con
     xn16[row] = nrm;
     rowid[row] = src;
     // non-negative floats order like their bit patterns
-    float e = sqrtf(err) * (1.0f + 1e-5f);
-    atomicMax(reinterpret_cast<unsigned int *>(leaf_eps + leaf_of_row[row]), f2u(e));
+    // (most rows are below their leaf's largest so far: thousands of atomics
+    // on each leaf's word serialised)
+    const float e = sqrtf(err) * (1.0f + 1e-5f);
+    float *to = leaf_eps + leaf_of_row[row];
+    if (e > __hip_atomic_load(to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(reinterpret_cast<unsigned int *>(to), f2u(e));
   }
 }
 
