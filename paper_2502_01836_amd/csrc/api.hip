@@ -1125,8 +1125,11 @@ int leafi_create(leafi_alloc_fn alloc, leafi_free_fn free_fn, void *alloc_ctx, l
 
 void leafi_destroy(leafi_index *index) { delete index; }
 
-// Series from which a binary tree is built on the device.
-constexpr int64_t kDeviceTreeMin = 16384;
+// Series from which a binary tree is built on the device, whose time is mostly
+// launches: index builds of m = 128 into 64 leaves, median splits, 5,000
+// series 0.78 ms on the host and 1.12 on the device, 10,000 1.91 and 1.36;
+// midpoint splits (deeper) 10,000 1.42 and 2.06, 20,000 2.49 and 2.46.
+constexpr int64_t kDeviceTreeMin[2] = {8192, 20000};
 
 int leafi_build_index(leafi_index *ix, const float *series, int64_t n, int32_t m, const leafi_build_opts *opts,
                       void *stream) {
@@ -1155,7 +1158,7 @@ int leafi_build_index(leafi_index *ix, const float *series, int64_t n, int32_t m
     launch_series_stats(series, n, m, S, mean.get(), sd.get(), smu.get(), ssd.get(), st);
     // 2. tree
     constexpr int kMaxLeaves = 16384;
-    const bool on_device = opts->split_rule != 2 && n >= kDeviceTreeMin;
+    const bool on_device = opts->split_rule != 2 && n >= kDeviceTreeMin[opts->split_rule];
     DevBuf<int32_t> ids;  // the members in tree order
     TreeResult tree;
     std::vector<int64_t> lsz;
@@ -1185,12 +1188,12 @@ int leafi_build_index(leafi_index *ix, const float *series, int64_t n, int32_t m
     std::vector<int64_t> members(n);
     DevBuf<int64_t> dsrc(rows);
     DevBuf<int32_t> dleaf(rows);
-    ix->leaf_off.alloc(N + 1);
-    h2d(ix->leaf_off.get(), off.data(), N + 1, st);
+    DevBuf<int64_t> doff(N + 1);
+    h2d(doff.get(), off.data(), N + 1, st);
     if (on_device) {
       DevBuf<int64_t> dfirst(N + 1), dmembers(n);
       h2d(dfirst.get(), first.data(), N + 1, st);
-      launch_tree_rows(rows, N, ix->leaf_off.get(), dfirst.get(), ids.get(), dsrc.get(), dleaf.get(), dmembers.get(), st);
+      launch_tree_rows(rows, N, doff.get(), dfirst.get(), ids.get(), dsrc.get(), dleaf.get(), dmembers.get(), st);
       d2h(members.data(), dmembers.get(), n, st);
       HIP_OK(hipStreamSynchronize(st));
       ids.release();
@@ -1222,6 +1225,7 @@ int leafi_build_index(leafi_index *ix, const float *series, int64_t n, int32_t m
     ix->x16.alloc(static_cast<size_t>(rows) * m);
     ix->xn16.alloc(rows);
     ix->rowid.alloc(rows);
+    ix->leaf_off = std::move(doff);
     ix->leaf_n.alloc(N);
     ix->boxes.alloc(boxes.size());
     ix->boxes_t.alloc(boxes.size());

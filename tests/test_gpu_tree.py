@@ -1,4 +1,4 @@
-"""Binary trees built on the device (from 16,384 series) against the oracle's:
+"""Binary trees built on the device (large collections) against the oracle's:
 the same leaves, member for member, and boxes that hold them.  Ties by the
 thousand (few distinct series), midpoints with an empty side, segment counts
 that are no power of two, chunks and nodes that end anywhere, capacity 1."""
@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("n,m,S,capacity,rule,distinct", [
-    (16384, 64, 16, 100, "median", 0), (16383, 64, 16, 100, "median", 0), (40001, 32, 5, 700, "median", 40),
+    (8192, 64, 16, 100, "median", 0), (8191, 64, 16, 100, "median", 0), (40001, 32, 5, 700, "median", 40),
     (33000, 32, 1, 9, "median", 0), (30011, 96, 12, 500, "midpoint", 0), (20000, 64, 32, 300, "midpoint", 7),
     (16500, 64, 64, 2, "median", 0)])
 def test_device_tree_is_the_oracles(n, m, S, capacity, rule, distinct):
