@@ -335,9 +335,10 @@ int pick_chunk(const leafi_index *ix, int kprime, int pref) {
 // dependent loads and list sorts however few rows it has), shorter ones for
 // small passes, whose tiles would otherwise leave CUs idle and scan for
 // longer each.  Measured against 1,024 rows x 32 queries: 10M x 256, 1,024
-// queries 3.92 -> 3.34 ms (2,048 x 48; 4,096 rows 3.57); 2.5M x 96 ragged,
-// 4,096 queries 14.9 -> 11.6 ms; 20k x 256, 100 queries 128 -> 116 us (256
-// rows); one query at 1M 175 -> 168 us (256 rows).  An all-pairs pass, whose
+// queries 3.22 -> 2.61 ms; 2.5M x 96 ragged, 4,096 queries 8.62 -> 4.86 ms
+// (fewer tiles, each starting with a tighter shared bound); 20k x 256, 100
+// queries 116 -> 108 us and one query at 1M 169 -> 166 (256 rows); 1M x 256,
+// 1,000 queries 354 and 356.  An all-pairs pass, whose
 // lists fill once per tile however long it is, takes 4,096 rows (500 queries
 // x 128 leaves 1,618 -> 1,465 us).  A round of one leaf per query keeps 16
 // queries per tile (few share a leaf).
