@@ -336,10 +336,20 @@ void split_launch_ht(int ht, const SplitArgs &a, dim3 grid, hipStream_t st) {
 // time (wr / HT), then by more hidden tiles (each operand read from LDS
 // serves more products).  With listed pairs, whose numbers only the device
 // knows, an eighth of the queries stands for a filter's rows.
+// Small calls are left to the FP32 kernels' tiles of 32 rows, which need not
+// read and split all of W1 (about 15 us) first: dense ones of up to kSplitTiles
+// tiles per CU (3 filters 240 -> 152, 35 rows: 12.6 us, here 18.5; 16 filters
+// 256 -> 256, 500 rows: 15.5 and 19.2; 300 of 100 -> 100, 50 rows: 17.7 and
+// 23.2; but 128 of 256 -> 256, 200 rows: 51 and 35, 64 of 128 -> 128, 500 rows:
+// 26 and 18), and listed ones of fewer filters than CUs (128 filters, 1,000
+// queries' pairs: 30 and 32; by the filters alone, so that a query's values do
+// not depend on its batch).
+constexpr int kSplitTiles = 3;
 bool launch_mlp_infer_split(const float *w, int F, int m, int h, const float *x, int64_t nq, float *out,
                             const int64_t *plist, const int32_t *pcnt, int64_t stride, int N, const int32_t *pair,
                             const float *offsets, float *dfo, bool small_batches, hipStream_t st) {
   if (m > 256 || h > 256 || m % 4 != 0 || reinterpret_cast<uintptr_t>(x) % 16 != 0) return false;
+  if (plist ? F < device_cus() : F * ceil_div(nq, 32) <= static_cast<int64_t>(kSplitTiles) * device_cus()) return false;
   const int ks = (m + 31) / 32, ht_all = (h + 15) / 16, tiles = 24 / ks;
   SplitArgs a{w, F, m, h, x, nq, out, plist, pcnt, stride, N, pair, offsets, dfo, 0, 0, 0};
   int ht = 0;

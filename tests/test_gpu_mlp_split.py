@@ -62,3 +62,29 @@ def test_split_inference_with_values_that_are_not_finite(m, h):
         rest = ~fin & (mag > 1e39)  # infinite in FP32 too
         assert np.array_equal(np.isfinite(got[rest, f]), np.isfinite(want[rest]) & (np.abs(want[rest]) < 3.4e38))
     assert got[3, 0] == w[0, -1]  # every hidden unit a NaN: the output bias alone
+
+
+@pytest.mark.parametrize("F,m,h,nq", [(800, 4, 4, 1), (500, 36, 20, 33), (260, 32, 256, 129), (260, 256, 256, 97),
+                                      (780, 228, 144, 31), (780, 160, 200, 17), (400, 128, 252, 64), (260, 256, 64, 100),
+                                      (769, 192, 160, 32), (768, 192, 160, 32)])
+def test_split_inference_of_many_filters(F, m, h, nq):
+    """As above with the filters it takes for the work to be worth the split (the last two: either side of it)."""
+    test_split_inference_at_tile_edges(F, m, h, nq)
+
+
+@pytest.mark.parametrize("m,h", [(256, 256), (96, 96)])
+def test_many_filters_with_values_that_are_not_finite(m, h):
+    pkg = _pkg()
+    F = 300
+    w, x = _draw(F, m, h, 97, 5)
+    x[3, 7], x[40, 1] = np.nan, np.inf
+    x[66, 2] = 3.4e38       # finite, but a bf16 part would round it to infinity
+    w[1, 11] = np.inf       # input 0, hidden unit 11
+    got = pkg.mlp_infer(torch.from_numpy(w).cuda(), m, h, torch.from_numpy(x).cuda()).cpu().numpy()
+    for f in (0, 1, 2, F - 1):
+        want, mag = _forward(w[f], x, m, h)
+        fin = np.isfinite(want) & np.isfinite(mag) & (mag < 1e37)
+        assert np.all(np.abs(got[fin, f] - want[fin]) <= (m + h + 8) * 2.0 ** -24 * mag[fin])
+        rest = ~fin & (mag > 1e39)  # infinite in FP32 too
+        assert np.array_equal(np.isfinite(got[rest, f]), np.isfinite(want[rest]) & (np.abs(want[rest]) < 3.4e38))
+    assert got[3, 0] == w[0, -1]  # every hidden unit a NaN: the output bias alone
