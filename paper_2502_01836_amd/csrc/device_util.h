@@ -204,28 +204,6 @@ __host__ __device__ __forceinline__ int pow2_at_least(int n) {
   return p;
 }
 
-// Bitonic sort of P (power of two) 32- or 64-bit keys in LDS by one
-// wavefront, ascending.
-template <typename K>
-__device__ inline void wave_sort_keys(K *a, int P, int lane) {
-  for (int size = 2; size <= P; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int i = lane; i < (P >> 1); i += kWave) {
-        int lo = 2 * i - (i & (stride - 1));
-        int hi = lo + stride;
-        bool up = (lo & size) == 0;
-        const K x = a[lo], y = a[hi];
-        if ((x > y) == up) {
-          a[lo] = y;
-          a[hi] = x;
-        }
-      }
-      wave_lds_sync();
-    }
-  }
-}
-__device__ inline void wave_sort_u64(uint64_t *a, int P, int lane) { wave_sort_keys(a, P, lane); }
-
 // Sort of the first n keys of a (any n >= 0), ascending, by one wavefront,
 // touching no entry at or past n.  Bitonic network in the form whose every
 // comparator puts the smaller key at the lower index (each merge starts by
@@ -258,30 +236,6 @@ __device__ inline void wave_sort_keys_n(K *a, int n, int lane) {
             a[lo] = y;
             a[hi] = x;
           }
-        }
-      }
-      wave_lds_sync();
-    }
-  }
-}
-
-// Bitonic sort of P (power of two) (double, uint32) pairs, ascending by
-// (value, tag), by one wavefront.
-__device__ inline void wave_sort_dbl_tag(double *v, uint32_t *t, int P, int lane) {
-  for (int size = 2; size <= P; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int i = lane; i < (P >> 1); i += kWave) {
-        int lo = 2 * i - (i & (stride - 1));
-        int hi = lo + stride;
-        bool up = (lo & size) == 0;
-        double x = v[lo], y = v[hi];
-        uint32_t tx = t[lo], ty = t[hi];
-        bool gt = (x > y) || (x == y && tx > ty);
-        if (gt == up) {
-          v[lo] = y;
-          v[hi] = x;
-          t[lo] = ty;
-          t[hi] = tx;
         }
       }
       wave_lds_sync();

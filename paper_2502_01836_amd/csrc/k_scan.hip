@@ -2,7 +2,7 @@
 // once); the per-item rerank of their candidate lists is in k_rerank.hip.
 //
 // A scan tile is (leaf L, group of up to MQ queries that all search L this
-// round, chunk of kChunkRows rows of L).  The persistent grid walks the tiles;
+// round, chunk of the pass's rows of L).  The persistent grid walks the tiles;
 // per tile it streams the chunk's rows once for all the group's queries and
 // keeps, per query, the kprime best (squared distance, row) keys.
 //
@@ -13,12 +13,12 @@
 // per K step, so the four lanes of a row read 64 contiguous bytes.
 //
 // FP32 form: direct difference sum_t (q_t - x_t)^2, 16 lanes per row, each
-// lane summing m/16 contiguous elements, then a fixed 16-lane tree.
+// lane summing every 16th pair of elements, then a fixed 16-lane tree.
 //
 // Candidate keeping (both forms): per query an LDS list with a threshold; a
 // key below the threshold is appended with an LDS atomic; when a list could
-// overflow in the next 64 rows it is sorted (bitonic, one wavefront) and cut
-// to kprime, which also tightens the threshold.
+// overflow in the next 64 rows it is sorted (in one wavefront's registers) and
+// cut to kprime, which also tightens the threshold.
 //
 // The BF16 form keeps 32-bit keys in LDS: the squared distance's float bits
 // with the lowest kDropBits cut off (rounded down, so the value a key stands
