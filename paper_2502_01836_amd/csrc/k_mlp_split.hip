@@ -29,8 +29,11 @@
 // where the FP32 kernel had three of its eight wavefronts at work.
 //
 // bf16 parts of an infinity (or of a value that rounds to one) have no finite
-// remainder, so a filter or batch that holds one, or a NaN, is evaluated with
-// plain FP32 arithmetic instead.
+// remainder, so a row that holds one, or a NaN, is evaluated with plain FP32
+// arithmetic instead, and with such a weight every row of its filter.  The
+// other rows of its batch keep the matrix products' values (an operand column
+// reaches its own output column alone): what a row's prediction is does not
+// depend on the rows beside it.
 #include <algorithm>
 
 #include "device_util.h"
@@ -76,17 +79,21 @@ __device__ __forceinline__ void load_to_lds(const float *p, const float *base) {
 // Until every load this wavefront requested, into LDS or registers, has landed.
 __device__ __forceinline__ void wait_lds_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// Plain FP32 evaluation of the batch's rows, one wavefront per row: row sums
-// into red (the other hidden groups' sums zero).
+// Plain FP32 evaluation of the batch's flagged rows, or with `all` of every
+// row, one wavefront per row: row sums into red (the other hidden groups' sums
+// zero).
 __device__ __forceinline__ void split_plain_rows(const float *__restrict__ wf, int m, int h, const float *__restrict__ x,
-                                              const int64_t *rowq, int nr, int rb, int wh, float *red) {
+                                              const int64_t *rowq, const int *rowbad, bool all, int nr, int rb, int wh,
+                                              float *red) {
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const float *b1 = wf + static_cast<int64_t>(h) * m, *w2 = b1 + h;
   for (int c = wave; c < nr; c += kSplitWaves) {
+    if (!all && rowbad[c] == 0) continue;  // uniform
     const float *xr = x + rowq[c] * m;
     float p = 0.0f;
     for (int j = lane; j < h; j += kWave) {
       float z = 0.0f;
+#pragma unroll 8
       for (int i = 0; i < m; ++i) z = fmaf(xr[i], wf[static_cast<int64_t>(i) * h + j], z);
       p = fmaf(w2[j], fmaxf(z + b1[j], 0.0f), p);
     }
@@ -97,12 +104,12 @@ __device__ __forceinline__ void split_plain_rows(const float *__restrict__ wf, i
 }
 
 // LDS of a work-group: the next batch's rows, the planes, b1 and w2 (padded hidden units), the
-// hidden groups' row sums (two batches), the batch's query rows and list
-// entries (two batches), four flags.
+// hidden groups' row sums (two batches), the batch's query rows, list
+// entries and row flags (two batches), four flags.
 __host__ __device__ inline int split_rows(const SplitArgs &a) { return 16 * a.wr * a.rt; }
 size_t split_lds(const SplitArgs &a, int ks, int ht) {
   const size_t rb = split_rows(a);
-  return rb * a.m * 4 + 3 * rb * (32 * ks + 8) * 2 + 2 * static_cast<size_t>(16 * ht * a.wh) * 4 + 2 * a.wh * rb * 4 + 4 * rb * 8 + 16;
+  return rb * a.m * 4 + 3 * rb * (32 * ks + 8) * 2 + 2 * static_cast<size_t>(16 * ht * a.wh) * 4 + 2 * a.wh * rb * 4 + 4 * rb * 8 + 2 * rb * 4 + 16;
 }
 
 template <int KS, int HT>
@@ -123,7 +130,8 @@ __global__ void __launch_bounds__(kSplitThreads, 2) k_mlp_infer_split(SplitArgs 
   float *red = w2s + hp;                                       // [2][wh][rb]
   int64_t *rowq = reinterpret_cast<int64_t *>(red + 2 * wh * rb);  // [2][rb]
   int64_t *rent = rowq + 2 * rb;                                   // [2][rb]
-  int *bad = reinterpret_cast<int *>(rent + 2 * rb);               // [2] batch, [1] weights
+  int *rowbad = reinterpret_cast<int *>(rent + 2 * rb);            // [2][rb] rows for plain arithmetic
+  int *bad = rowbad + 2 * rb;                                      // [2] batch holds such rows, [1] weights
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int col = lane & 15, q = lane >> 4;
   const int hg = wave % wh, rg = wave / wh;
@@ -144,6 +152,7 @@ __global__ void __launch_bounds__(kSplitThreads, 2) k_mlp_infer_split(SplitArgs 
       }
       rowq[s * rb + tid] = qr;
       rent[s * rb + tid] = e;
+      rowbad[s * rb + tid] = 0;
     }
   };
   int64_t b = blockIdx.y;
@@ -240,7 +249,6 @@ __global__ void __launch_bounds__(kSplitThreads, 2) k_mlp_infer_split(SplitArgs 
     const int nr = static_cast<int>(n - b * rb < rb ? n - b * rb : rb);
     __syncthreads();  // the planes and the other slot's sums are complete
     write_out(s ^ 1, nr_prev);
-    uint32_t big = 0;
     wait_lds_loads();  // each thread splits the pieces its own wavefront requested
     {
       const int t = my_thread();
@@ -250,18 +258,18 @@ __global__ void __launch_bounds__(kSplitThreads, 2) k_mlp_infer_split(SplitArgs 
         const int c = static_cast<int>((static_cast<uint32_t>(e4) * inv4) >> 20);
         if (c < nr) {
           const float4 v = *reinterpret_cast<const float4 *>(raw + 4 * e4);
-          const uint32_t g = split_store4(v, planes, plane, c * MP + 4 * (e4 - c * m4));
-          big = g > big ? g : big;
+          if (split_store4(v, planes, plane, c * MP + 4 * (e4 - c * m4)) >= kSplitHuge) {
+            rowbad[s * rb + c] = 1;
+            bad[s] = 1;
+          }
         }
       }
     }
-    if (big >= kSplitHuge) bad[s] = 1;
     find_rows(b + gridDim.y, s ^ 1);
     __syncthreads();
     fetch(s ^ 1);
-    if (bad[s] | bad[2]) {
-      split_plain_rows(wf, m, h, a.x, rowq + s * rb, nr, rb, wh, red + s * wh * rb);
-    } else if (rg < wr) {
+    const bool all = bad[2] != 0, some = bad[s] != 0;  // uniform
+    if (rg < wr && !all) {
       for (int rt = 0; rt < a.rt; ++rt) {
         const int row0 = 16 * (rg + wr * rt);
         if (row0 >= nr) break;  // uniform
@@ -302,6 +310,10 @@ __global__ void __launch_bounds__(kSplitThreads, 2) k_mlp_infer_split(SplitArgs 
         p += __shfl_xor(p, 32, kWave);
         if (lane < 16) red[(s * wh + hg) * rb + row0 + lane] = p;
       }
+    }
+    if (all || some) {
+      __syncthreads();  // the flagged rows' own sums replace the products'
+      split_plain_rows(wf, m, h, a.x, rowq + s * rb, rowbad + s * rb, all, nr, rb, wh, red + s * wh * rb);
     }
     if (tid == 0) bad[s ^ 1] = 0;  // the next batch's (set only after the next barrier)
     nr_prev = nr;
