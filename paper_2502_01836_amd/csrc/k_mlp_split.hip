@@ -348,20 +348,22 @@ void split_launch_ht(int ht, const SplitArgs &a, dim3 grid, hipStream_t st) {
 // time (wr / HT), then by more hidden tiles (each operand read from LDS
 // serves more products).  With listed pairs, whose numbers only the device
 // knows, an eighth of the queries stands for a filter's rows.
-// Small calls are left to the FP32 kernels' tiles of 32 rows, which need not
-// read and split all of W1 (about 15 us) first: dense ones of up to kSplitTiles
-// tiles per CU (3 filters 240 -> 152, 35 rows: 12.6 us, here 18.5; 16 filters
-// 256 -> 256, 500 rows: 15.5 and 19.2; 300 of 100 -> 100, 50 rows: 17.7 and
-// 23.2; but 128 of 256 -> 256, 200 rows: 51 and 35, 64 of 128 -> 128, 500 rows:
-// 26 and 18), and listed ones of fewer filters than CUs (128 filters, 1,000
-// queries' pairs: 30 and 32; by the filters alone, so that a query's values do
-// not depend on its batch).
-constexpr int kSplitTiles = 3;
+//
+// Which filters are evaluated here follows from the filters alone (their
+// number and sizes), never from the rows of a call: a prediction's bits are
+// the same in any batch, and the same in a calibration (dense) as in the
+// search that tests its offset (listed).  Few filters are left to the FP32
+// kernels' tiles of 32 rows, which need not read and split all of W1 (about 15
+// us) first (3 filters 240 -> 152, 35 rows: 12.6 us, here 18.5; 128 of 256 ->
+// 256: 14 and 20 for 40 rows, 90 and 57 for 500), and so are wide ones whose
+// sizes pad its 16 x 16 tiles (300 of 228 -> 144: 31 and 39 for 40 rows, 175 and
+// 151 for 500).  From a filter per CU on the rest is the faster here: 256
+// -> 256, 256 filters, one row 25 us (the FP32 kernel that kept W1 in registers)
+// and 19, 500 rows 178 and 99.
 bool launch_mlp_infer_split(const float *w, int F, int m, int h, const float *x, int64_t nq, float *out,
                             const int64_t *plist, const int32_t *pcnt, int64_t stride, int N, const int32_t *pair,
                             const float *offsets, float *dfo, bool small_batches, hipStream_t st) {
-  if (m > 256 || h > 256 || m % 4 != 0 || reinterpret_cast<uintptr_t>(x) % 16 != 0) return false;
-  if (plist ? F < device_cus() : F * ceil_div(nq, 32) <= static_cast<int64_t>(kSplitTiles) * device_cus()) return false;
+  if (F < device_cus() || m > 256 || h > 256 || m % 4 != 0 || reinterpret_cast<uintptr_t>(x) % 16 != 0) return false;
   const int ks = (m + 31) / 32, ht_all = (h + 15) / 16, tiles = 24 / ks;
   SplitArgs a{w, F, m, h, x, nq, out, plist, pcnt, stride, N, pair, offsets, dfo, 0, 0, 0};
   int ht = 0;
@@ -375,6 +377,8 @@ bool launch_mlp_infer_split(const float *w, int F, int m, int h, const float *x,
       a.wr = wr;
     }
   }
+  const bool narrow = ks <= 4 && a.wh <= 4;
+  if (!narrow && (m % 16 != 0 || h % 16 != 0)) return false;
   a.rt = small_batches ? 1 : std::max(1, std::min(3, tiles / a.wr));
   // how many work-groups share a filter: rounds of the chip x (the read of W1,
   // about three batches' time, and the batches of one)

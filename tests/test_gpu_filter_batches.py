@@ -37,3 +37,54 @@ def test_rows_beside_rows_that_are_not_finite(F, m, h):
     assert np.array_equal(got[same], want[same])
     # a NaN unit counts as 0: a row of NaN alone is left with the output bias
     assert np.array_equal(got[41], w[:, -1].cpu().numpy())
+
+
+@pytest.mark.parametrize("F,m,h", [(3, 256, 256), (64, 128, 128), (128, 256, 256), (255, 96, 96), (256, 96, 96),
+                                   (300, 100, 100), (300, 228, 144), (520, 256, 256), (1024, 32, 64)])
+def test_rows_in_calls_of_any_size(F, m, h):
+    pkg = _pkg()
+    w = torch.from_numpy(W.mlp_weights(F, m, h, seed=F + h)).cuda()
+    x = torch.from_numpy(_rows(500, m, h)).cuda()
+    want = pkg.mlp_infer(w, m, h, x)
+    for a, b in ((0, 1), (0, 17), (33, 65), (100, 333), (499, 500)):
+        assert torch.equal(pkg.mlp_infer(w, m, h, x[a:b].clone()), want[a:b]), (a, b)
+
+
+@pytest.mark.parametrize("arch", ["mlp", "cnn"])
+@pytest.mark.parametrize("n_leaves", [128, 256, 512])
+def test_listed_pairs_have_the_dense_predictions(arch, n_leaves):
+    """What a search subtracts its offsets from is what calibration fits them
+    on.  Predictions of 1e9 and more stand a thousand apart, distances are
+    below 50: with every offset the dense prediction itself no pair may be
+    pruned, with the next float below it every pair that the search evaluates
+    must be, for every query (each with a target, and so offsets, of its own)."""
+    pkg = _pkg()
+    m, nq = (128, 300) if arch == "mlp" else (32, 60)
+    h = m if arch == "mlp" else 8
+    raw = W.random_walk(n_leaves * 40, m, seed=n_leaves)
+    ix = pkg.Index().build(torch.from_numpy(raw).cuda(), leaf_capacity=40, n_segments=8)
+    F = ix.info()["n_leaves"]
+    assert F == n_leaves
+    g = np.random.default_rng(F)
+    leaves = np.arange(F, dtype=np.int32)
+    q = torch.from_numpy(W.noisy_queries(raw, nq, 0.4, 1, 2)[0]).cuda()
+    if arch == "mlp":
+        w = W.mlp_weights(F, m, h, seed=F)
+        w[:, m * h + h: m * h + 2 * h] = g.uniform(1e9, 2e9, (F, h))
+        ix.set_filters(leaves, torch.from_numpy(w).cuda(), h)
+        y = pkg.mlp_infer(torch.from_numpy(w).cuda(), m, h, pkg.znorm(q))
+    else:
+        w = g.uniform(-0.5, 0.5, (F, 3 * h * h + 6 * h + 1)).astype(np.float32)
+        w[:, 3 * h * h + 4 * h:3 * h * h + 5 * h] = 0.5  # the second layer's biases
+        w[:, 3 * h * h + 5 * h:-1] = g.uniform(1e10, 2e10, (F, h))
+        ix.set_cnn_filters(leaves, torch.from_numpy(w).cuda(), h)
+        y = pkg.cnn_infer(torch.from_numpy(w).cuda(), m, h, pkg.znorm(q))
+    y = y.cpu().numpy()
+    assert y.min() > 1e9
+    targets = ((np.arange(nq) + 1) / (nq + 1)).astype(np.float32)
+    t = torch.from_numpy(targets).cuda()
+    for offsets, share in ((y, 0), (np.nextafter(y, np.float32(0)), 1)):
+        ix.set_offsets([1], targets, offsets)
+        _, _, st = ix.search(q, k=1, target=t, k_max=1, schedule=(1, 0), with_stats=True)
+        assert st["filter_evals"] > nq
+        assert st["leaves_filter_pruned"] == share * st["filter_evals"]
