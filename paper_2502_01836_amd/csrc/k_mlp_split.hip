@@ -81,9 +81,9 @@ __device__ __forceinline__ void wait_lds_loads() { asm volatile("s_waitcnt vmcnt
 
 // Plain FP32 evaluation of the batch's flagged rows, or with `all` of every
 // row, one wavefront per row: row sums into red (the other hidden groups' sums
-// zero).
+// zero), the flags back to 0.
 __device__ __forceinline__ void split_plain_rows(const float *__restrict__ wf, int m, int h, const float *__restrict__ x,
-                                              const int64_t *rowq, const int *rowbad, bool all, int nr, int rb, int wh,
+                                              const int64_t *rowq, int *rowbad, bool all, int nr, int rb, int wh,
                                               float *red) {
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const float *b1 = wf + static_cast<int64_t>(h) * m, *w2 = b1 + h;
@@ -93,23 +93,24 @@ __device__ __forceinline__ void split_plain_rows(const float *__restrict__ wf, i
     float p = 0.0f;
     for (int j = lane; j < h; j += kWave) {
       float z = 0.0f;
-#pragma unroll 8
       for (int i = 0; i < m; ++i) z = fmaf(xr[i], wf[static_cast<int64_t>(i) * h + j], z);
       p = fmaf(w2[j], fmaxf(z + b1[j], 0.0f), p);
     }
     p = wave_sum(p);
-    if (lane == 0)
+    if (lane == 0) {
+      rowbad[c] = 0;
       for (int g = 0; g < wh; ++g) red[g * rb + c] = g == 0 ? p : 0.0f;
+    }
   }
 }
 
 // LDS of a work-group: the next batch's rows, the planes, b1 and w2 (padded hidden units), the
-// hidden groups' row sums (two batches), the batch's query rows, list
-// entries and row flags (two batches), four flags.
+// hidden groups' row sums (two batches), the batch's query rows and list
+// entries (two batches), its row flags, four flags.
 __host__ __device__ inline int split_rows(const SplitArgs &a) { return 16 * a.wr * a.rt; }
 size_t split_lds(const SplitArgs &a, int ks, int ht) {
   const size_t rb = split_rows(a);
-  return rb * a.m * 4 + 3 * rb * (32 * ks + 8) * 2 + 2 * static_cast<size_t>(16 * ht * a.wh) * 4 + 2 * a.wh * rb * 4 + 4 * rb * 8 + 2 * rb * 4 + 16;
+  return rb * a.m * 4 + 3 * rb * (32 * ks + 8) * 2 + 2 * static_cast<size_t>(16 * ht * a.wh) * 4 + 2 * a.wh * rb * 4 + 4 * rb * 8 + rb * 4 + 16;
 }
 
 template <int KS, int HT>
@@ -130,8 +131,8 @@ __global__ void __launch_bounds__(kSplitThreads, 2) k_mlp_infer_split(SplitArgs 
   float *red = w2s + hp;                                       // [2][wh][rb]
   int64_t *rowq = reinterpret_cast<int64_t *>(red + 2 * wh * rb);  // [2][rb]
   int64_t *rent = rowq + 2 * rb;                                   // [2][rb]
-  int *rowbad = reinterpret_cast<int *>(rent + 2 * rb);            // [2][rb] rows for plain arithmetic
-  int *bad = rowbad + 2 * rb;                                      // [2] batch holds such rows, [1] weights
+  int *rowbad = reinterpret_cast<int *>(rent + 2 * rb);            // [rb] the batch's rows for plain arithmetic
+  int *bad = rowbad + rb;                                          // [2] batch holds such rows, [1] weights
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int col = lane & 15, q = lane >> 4;
   const int hg = wave % wh, rg = wave / wh;
@@ -152,12 +153,11 @@ __global__ void __launch_bounds__(kSplitThreads, 2) k_mlp_infer_split(SplitArgs 
       }
       rowq[s * rb + tid] = qr;
       rent[s * rb + tid] = e;
-      rowbad[s * rb + tid] = 0;
     }
   };
   int64_t b = blockIdx.y;
   find_rows(b, 0);
-  if (tid < 4) bad[tid] = 0;
+  for (int e = tid; e < rb + 4; e += kSplitThreads) rowbad[e] = 0;  // and bad
   // inputs past m are zero in every row and in W1
   if (m < 32 * KS)
     for (int e = tid; e < 3 * rb * (32 * KS - m); e += kSplitThreads) {
@@ -250,6 +250,7 @@ __global__ void __launch_bounds__(kSplitThreads, 2) k_mlp_infer_split(SplitArgs 
     __syncthreads();  // the planes and the other slot's sums are complete
     write_out(s ^ 1, nr_prev);
     wait_lds_loads();  // each thread splits the pieces its own wavefront requested
+    uint32_t big = 0;
     {
       const int t = my_thread();
 #pragma unroll
@@ -258,12 +259,17 @@ __global__ void __launch_bounds__(kSplitThreads, 2) k_mlp_infer_split(SplitArgs 
         const int c = static_cast<int>((static_cast<uint32_t>(e4) * inv4) >> 20);
         if (c < nr) {
           const float4 v = *reinterpret_cast<const float4 *>(raw + 4 * e4);
-          if (split_store4(v, planes, plane, c * MP + 4 * (e4 - c * m4)) >= kSplitHuge) {
-            rowbad[s * rb + c] = 1;
-            bad[s] = 1;
-          }
+          const uint32_t g = split_store4(v, planes, plane, c * MP + 4 * (e4 - c * m4));
+          big = g > big ? g : big;
         }
       }
+    }
+    if (big >= kSplitHuge) {  // rare: which of the thread's pieces
+      bad[s] = 1;
+      for (int e4 = tid; e4 / m4 < nr; e4 += kSplitThreads)
+        if (split_store4(*reinterpret_cast<const float4 *>(raw + 4 * e4), planes, plane,
+                         e4 / m4 * MP + 4 * (e4 % m4)) >= kSplitHuge)
+          rowbad[e4 / m4] = 1;
     }
     find_rows(b + gridDim.y, s ^ 1);
     __syncthreads();
@@ -313,7 +319,7 @@ __global__ void __launch_bounds__(kSplitThreads, 2) k_mlp_infer_split(SplitArgs 
     }
     if (all || some) {
       __syncthreads();  // the flagged rows' own sums replace the products'
-      split_plain_rows(wf, m, h, a.x, rowq + s * rb, rowbad + s * rb, all, nr, rb, wh, red + s * wh * rb);
+      split_plain_rows(wf, m, h, a.x, rowq + s * rb, rowbad, all, nr, rb, wh, red + s * wh * rb);
     }
     if (tid == 0) bad[s ^ 1] = 0;  // the next batch's (set only after the next barrier)
     nr_prev = nr;
