@@ -11,7 +11,7 @@
 // FP32 matrix products 7.8e-8).  Six v_mfma_f32_16x16x32_bf16 replace eight
 // v_mfma_f32_16x16x4_f32, which take 2.7 times as long.
 //
-// A work-group of eight wavefronts takes one filter and every gridDim.y-th
+// A work-group of eight wavefronts, or four, takes one filter and every gridDim.y-th
 // batch of its rows (all queries, or the filter's listed (query, leaf)
 // pairs).  The filter's W1 is read once and kept as bf16 parts in registers:
 // wavefront w holds the HT 16-unit hidden tiles of hidden group w mod wh for
@@ -20,7 +20,10 @@
 // work-group into three LDS planes (row stride 8 elements past the inputs, so
 // the 16 rows of an operand read start in different banks), and read from
 // there as the B operand.  With m = h = 256 the parts of W1 take 192 of a
-// lane's 256 registers: one work-group per CU, two wavefronts per SIMD.
+// lane's 256 registers: one work-group per CU, two wavefronts per SIMD.  With
+// more filters than CUs, narrow ones are dealt to work-groups of half the size,
+// two and more per CU, whose waits overlap: the read and split of a filter's W1
+// is most of a small call.
 // What bounds it is the matrix cores (45 % of the wavefronts' cycles, at the
 // clock the chip holds under them), then the split and the two barriers of a
 // batch, and the read of W1 at its start.  1,024 filters x 500 rows, m = h =
@@ -44,9 +47,8 @@ namespace leafi {
 
 namespace {
 
-constexpr int kSplitWaves = 8;
-constexpr int kSplitThreads = kWave * kSplitWaves;
-constexpr int kSplitPre = 6;  // 16-byte pieces of a batch per thread: rows x padded inputs <= 12,288
+constexpr int kSplitWaves = 8;  // most wavefronts of a work-group (4 or 8)
+constexpr int kSplitPre = 6;    // 16-byte pieces of a batch per thread: of eight wavefronts, rows x padded inputs <= 12,288
 
 struct SplitArgs {
   const float *w;
@@ -87,7 +89,7 @@ __device__ __forceinline__ void split_plain_rows(const float *__restrict__ wf, i
                                               float *red) {
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const float *b1 = wf + static_cast<int64_t>(h) * m, *w2 = b1 + h;
-  for (int c = wave; c < nr; c += kSplitWaves) {
+  for (int c = wave; c < nr; c += blockDim.x / kWave) {
     if (!all && rowbad[c] == 0) continue;  // uniform
     const float *xr = x + rowq[c] * m;
     float p = 0.0f;
@@ -113,9 +115,10 @@ size_t split_lds(const SplitArgs &a, int ks, int ht) {
   return rb * a.m * 4 + 3 * rb * (32 * ks + 8) * 2 + 2 * static_cast<size_t>(16 * ht * a.wh) * 4 + 2 * a.wh * rb * 4 + 4 * rb * 8 + rb * 4 + 16;
 }
 
-template <int KS, int HT>
-__global__ void __launch_bounds__(kSplitThreads, 2) k_mlp_infer_split(SplitArgs a) {
+template <int KS, int HT, int NW>
+__global__ void __launch_bounds__(kWave * NW, 2) k_mlp_infer_split(SplitArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int kSplitThreads = kWave * NW;
   constexpr int MP = 32 * KS + 8;  // row stride of the planes
   const int f = blockIdx.x;
   const int64_t n = a.plist ? static_cast<int64_t>(a.pcnt[f]) : a.nq;
@@ -329,31 +332,40 @@ __global__ void __launch_bounds__(kSplitThreads, 2) k_mlp_infer_split(SplitArgs 
 }
 
 template <int KS, int HT>
-void split_launch(const SplitArgs &a, dim3 grid, hipStream_t st) {
+void split_launch(const SplitArgs &a, int waves, dim3 grid, hipStream_t st) {
   const size_t lds = split_lds(a, KS, HT);
-  auto kern = k_mlp_infer_split<KS, HT>;
+  auto kern = waves == 4 ? k_mlp_infer_split<KS, HT, 4> : k_mlp_infer_split<KS, HT, kSplitWaves>;
   allow_lds(reinterpret_cast<const void *>(kern), lds);
-  hipLaunchKernelGGL(kern, grid, dim3(kSplitThreads), lds, st, a);
+  hipLaunchKernelGGL(kern, grid, dim3(kWave * waves), lds, st, a);
   LAUNCH_OK("mlp_infer_split");
 }
 
 template <int KS>
-void split_launch_ht(int ht, const SplitArgs &a, dim3 grid, hipStream_t st) {
+void split_launch_ht(int ht, const SplitArgs &a, int waves, dim3 grid, hipStream_t st) {
   if constexpr (KS <= 3)
-    if (ht == 4) return split_launch<KS, 4>(a, grid, st);
+    if (ht == 4) return split_launch<KS, 4>(a, waves, grid, st);
   if constexpr (KS <= 4)
-    if (ht == 3) return split_launch<KS, 3>(a, grid, st);
-  if (ht == 2) return split_launch<KS, 2>(a, grid, st);
-  split_launch<KS, 1>(a, grid, st);
+    if (ht == 3) return split_launch<KS, 3>(a, waves, grid, st);
+  if (ht == 2) return split_launch<KS, 2>(a, waves, grid, st);
+  split_launch<KS, 1>(a, waves, grid, st);
 }
 
 }  // namespace
 
-// The arrangement of the eight wavefronts: HT hidden tiles per wavefront (as
-// many as its 256 registers hold the parts and accumulators of) in wh hidden groups x wr row groups, by the row tiles finished per unit of
-// time (wr / HT), then by more hidden tiles (each operand read from LDS
-// serves more products).  With listed pairs, whose numbers only the device
-// knows, an eighth of the queries stands for a filter's rows.
+// The arrangement of eight wavefronts: HT hidden tiles per wavefront (as many
+// as its 256 registers hold the parts and accumulators of) in wh hidden groups
+// x wr row groups, by the row tiles finished per unit of time (wr / HT), then by
+// more hidden tiles (each operand read from LDS serves more products).  With
+// listed pairs, whose numbers only the device knows, an eighth of the queries
+// stands for a filter's rows.
+//
+// Four wavefronts hold the same HT and wh, so the same sums, with fewer row
+// groups, where there are more filters than CUs and up to four hidden groups,
+// as many rows at a time as let a second work-group share the CU's LDS: for up
+// to 128 inputs (1,024 filters 96 -> 96: one row 33 -> 17 us, 500 rows 96 -> 84;
+// the FP32 kernel that kept W1 in registers 20 and 271), above that, where the
+// batches would be of 16 rows, for dense calls of up to 32 (256 -> 64, one row: 34 ->
+// 18 us).
 //
 // Which filters are evaluated here follows from the filters alone (their
 // number and sizes), never from the rows of a call: a prediction's bits are
@@ -386,6 +398,21 @@ bool launch_mlp_infer_split(const float *w, int F, int m, int h, const float *x,
   const bool narrow = ks <= 4 && a.wh <= 4;
   if (!narrow && (m % 16 != 0 || h % 16 != 0)) return false;
   a.rt = small_batches ? 1 : std::max(1, std::min(3, tiles / a.wr));
+  int waves = kSplitWaves;
+  if (F > device_cus() && a.wh <= 4 && (ks <= 4 || (!plist && nq <= 32))) {
+    waves = 4;
+    a.wr = std::min(waves / a.wh, tiles);
+    a.rt = small_batches ? 1 : std::min(3, tiles / a.wr);
+  }
+  if (!plist) {  // no LDS for rows that a call does not have
+    const int need = static_cast<int>(std::min<int64_t>(ceil_div(nq, 16), tiles));
+    a.wr = std::min(a.wr, need);
+    a.rt = std::min<int>(a.rt, ceil_div(need, a.wr));
+  }
+  auto fits = [&] {
+    return split_rows(a) * m / 4 <= kSplitPre * kWave * waves && (waves == kSplitWaves || split_lds(a, ks, ht) <= 80 * 1024);
+  };
+  while (!fits()) --(a.rt > 1 ? a.rt : a.wr);
   // how many work-groups share a filter: rounds of the chip x (the read of W1,
   // about three batches' time, and the batches of one)
   const int64_t nb = std::max<int64_t>(1, ceil_div(plist ? ceil_div(stride, 8) : nq, split_rows(a)));
@@ -400,14 +427,14 @@ bool launch_mlp_infer_split(const float *w, int F, int m, int h, const float *x,
   }
   const dim3 grid(F, share);
   switch (ks) {
-    case 1: split_launch_ht<1>(ht, a, grid, st); break;
-    case 2: split_launch_ht<2>(ht, a, grid, st); break;
-    case 3: split_launch_ht<3>(ht, a, grid, st); break;
-    case 4: split_launch_ht<4>(ht, a, grid, st); break;
-    case 5: split_launch_ht<5>(ht, a, grid, st); break;
-    case 6: split_launch_ht<6>(ht, a, grid, st); break;
-    case 7: split_launch_ht<7>(ht, a, grid, st); break;
-    default: split_launch_ht<8>(ht, a, grid, st); break;
+    case 1: split_launch_ht<1>(ht, a, waves, grid, st); break;
+    case 2: split_launch_ht<2>(ht, a, waves, grid, st); break;
+    case 3: split_launch_ht<3>(ht, a, waves, grid, st); break;
+    case 4: split_launch_ht<4>(ht, a, waves, grid, st); break;
+    case 5: split_launch_ht<5>(ht, a, waves, grid, st); break;
+    case 6: split_launch_ht<6>(ht, a, waves, grid, st); break;
+    case 7: split_launch_ht<7>(ht, a, waves, grid, st); break;
+    default: split_launch_ht<8>(ht, a, waves, grid, st); break;
   }
   return true;
 }

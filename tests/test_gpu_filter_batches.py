@@ -40,7 +40,8 @@ def test_rows_beside_rows_that_are_not_finite(F, m, h):
 
 
 @pytest.mark.parametrize("F,m,h", [(3, 256, 256), (64, 128, 128), (128, 256, 256), (255, 96, 96), (256, 96, 96),
-                                   (300, 100, 100), (300, 228, 144), (520, 256, 256), (1024, 32, 64)])
+                                   (300, 100, 100), (300, 228, 144), (520, 256, 256), (1024, 32, 64),
+                                   (300, 256, 64), (520, 160, 128), (300, 68, 36), (300, 128, 256)])
 def test_rows_in_calls_of_any_size(F, m, h):
     pkg = _pkg()
     w = torch.from_numpy(W.mlp_weights(F, m, h, seed=F + h)).cuda()
