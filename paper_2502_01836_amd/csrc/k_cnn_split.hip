@@ -112,7 +112,7 @@ __global__ void __launch_bounds__(KS <= 9 ? 768 : 512, KS <= 9 ? 3 : 2) k_cnn_in
   // kb): input channels 32 kb + 8 q .. + 8
   bf16x8 W[KS][3];
   float b2[4], w3[4];
-  uint32_t bigw = 0;
+  bool oddw = false;
   {
     const int o = 16 * tile + col;
 #pragma unroll
@@ -128,10 +128,7 @@ __global__ void __launch_bounds__(KS <= 9 ? 768 : 512, KS <= 9 ? 3 : 2) k_cnn_in
         for (int t = 0; t < 3; ++t) raw[t][e] = in ? p[t] : 0.0f;
       }
 #pragma unroll
-      for (int t = 0; t < 3; ++t) {
-        const uint32_t g = split8(raw[t], W[3 * kb + t][0], W[3 * kb + t][1], W[3 * kb + t][2]);
-        bigw = g > bigw ? g : bigw;
-      }
+      for (int t = 0; t < 3; ++t) oddw |= split8(raw[t], W[3 * kb + t][0], W[3 * kb + t][1], W[3 * kb + t][2]);
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {  // the products' output rows: channels 16 tile + 4 q + r
@@ -160,15 +157,14 @@ __global__ void __launch_bounds__(KS <= 9 ? 768 : 512, KS <= 9 ? 3 : 2) k_cnn_in
   auto first_layer = [&](int j) {
     const float *xp = xs + (j % 3) * xrow;
     uint16_t *pl = planes + 3 * (j & 1) * plane;
-    uint32_t big = 0;
+    SplitRange range;
     if (first)
       for (int p = p0; p < m; p += per) {
         const float4 v = make_float4(conv_first(w1s[4 * cg], xp, p), conv_first(w1s[4 * cg + 1], xp, p),
                                      conv_first(w1s[4 * cg + 2], xp, p), conv_first(w1s[4 * cg + 3], xp, p));
-        const uint32_t g = split_store4(v, pl, plane, (cg >> 1) * rows8 + 8 * (p + 1) + 4 * (cg & 1));
-        big = g > big ? g : big;
+        split_store4(v, pl, plane, (cg >> 1) * rows8 + 8 * (p + 1) + 4 * (cg & 1), range);
       }
-    if (big >= kSplitHuge) bad[j & 3] = 1;
+    if (range.exceeded()) bad[j & 3] = 1;
   };
   auto write_out = [&](int64_t e, int j) {
     float y = 0.0f;
@@ -180,7 +176,7 @@ __global__ void __launch_bounds__(KS <= 9 ? 768 : 512, KS <= 9 ? 3 : 2) k_cnn_in
   const int64_t step = gridDim.y;
   int64_t i = blockIdx.y, e_cur = entry(i), e_prev = -1;
   __syncthreads();
-  if (bigw >= kSplitHuge) bad[4] = 1;
+  if (oddw) bad[4] = 1;
   stage_row(e_cur, 0);
   __syncthreads();
   first_layer(0);

@@ -2,7 +2,7 @@
 // 256 inputs and 256 hidden units (any multiples of 4).
 //
 // Every FP32 operand is split into three bf16 parts, v = v0 + v1 + v2 (each
-// part the rounded remainder of the ones before, so 24 bits in all), and a
+// part the rounded remainder of the ones before, 24 bits in all), and a
 // product keeps the six terms of its parts down to 2^-18 of it: x0 w0, x0 w1,
 // x1 w0, x1 w1, x0 w2, x2 w0; the terms left out are 2^-26 of it.  The parts'
 // products are exact and are accumulated in FP32, the leading term apart from
@@ -31,9 +31,9 @@
 // 151); the 6.6M pairs of a 2,198-filter 96 -> 96 -> 1 batch: 3.9 -> 1.2 ms,
 // where the FP32 kernel had three of its eight wavefronts at work.
 //
-// bf16 parts of an infinity (or of a value that rounds to one) have no finite
-// remainder, so a row that holds one, or a NaN, is evaluated with plain FP32
-// arithmetic instead, and with such a weight every row of its filter.  The
+// A row that holds an infinity, a NaN or an operand out of the parts' range
+// (split_bf16.h) is evaluated with plain FP32 arithmetic instead, and with such
+// a weight every row of its filter.  The
 // other rows of its batch keep the matrix products' values (an operand column
 // reaches its own output column alone): what a row's prediction is does not
 // depend on the rows beside it.
@@ -226,15 +226,12 @@ __global__ void __launch_bounds__(kWave * NW, 2) k_mlp_infer_split(SplitArgs a) 
         }
     }
     __builtin_amdgcn_sched_barrier(0);
-    uint32_t big = 0;
+    bool odd = false;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-      for (int t = 0; t < HT; ++t) {
-        const uint32_t g = split8(raw[ks][t], W[t][ks][0], W[t][ks][1], W[t][ks][2]);
-        big = g > big ? g : big;
-      }
-    if (rg < wr && big >= kSplitHuge) bad[2] = 1;
+      for (int t = 0; t < HT; ++t) odd |= split8(raw[ks][t], W[t][ks][0], W[t][ks][1], W[t][ks][2]);
+    if (rg < wr && odd) bad[2] = 1;
   }
   fetch(0);
   int nr_prev = 0;
@@ -253,7 +250,7 @@ __global__ void __launch_bounds__(kWave * NW, 2) k_mlp_infer_split(SplitArgs a) 
     __syncthreads();  // the planes and the other slot's sums are complete
     write_out(s ^ 1, nr_prev);
     wait_lds_loads();  // each thread splits the pieces its own wavefront requested
-    uint32_t big = 0;
+    SplitRange range;
     {
       const int t = my_thread();
 #pragma unroll
@@ -262,17 +259,17 @@ __global__ void __launch_bounds__(kWave * NW, 2) k_mlp_infer_split(SplitArgs a) 
         const int c = static_cast<int>((static_cast<uint32_t>(e4) * inv4) >> 20);
         if (c < nr) {
           const float4 v = *reinterpret_cast<const float4 *>(raw + 4 * e4);
-          const uint32_t g = split_store4(v, planes, plane, c * MP + 4 * (e4 - c * m4));
-          big = g > big ? g : big;
+          split_store4(v, planes, plane, c * MP + 4 * (e4 - c * m4), range);
         }
       }
     }
-    if (big >= kSplitHuge) {  // rare: which of the thread's pieces
+    if (range.exceeded()) {  // rare: which of the thread's pieces
       bad[s] = 1;
-      for (int e4 = tid; e4 / m4 < nr; e4 += kSplitThreads)
-        if (split_store4(*reinterpret_cast<const float4 *>(raw + 4 * e4), planes, plane,
-                         e4 / m4 * MP + 4 * (e4 % m4)) >= kSplitHuge)
-          rowbad[e4 / m4] = 1;
+      for (int e4 = tid; e4 / m4 < nr; e4 += kSplitThreads) {
+        SplitRange piece;
+        split_store4(*reinterpret_cast<const float4 *>(raw + 4 * e4), planes, plane, e4 / m4 * MP + 4 * (e4 % m4), piece);
+        if (piece.exceeded()) rowbad[e4 / m4] = 1;
+      }
     }
     find_rows(b + gridDim.y, s ^ 1);
     __syncthreads();

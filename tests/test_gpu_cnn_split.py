@@ -69,3 +69,34 @@ def test_split_cnn_inference_with_values_that_are_not_finite():
         assert fin.sum() >= (9 if f != 1 else 0)
         assert np.all(np.abs(got[fin, f] - want[fin]) <= (4 * C + m + 11) * 2.0 ** -24 * mag[fin])
         assert np.array_equal(np.isfinite(got[:, f]), np.isfinite(want))
+
+
+@pytest.mark.parametrize("m,C", [(40, 20), (96, 96)])
+@pytest.mark.parametrize("ea,ew,eo", [(0, 0, 0), (58, -58, 0), (105, -105, 0), (118, -118, 0), (-105, 105, 0), (-118, 118, 0),
+                                      (0, -122, 122), (-122, 0, 122)])
+def test_operands_at_the_ends_of_the_range(m, C, ea, ew, eo):
+    """The first layer, the second and the readout times 2^ea, 2^ew and 2^eo:
+    FP32 accuracy, whatever a bf16 part can hold."""
+    pkg = _pkg()
+    w = W.cnn_weights(2, C, seed=9)
+    w[:, : 4 * C] *= np.float32(2.0 ** ea)
+    w[:, 4 * C: 4 * C + 3 * C * C] *= np.float32(2.0 ** ew)
+    w[:, 4 * C + 3 * C * C: 5 * C + 3 * C * C] = 0
+    w[:, 5 * C + 3 * C * C: -1] *= np.float32(2.0 ** eo)
+    w[:, -1] = 0
+    x = np.random.default_rng(m).standard_normal((7, m)).astype(np.float32)
+    got = pkg.cnn_infer(torch.from_numpy(w).cuda(), m, C, torch.from_numpy(x).cuda()).cpu().numpy()
+    for f in range(2):
+        want, mag = _forward(w[f], x, C)
+        assert np.all(np.abs(got[:, f] - want) <= (4 * C + m + 11) * 2.0 ** -24 * mag)
+
+
+def test_finite_operands_whose_products_overflow():
+    pkg = _pkg()
+    m, C = 40, 20
+    w = np.abs(W.cnn_weights(2, C, seed=10)) + np.float32(0.01)
+    w[:, : 4 * C] *= np.float32(1e25)
+    w[:, 4 * C: 4 * C + 3 * C * C] *= np.float32(1e25)
+    x = np.abs(np.random.default_rng(1).standard_normal((7, m))).astype(np.float32) + np.float32(0.01)
+    got = pkg.cnn_infer(torch.from_numpy(w).cuda(), m, C, torch.from_numpy(x).cuda()).cpu().numpy()
+    assert np.all(np.isposinf(got))

@@ -88,3 +88,42 @@ def test_many_filters_with_values_that_are_not_finite(m, h):
         rest = ~fin & (mag > 1e39)  # infinite in FP32 too
         assert np.array_equal(np.isfinite(got[rest, f]), np.isfinite(want[rest]) & (np.abs(want[rest]) < 3.4e38))
     assert got[3, 0] == w[0, -1]  # every hidden unit a NaN: the output bias alone
+
+
+@pytest.mark.parametrize("m,h", [(256, 256), (96, 96)])
+@pytest.mark.parametrize("ex,ew,eo", [(0, 0, 0), (58, -58, 0), (60, -60, 0), (105, -105, 0), (120, -120, 0), (-105, 105, 0),
+                                      (-120, 120, 0), (0, -112, 112), (0, -122, 122), (-122, 0, 122), (58, 58, -60),
+                                      (-60, -60, 120)])
+def test_operands_at_the_ends_of_the_range(m, h, ex, ew, eo):
+    """Inputs, first and output weights times 2^ex, 2^ew and 2^eo: FP32 accuracy
+    as long as FP32's own sums are in range, whatever a bf16 part can hold."""
+    pkg = _pkg()
+    F = 300
+    w, x = _draw(F, m, h, 97, 7)
+    w[:, : m * h] *= np.float32(2.0 ** ew)
+    w[:, m * h: m * h + h] = 0
+    w[:, m * h + h: -1] *= np.float32(2.0 ** eo)
+    w[:, -1] = 0
+    x *= np.float32(2.0 ** ex)
+    got = pkg.mlp_infer(torch.from_numpy(w).cuda(), m, h, torch.from_numpy(x).cuda()).cpu().numpy()
+    for f in (0, 7, F - 1):
+        want, mag = _forward(w[f], x, m, h)
+        assert np.all(np.abs(got[:, f] - want) <= (m + h + 8) * 2.0 ** -24 * mag)
+
+
+@pytest.mark.parametrize("m,h", [(256, 256), (96, 96)])
+def test_finite_operands_whose_products_overflow(m, h):
+    """Every term positive and beyond the largest float: infinity, not what
+    +inf and -inf of its parts would leave."""
+    pkg = _pkg()
+    F = 300
+    w, x = _draw(F, m, h, 97, 8)
+    w, x = np.abs(w), np.abs(x)
+    w[:, : m * h] = (w[:, : m * h] + np.float32(0.01)) * np.float32(1e25)
+    y = (x + np.float32(0.01)) * np.float32(1e25)
+    y[1::2] = x[1::2]  # rows in range between them
+    got = pkg.mlp_infer(torch.from_numpy(w).cuda(), m, h, torch.from_numpy(y).cuda()).cpu().numpy()
+    assert np.all(np.isposinf(got[0::2]))
+    for f in (0, 7, F - 1):
+        want, mag = _forward(w[f], y[1::2], m, h)
+        assert np.all(np.abs(got[1::2, f] - want) <= (m + h + 8) * 2.0 ** -24 * mag)
