@@ -126,7 +126,10 @@ struct Builder {
       std::vector<int64_t> idx(n);
       for (int64_t i = 0; i < n; ++i) idx[i] = i;
       const int64_t nl = (n + 1) / 2;
-      auto less = [&](int64_t a, int64_t b) { return col[a] < col[b] || (col[a] == col[b] && a < b); };
+      // (NaN after every number, as on the device: left unordered, a pivot that
+      // is one would send every member left, without end)
+      auto below = [](float x, float y) { return x < y || (x == x && y != y); };
+      auto less = [&](int64_t a, int64_t b) { return below(col[a], col[b]) || (!below(col[b], col[a]) && a < b); };
       std::nth_element(idx.begin(), idx.begin() + (nl - 1), idx.end(), less);
       const int64_t pivot = idx[nl - 1];
       for (int64_t i = 0; i < n; ++i) go_left[i] = !less(pivot, i);

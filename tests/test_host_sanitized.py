@@ -169,3 +169,22 @@ def test_calibration_matches_oracle(harness, calib_case, mapping, corrected):
             assert np.array_equal(np.isinf(got[b]), np.isinf(want)), (k, t)
             fin = np.isfinite(want)
             assert np.allclose(got[b][fin], want[fin], rtol=1e-6, atol=1e-7), (k, t)
+
+
+@pytest.mark.parametrize("rule", [0, 1, 2])
+@pytest.mark.parametrize("share", [0.05, 0.6, 1.0])
+def test_tree_of_series_that_are_not_finite(harness, rule, share):
+    """Series with NaN statistics (from a NaN or an infinity in the series) end
+    up in leaves like any other, within the capacity of a binary tree."""
+    n, S, m, cap = 700, 5, 40, 13
+    g = np.random.default_rng(int(100 * share))
+    mu, sd = g.standard_normal((n, S)).astype(np.float32), g.random((n, S), dtype=np.float32)
+    bad = g.random(n) < share
+    mu[bad], sd[bad] = np.nan, np.nan
+    leaves, boxes = _tree(harness, mu, sd, m, cap, rule)
+    assert np.array_equal(np.sort(np.concatenate(leaves)), np.arange(n))
+    assert rule == 2 or max(len(l) for l in leaves) <= cap
+    for l, box in zip(leaves, boxes):
+        f = l[~bad[l]]
+        assert (mu[f] >= box[:, 0]).all() and (mu[f] <= box[:, 1]).all()
+        assert (sd[f] >= box[:, 2]).all() and (sd[f] <= box[:, 3]).all()
