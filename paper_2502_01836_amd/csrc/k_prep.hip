@@ -94,6 +94,8 @@ __global__ void __launch_bounds__(256) k_series_stats(const float *__restrict__ 
 // whole: stored row by row, 16 bytes here and there of its 128-byte lines,
 // 1M rows of 256 took 5.3 ms with an atomic per row on their leaf's word, 1.6
 // without (2.5 GB of traffic: 0.5 at the rate of a copy); now 1.4.
+// A series that is not finite (its normalised values are NaN) is stored for the
+// bf16 scan as infinitely far, and has no say in its leaf's rounding radius.
 __global__ void __launch_bounds__(16 * kWave) k_pack(const float *__restrict__ raw, const int64_t *__restrict__ src_of_row,
                                                      const int32_t *__restrict__ leaf_of_row, int64_t rows, int m,
                                                      const double *__restrict__ mean, const double *__restrict__ sdv,
@@ -130,14 +132,17 @@ __global__ void __launch_bounds__(16 * kWave) k_pack(const float *__restrict__ r
     }
     nrm = wave_sum(nrm);
     err = wave_sum(err);
+    const bool finite = nrm < __builtin_inff();
+    if (!finite)  // a NaN's distance would come out as 0, the least
+      for (int t = lane; t < m; t += kWave) panel[panel_index(rr, t)] = 0;
     if (lane == 0) {
-      xn16[row] = nrm;
+      xn16[row] = finite ? nrm : __builtin_inff();
       rowid[row] = src;
       // non-negative floats order like their bit patterns; most rows are
       // below their leaf's largest so far
       const float e = sqrtf(err) * (1.0f + 1e-5f);
       float *to = leaf_eps + leaf_of_row[row];
-      if (e > __hip_atomic_load(to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      if (finite && e > __hip_atomic_load(to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
         atomicMax(reinterpret_cast<unsigned int *>(to), f2u(e));
     }
   }

@@ -429,12 +429,13 @@ __global__ void __launch_bounds__(256, 3) k_item_rerank(StoreView s, QueryView q
         wave_lds_sync();
       }
       const uint64_t kth = keys[kp - 1];
-      // the real candidates among the first kp; in search rounds only those
+      // the real candidates among the first kp (not those at no finite
+      // distance: their series are not finite); in search rounds only those
       // that can still enter the query's top k (lower bound not above U)
       int nc = 0;
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        bool use = best[r] != kKeyMax;
+        bool use = static_cast<uint32_t>(best[r] >> 32) < f2u(__builtin_inff());
         if (use && use_bound) {
           const double v = static_cast<double>(key_d2(best[r])) - dq;
           const double lower = (v > 0.0 ? sqrt(v) : 0.0) - qe_q - le_L;
