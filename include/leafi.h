@@ -437,19 +437,21 @@ typedef struct {
 /*
  * Time the sample batch (queries_dev [nq, m], k_dev, target_dev and opts as
  * for leafi_search_knn, BF16 scan) once per candidate tile shape -- rows per
- * tile in {512, 1024, 2048} times 16, 32, 48 or 64 queries per tile --
- * `repeats` times each after one warm-up, and keep the shape with the
- * smallest median for all later searches of this index.  Results of every search are identical under every shape.
- * The stream is synchronised.  `report` (host) may be NULL.
+ * tile in {512, 1024, 2048} times 16, 32, 48 or 64 queries per tile, 1024 x 32
+ * standing for the default (see leafi_set_tiling) -- `repeats` times each
+ * after one warm-up, and keep the shape with the smallest median for all
+ * later searches of this index.  Results of every search are identical under
+ * every shape.  The stream is synchronised.  `report` (host) may be NULL.
  */
 int leafi_autotune(leafi_index *index, const float *queries_dev, int64_t nq, const int32_t *k_dev,
                    const float *target_dev, const leafi_search_opts *opts, int32_t repeats,
                    leafi_tune_report *report, void *stream);
 
-/* Set the BF16 scan's tile shape directly (what leafi_autotune chooses):
- * chunk_rows in {128, 256, ..., 4096}; queries_per_tile 16, 32, 48 or 64.
- * By default each pass's shape follows from its sizes (1024 rows and 32
- * queries in leafi_search_knn_noalloc).  Results do not depend on the shape. */
+/* Set the tile shape of this index's BF16 searches directly (what
+ * leafi_autotune chooses): chunk_rows in {128, 256, ..., 4096};
+ * queries_per_tile 16, 32, 48 or 64.  1024 and 32 are the default: each
+ * pass's shape then follows from its sizes (in leafi_search_knn_noalloc it is
+ * 1024 x 32 itself).  Results do not depend on the shape. */
 int leafi_set_tiling(leafi_index *index, int32_t chunk_rows, int32_t queries_per_tile);
 
 /* Item capacity of a planned batch's passes (see leafi_search_knn): at most

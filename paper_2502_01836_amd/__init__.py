@@ -367,6 +367,7 @@ class Index:
                            "ms": rep.ms[rep.chosen]}}
 
     def set_tiling(self, chunk_rows: int = 1024, queries_per_tile: int = 32):
+        """Tile shape of the BF16 searches; the defaults restore the choice per pass."""
         check(load().leafi_set_tiling(self._h, chunk_rows, queries_per_tile))
 
     def graph_note(self) -> str:

@@ -340,13 +340,13 @@ int pick_chunk(const leafi_index *ix, int kprime, int pref) {
 // queries 116 -> 108 us and one query at 1M 169 -> 166 (256 rows); 1M x 256,
 // 1,000 queries 354 and 356.  An all-pairs pass, whose
 // lists fill once per tile however long it is, takes 4,096 rows (500 queries
-// x 128 leaves 1,618 -> 1,465 us).  A round of one leaf per query keeps 16
-// queries per tile (few share a leaf).
+// x 128 leaves 1,618 -> 1,465 us), whatever shape the caller's searches use.  A
+// round of one leaf per query keeps 16 queries per tile (few share a leaf).
 constexpr int kShapeTiles = 2048;  // tiles a pass should have before its tiles grow longer
 PassShape pass_shape(const leafi_index *ix, bool bf16, int kprime, const ItemsEst &est, bool one_leaf) {
   PassShape s;
   int chunk = bf16 ? kChunkRows : kFp32ChunkRows, mq = 32;
-  if (bf16 && ix->tune_mq > 0) {
+  if (bf16 && ix->tune_mq > 0 && !est.all_pairs) {
     chunk = ix->tune_chunk;
     mq = one_leaf ? 16 : ix->tune_mq;
   } else if (bf16 && est.items >= 0) {
@@ -1936,6 +1936,14 @@ int leafi_set_plan_capacity(leafi_index *ix, int64_t max_items) {
   });
 }
 
+// The shape that the caller names or the tuner times: 1,024 rows x 32 queries
+// stand for the default, which chooses per pass (pass_shape).
+static void use_tiling(leafi_index *ix, int chunk, int mq) {
+  const bool automatic = chunk == kChunkRows && mq == 32;
+  ix->tune_chunk = automatic ? 0 : chunk;
+  ix->tune_mq = automatic ? 0 : mq;
+}
+
 int leafi_set_tiling(leafi_index *ix, int32_t chunk_rows, int32_t queries_per_tile) {
   return guarded([&] {
     require_built(ix);
@@ -1945,8 +1953,7 @@ int leafi_set_tiling(leafi_index *ix, int32_t chunk_rows, int32_t queries_per_ti
     LEAFI_CHECK_ARG(queries_per_tile == 16 || queries_per_tile == 32 || queries_per_tile == 48 ||
                         queries_per_tile == 64,
                     "queries_per_tile must be 16, 32, 48 or 64");
-    ix->tune_chunk = chunk_rows;
-    ix->tune_mq = queries_per_tile;
+    use_tiling(ix, chunk_rows, queries_per_tile);
   });
 }
 
@@ -1974,8 +1981,7 @@ int leafi_autotune(leafi_index *ix, const float *queries, int64_t nq, const int3
     const int old_chunk = ix->tune_chunk, old_mq = ix->tune_mq;
     try {
       for (size_t c = 0; c < cand.size(); ++c) {
-        ix->tune_chunk = cand[c].first;
-        ix->tune_mq = cand[c].second;
+        use_tiling(ix, cand[c].first, cand[c].second);
         std::vector<double> t;
         for (int r = 0; r <= repeats; ++r) {
           HIP_OK(hipEventRecord(e0, st));
@@ -2000,8 +2006,7 @@ int leafi_autotune(leafi_index *ix, const float *queries, int64_t nq, const int3
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     const size_t best = static_cast<size_t>(std::min_element(med.begin(), med.end()) - med.begin());
-    ix->tune_chunk = cand[best].first;
-    ix->tune_mq = cand[best].second;
+    use_tiling(ix, cand[best].first, cand[best].second);
     if (report) {
       std::memset(report, 0, sizeof(*report));
       report->n_candidates = static_cast<int32_t>(cand.size());

@@ -220,8 +220,8 @@ struct leafi_index {
   int64_t plan_items_seen = 0;
   int64_t plan_tiles_seen = 0;
   double dev_mem = 0.0;  // the device's memory (bytes)
-  // BF16 scan tiling (set by leafi_autotune or leafi_set_tiling): rows and
-  // queries per tile; 0: chosen per pass (pass_shape)
+  // BF16 scan tiling of the searches (set by leafi_autotune or leafi_set_tiling):
+  // rows and queries per tile; 0: chosen per pass (pass_shape)
   int tune_chunk = 0;
   int tune_mq = 0;
   ~leafi_index();
