@@ -19,8 +19,10 @@
  *     resident device memory it allocates (leaf store, filters, tables); it
  *     is released by leafi_destroy().
  *   - `stream` is a hipStream_t (NULL = the default stream).  Kernels are
- *     enqueued on it; calls return once their results are on the device
- *     (they may synchronise the stream to read small control values).
+ *     enqueued on it; calls return once their results are on the device, with
+ *     these exceptions, which may return as soon as the work is enqueued:
+ *     leafi_search_knn without statistics, leafi_search_knn_noalloc,
+ *     leafi_znorm, leafi_mlp_infer, leafi_mlp_sgd_step and leafi_cnn_infer.
  *   - Matrices are row-major.  Series and queries are raw fp32; the library
  *     z-normalises them itself (mean and population standard deviation in
  *     FP64; a series whose deviation is below 1e-8 becomes all zeros).
@@ -567,7 +569,8 @@ int leafi_cnn_infer(const float *weights_dev, int32_t n_filters, int32_t m, int3
 
 /* One plain SGD step per CNN filter on its own batch (as leafi_mlp_sgd_step):
  * x_dev [n_filters, batch, m], y_dev [n_filters, batch]; loss_dev
- * [n_filters] receives the batch loss before the step. */
+ * [n_filters] receives the batch loss before the step.  Returns once the
+ * step is done. */
 int leafi_cnn_sgd_step(float *weights_dev, int32_t n_filters, int32_t m, int32_t channels, const float *x_dev,
                        const float *y_dev, int32_t batch, float lr, float *loss_dev, void *stream);
 

@@ -2093,10 +2093,12 @@ int leafi_cnn_sgd_step(float *w, int32_t F, int32_t m, int32_t C, const float *x
     LEAFI_CHECK_ARG(w && x && y && loss, "NULL pointer");
     LEAFI_CHECK_ARG(F <= 65535, "too many filters in one call");
     hipStream_t st = as_stream(stream);
-    if (launch_cnn_sgd_step_mfma(w, F, m, C, x, y, batch, lr, loss, st)) return;
-    DevBuf<float> gbuf(static_cast<size_t>(F) * cnn_param_count(C));
-    launch_cnn_sgd_step(w, F, m, C, x, y, batch, lr, loss, gbuf.get(), st);
-    HIP_OK(hipStreamSynchronize(st));  // gbuf is freed on return
+    DevBuf<float> gbuf;
+    if (!launch_cnn_sgd_step_mfma(w, F, m, C, x, y, batch, lr, loss, st)) {
+      gbuf.alloc(static_cast<size_t>(F) * cnn_param_count(C));
+      launch_cnn_sgd_step(w, F, m, C, x, y, batch, lr, loss, gbuf.get(), st);
+    }
+    HIP_OK(hipStreamSynchronize(st));  // the step is done on return (and gbuf is freed)
   });
 }
 

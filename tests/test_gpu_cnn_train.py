@@ -63,3 +63,18 @@ def test_cnn_steps_in_a_row_and_alone_agree():
         for _ in range(5):
             pkg.cnn_sgd_step(wt, m, C, x[f:f + 1].contiguous(), y[f:f + 1].contiguous(), 0.02)
         assert torch.equal(wt[0].cpu(), runs[0][f])
+
+
+@pytest.mark.parametrize("F,m,C,B", [(128, 96, 32, 32), (16, 132, 84, 4)])
+def test_cnn_step_is_done_on_return(F, m, C, B):
+    """Both kernels' calls return with the step's results on the device."""
+    pkg = _pkg()
+    w = torch.from_numpy(W.cnn_weights(F, C, seed=3)).cuda()
+    x, y = torch.randn((F, B, m), device="cuda"), torch.rand((F, B), device="cuda")
+    pkg.cnn_sgd_step(w, m, C, x, y, 0.02)
+    torch.cuda.synchronize()
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        for _ in range(3):
+            pkg.cnn_sgd_step(w, m, C, x, y, 0.02)
+            assert stream.query()
