@@ -1710,12 +1710,12 @@ int leafi_train_filters(leafi_index *ix, const leafi_train_opts *o, leafi_train_
       ta.val_trace = vtrace.get();
     }
     auto t2 = std::chrono::steady_clock::now();
-    if (cnn) {
+    if (!cnn) {
+      launch_mlp_train(ta, st);
+    } else if (!launch_cnn_train_mfma(ta, st)) {
       DevBuf<float> gbuf(static_cast<size_t>(F) * P);
       launch_cnn_train(ta, gbuf.get(), st);
       HIP_OK(hipStreamSynchronize(st));  // gbuf is freed on leaving the scope
-    } else {
-      launch_mlp_train(ta, st);
     }
     std::vector<float> hv(F);
     std::vector<int32_t> he(F);

@@ -496,7 +496,7 @@ void launch_cnn_infer_pairs(const float *w, int F, int m, int C, const float *x,
 
 void launch_cnn_train(const TrainArgs &a, float *gbuf, hipStream_t st) {
   check_cnn_shape(a.m, a.h);
-  if (a.F <= 0 || launch_cnn_train_mfma(a, st)) return;
+  if (a.F <= 0) return;
   const size_t lds = static_cast<size_t>(cnn_train_lds_floats(a.m, a.h)) * sizeof(float) +
                      static_cast<size_t>(a.n_train) * sizeof(int32_t);
   if (lds > 160 * 1024) fail(LEAFI_EINVAL, "CNN training: activations and shuffle table exceed the LDS");

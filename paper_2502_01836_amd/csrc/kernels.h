@@ -386,8 +386,8 @@ void launch_cnn_infer_pairs(const float *w, int F, int m, int C, const float *x,
 bool launch_cnn_train_mfma(const TrainArgs &a, hipStream_t st);
 bool launch_cnn_sgd_step_mfma(float *w, int F, int m, int C, const float *x, const float *y, int batch, float lr,
                               float *loss, hipStream_t st);
-// Full SGD training, one work-group per filter (a.h = channels); gbuf [F, P]
-// is gradient scratch (the matrix-core kernel where it holds the shape).
+// Full SGD training of other shapes, one work-group per filter (a.h =
+// channels); gbuf [F, P] is gradient scratch.
 void launch_cnn_train(const TrainArgs &a, float *gbuf, hipStream_t st);
 // One SGD step per filter on explicit batches; gbuf [F, P] scratch.
 void launch_cnn_sgd_step(float *w, int F, int m, int C, const float *x, const float *y, int batch, float lr,

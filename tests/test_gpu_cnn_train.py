@@ -78,3 +78,25 @@ def test_cnn_step_is_done_on_return(F, m, C, B):
         for _ in range(3):
             pkg.cnn_sgd_step(w, m, C, x, y, 0.02)
             assert stream.query()
+
+
+def test_cnn_training_allocates_no_gradients_it_does_not_use():
+    """Training on the matrix cores keeps the weights and the best ones, and no
+    third array of their size."""
+    pkg = _pkg()
+    sizes = []
+
+    class Counted(dict):
+        def __setitem__(self, ptr, nbytes):
+            sizes.append(nbytes)
+            super().__setitem__(ptr, nbytes)
+
+    alloc = pkg.TorchAllocator()
+    alloc.live = Counted()
+    ix = pkg.Index(allocator=alloc).build(torch.from_numpy(W.random_walk(2000, 32, seed=1)).cuda(), leaf_capacity=100,
+                                          n_segments=8)
+    F, C = ix.info()["n_leaves"], 16
+    sizes.clear()
+    ix.train_filters(n_global=60, n_local=10, max_epochs=2, seed=3, arch="cnn", hidden=C, th_override=0.0)
+    assert ix.info()["n_filters"] == F
+    assert sizes.count(4 * F * (3 * C * C + 6 * C + 1)) == 2
