@@ -89,66 +89,93 @@ __global__ void __launch_bounds__(256) k_series_stats(const float *__restrict__ 
   }
 }
 
-// The store's rows from the raw series: one work-group per 16-row panel, one
-// wavefront per row.  The bf16 panel is put together in LDS and written
-// whole: stored row by row, 16 bytes here and there of its 128-byte lines,
-// 1M rows of 256 took 5.3 ms with an atomic per row on their leaf's word, 1.6
-// without (2.5 GB of traffic: 0.5 at the rate of a copy); now 1.4.
+// The store's rows from the raw series: one work-group per 16-row panel, four
+// rows per wavefront, their loads in flight together.  The bf16 panel is put
+// together in LDS and written whole (stored row by row, 16 bytes here and there
+// of its 128-byte lines), and a leaf's rounding radius is touched once per panel:
+// neighbouring leaves' words share a line, and rows that each read it, and
+// raise it while it is low, waited for each other.  1M rows of 256: 5.5 ms with an atomic
+// per row, 1.42 with a read per row, now 0.82 (2.5 GB of traffic: 0.5 at the
+// rate of a copy); 200,000 of 96 in leaves of 390: 0.51, 1.06, 0.26; 6,000 of 64
+// in leaves of 7: 38 us, 146, 45.
 // A series that is not finite (its normalised values are NaN) is stored for the
 // bf16 scan as infinitely far, and has no say in its leaf's rounding radius.
-__global__ void __launch_bounds__(16 * kWave) k_pack(const float *__restrict__ raw, const int64_t *__restrict__ src_of_row,
-                                                     const int32_t *__restrict__ leaf_of_row, int64_t rows, int m,
-                                                     const double *__restrict__ mean, const double *__restrict__ sdv,
-                                                     float *x32, uint16_t *x16, float *xn16, int64_t *rowid,
-                                                     float *leaf_eps) {
+constexpr int kPackRows = 4;  // per wavefront
+__global__ void __launch_bounds__(256) k_pack(const float *__restrict__ raw, const int64_t *__restrict__ src_of_row,
+                                              const int32_t *__restrict__ leaf_of_row, int64_t rows, int m,
+                                              const double *__restrict__ mean, const double *__restrict__ sdv,
+                                              float *x32, uint16_t *x16, float *xn16, int64_t *rowid, float *leaf_eps) {
   __shared__ __align__(16) uint16_t panel[16 * kMaxBuildM];
-  const int lane = threadIdx.x & (kWave - 1), rr = threadIdx.x / kWave;
-  const int64_t row = static_cast<int64_t>(blockIdx.x) * 16 + rr;  // rows is a multiple of 16
-  const int64_t src = src_of_row[row];
-  float *o32 = x32 + row * m;
-  if (src < 0) {
-    for (int t = lane; t < m; t += kWave) {
-      o32[t] = 0.0f;
-      panel[panel_index(rr, t)] = 0;
+  __shared__ float s_eps[4];
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  const int64_t first = static_cast<int64_t>(blockIdx.x) * 16;  // rows is a multiple of 16
+  uint4 *o16 = reinterpret_cast<uint4 *>(x16 + first * m);
+  // a leaf's members come first: a panel whose first row is padding is padding
+  if (src_of_row[first] < 0) {  // uniform
+    const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
+    uint4 *p32 = reinterpret_cast<uint4 *>(x32 + first * m);
+    for (int i = threadIdx.x; i < 4 * m; i += 256) p32[i] = zero;
+    for (int i = threadIdx.x; i < 2 * m; i += 256) o16[i] = zero;
+    if (threadIdx.x < 16) {
+      xn16[first + threadIdx.x] = __builtin_inff();
+      rowid[first + threadIdx.x] = -1;
     }
-    if (lane == 0) {
-      xn16[row] = __builtin_inff();
-      rowid[row] = -1;
-    }
-  } else {
-    const float *r = raw + src * m;
-    const double mu = mean[src], sd = sdv[src];
-    float nrm = 0.0f, err = 0.0f;
-#pragma unroll 4
-    for (int t = lane; t < m; t += kWave) {
-      const float z = normalise(r[t], mu, sd);
+    return;
+  }
+  int64_t src[kPackRows];
+  double mu[kPackRows], sd[kPackRows];
+  float nrm[kPackRows], err[kPackRows];
+#pragma unroll
+  for (int r = 0; r < kPackRows; ++r) src[r] = src_of_row[first + kPackRows * w + r];
+#pragma unroll
+  for (int r = 0; r < kPackRows; ++r) {
+    mu[r] = mean[src[r] < 0 ? 0 : src[r]];
+    sd[r] = sdv[src[r] < 0 ? 0 : src[r]];
+    nrm[r] = err[r] = 0.0f;
+  }
+#pragma unroll 2
+  for (int t = lane; t < m; t += kWave) {
+    float x[kPackRows];
+#pragma unroll
+    for (int r = 0; r < kPackRows; ++r) x[r] = raw[(src[r] < 0 ? 0 : src[r]) * m + t];
+#pragma unroll
+    for (int r = 0; r < kPackRows; ++r) {
+      const int rr = kPackRows * w + r;
+      const float z = src[r] < 0 ? 0.0f : normalise(x[r], mu[r], sd[r]);
       const uint16_t b = f32_to_bf16(z);
       const float zb = bf16_to_f32(b);
-      o32[t] = z;
+      x32[(first + rr) * m + t] = z;
       panel[panel_index(rr, t)] = b;
-      nrm = fmaf(zb, zb, nrm);
+      nrm[r] = fmaf(zb, zb, nrm[r]);
       const float e = z - zb;
-      err = fmaf(e, e, err);
-    }
-    nrm = wave_sum(nrm);
-    err = wave_sum(err);
-    const bool finite = nrm < __builtin_inff();
-    if (!finite)  // a NaN's distance would come out as 0, the least
-      for (int t = lane; t < m; t += kWave) panel[panel_index(rr, t)] = 0;
-    if (lane == 0) {
-      xn16[row] = finite ? nrm : __builtin_inff();
-      rowid[row] = src;
-      // non-negative floats order like their bit patterns; most rows are
-      // below their leaf's largest so far
-      const float e = sqrtf(err) * (1.0f + 1e-5f);
-      float *to = leaf_eps + leaf_of_row[row];
-      if (finite && e > __hip_atomic_load(to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-        atomicMax(reinterpret_cast<unsigned int *>(to), f2u(e));
+      err[r] = fmaf(e, e, err[r]);
     }
   }
+  float eps = 0.0f;  // the largest rounding radius of the wavefront's rows
+#pragma unroll
+  for (int r = 0; r < kPackRows; ++r) {
+    const int rr = kPackRows * w + r;
+    const float n = wave_sum(nrm[r]), e = sqrtf(wave_sum(err[r])) * (1.0f + 1e-5f);
+    const bool finite = n < __builtin_inff();
+    if (finite) eps = fmaxf(eps, e);
+    else  // a NaN's distance would come out as 0, the least
+      for (int t = lane; t < m; t += kWave) panel[panel_index(rr, t)] = 0;
+    if (lane == 0) {
+      xn16[first + rr] = finite && src[r] >= 0 ? n : __builtin_inff();
+      rowid[first + rr] = src[r];
+    }
+  }
+  if (lane == 0) s_eps[w] = eps;
   __syncthreads();
-  uint4 *o16 = reinterpret_cast<uint4 *>(x16 + static_cast<int64_t>(blockIdx.x) * 16 * m);
-  for (int i = threadIdx.x; i < 2 * m; i += 16 * kWave) o16[i] = reinterpret_cast<const uint4 *>(panel)[i];
+  for (int i = threadIdx.x; i < 2 * m; i += 256) o16[i] = reinterpret_cast<const uint4 *>(panel)[i];
+  if (threadIdx.x == 0) {
+    // non-negative floats order like their bit patterns; most panels are
+    // below their leaf's largest so far
+    const float e = fmaxf(fmaxf(s_eps[0], s_eps[1]), fmaxf(s_eps[2], s_eps[3]));
+    float *to = leaf_eps + leaf_of_row[first];
+    if (e > __hip_atomic_load(to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(reinterpret_cast<unsigned int *>(to), f2u(e));
+  }
 }
 
 __global__ void __launch_bounds__(256) k_znorm(const float *x, int64_t n, int m, float *out) {
@@ -689,7 +716,7 @@ void launch_pack(const float *raw, const int64_t *src_of_row, const int32_t *lea
                  const double *mean, const double *sd, float *x32, uint16_t *x16, float *xn16, int64_t *rowid,
                  float *leaf_eps, hipStream_t st) {
   if (rows % 16 != 0) fail(LEAFI_EINTERNAL, "pack: rows not in whole panels");
-  hipLaunchKernelGGL(k_pack, dim3(static_cast<unsigned>(rows / 16)), dim3(16 * kWave), 0, st, raw, src_of_row,
+  hipLaunchKernelGGL(k_pack, dim3(static_cast<unsigned>(rows / 16)), dim3(256), 0, st, raw, src_of_row,
                      leaf_of_row, rows, m, mean, sd, x32, x16, xn16, rowid, leaf_eps);
   LAUNCH_OK("pack");
 }
