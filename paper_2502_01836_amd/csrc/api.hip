@@ -1127,10 +1127,14 @@ int leafi_create(leafi_alloc_fn alloc, leafi_free_fn free_fn, void *alloc_ctx, l
 void leafi_destroy(leafi_index *index) { delete index; }
 
 // Series from which a binary tree is built on the device, whose time is mostly
-// launches: index builds of m = 128 into 64 leaves, median splits, 5,000
-// series 0.78 ms on the host and 1.12 on the device, 10,000 1.91 and 1.36;
-// midpoint splits (deeper) 10,000 1.42 and 2.06, 20,000 2.49 and 2.46.
-constexpr int64_t kDeviceTreeMin[2] = {8192, 20000};
+// the launches of its levels, so that capacity and segments weigh little: both
+// sides grow with the levels.  Index builds of m = 64 with 4 and 16 segments
+// into 16, 64 and 512 leaves, on the host and on the device: median splits of
+// 8,192 series 0.87 to 2.4 ms and 0.75 to 1.8 (of 5,000, m = 128, 64 leaves,
+// 0.78 and 1.12).  Midpoint splits, deeper, of 20,000
+// 1.31 to 3.4 and 1.58 to 3.4 (16 leaves the slower by a fifth), of 24,000 1.53 to
+// 4.3 and 1.55 to 3.5.
+constexpr int64_t kDeviceTreeMin[2] = {8192, 24000};
 
 int leafi_build_index(leafi_index *ix, const float *series, int64_t n, int32_t m, const leafi_build_opts *opts,
                       void *stream) {

@@ -35,3 +35,10 @@ def test_device_tree_is_the_oracles(n, m, S, capacity, rule, distinct):
     boxes, want = ix.boxes(), O.leaf_boxes(mu, sd, t)
     # the summaries' own rounding (FP32 of FP64 sums) and the box's one ulp
     assert np.allclose(np.asarray(boxes).reshape(want.shape), want, rtol=1e-6, atol=1e-6)
+
+
+@pytest.mark.parametrize("n,m,S,capacity,rule,distinct", [
+    (9000, 32, 4, 1, "median", 0), (24000, 32, 4, 600, "midpoint", 0), (23999, 32, 4, 600, "midpoint", 0),
+    (26000, 64, 32, 300, "midpoint", 7)])
+def test_device_tree_of_single_series_and_at_the_midpoint_rules_edge(n, m, S, capacity, rule, distinct):
+    test_device_tree_is_the_oracles(n, m, S, capacity, rule, distinct)
