@@ -51,16 +51,16 @@ def test_rows_in_calls_of_any_size(F, m, h):
         assert torch.equal(pkg.mlp_infer(w, m, h, x[a:b].clone()), want[a:b]), (a, b)
 
 
-@pytest.mark.parametrize("arch", ["mlp", "cnn"])
-@pytest.mark.parametrize("n_leaves", [128, 256, 512])
-def test_listed_pairs_have_the_dense_predictions(arch, n_leaves):
+@pytest.mark.parametrize("arch,n_leaves,nq", [("mlp", 128, 300), ("mlp", 256, 300), ("mlp", 256, 2000), ("mlp", 512, 300),
+                                              ("cnn", 128, 60), ("cnn", 512, 60)])
+def test_listed_pairs_have_the_dense_predictions(arch, n_leaves, nq):
     """What a search subtracts its offsets from is what calibration fits them
     on.  Predictions of 1e9 and more stand a thousand apart, distances are
     below 50: with every offset the dense prediction itself no pair may be
     pruned, with the next float below it every pair that the search evaluates
     must be, for every query (each with a target, and so offsets, of its own)."""
     pkg = _pkg()
-    m, nq = (128, 300) if arch == "mlp" else (32, 60)
+    m = 128 if arch == "mlp" else 32
     h = m if arch == "mlp" else 8
     raw = W.random_walk(n_leaves * 40, m, seed=n_leaves)
     ix = pkg.Index().build(torch.from_numpy(raw).cuda(), leaf_capacity=40, n_segments=8)

@@ -127,3 +127,19 @@ def test_finite_operands_whose_products_overflow(m, h):
     for f in (0, 7, F - 1):
         want, mag = _forward(w[f], y[1::2], m, h)
         assert np.all(np.abs(got[1::2, f] - want) <= (m + h + 8) * 2.0 ** -24 * mag)
+
+
+@pytest.mark.parametrize("F,m,h,nq", [(300, 256, 256, 2000), (260, 240, 64, 1999), (300, 96, 96, 4001), (257, 32, 64, 3000)])
+def test_filters_that_share_their_rows_among_work_groups(F, m, h, nq):
+    """Batches enough that a filter's are dealt to several work-groups, the last
+    of them with a remainder, rows that are not finite among them."""
+    pkg = _pkg()
+    w, x = _draw(F, m, h, nq, F + nq)
+    odd = [0, 47, 48, nq // 2, nq - 1]
+    x[odd[0], 1], x[odd[1], 0], x[odd[2]], x[odd[3], 3], x[odd[4], 2] = np.nan, np.inf, np.nan, -np.inf, np.nan
+    got = pkg.mlp_infer(torch.from_numpy(w).cuda(), m, h, torch.from_numpy(x).cuda()).cpu().numpy()
+    fine = np.setdiff1d(np.arange(nq), odd)
+    for f in (0, 1, F // 2, F - 1):
+        want, mag = _forward(w[f], x, m, h)
+        assert np.all(np.abs(got[fine, f] - want[fine]) <= (m + h + 8) * 2.0 ** -24 * mag[fine])
+        assert got[48, f] == w[f, -1]  # every hidden unit a NaN: the output bias alone
