@@ -189,9 +189,9 @@ typedef struct {
  *   d^f(q) = b3 + sum_c w3[c] mean_p ReLU(z2[c][p]); packed as
  *   [W1 (C, 3) | b1 (C) | W2 (C_out, C_in, 3) | b2 (C) | w3 (C) | b3],
  *   P = 3C^2 + 6C + 1 floats.  m and C multiples of 4 whose inference fits
- *   the 160 KiB LDS (C = m = 96 does); else LEAFI_EINVAL.  Inference and
- *   training are plain FP32 (no matrix cores): t^F, and so Algorithm 3's
- *   size threshold, is far larger than the MLP's. */
+ *   the 160 KiB LDS (C = m = 96 does); else LEAFI_EINVAL.  An inference is
+ *   6 C^2 m flops, where the MLP's is 2 h m: t^F, and so Algorithm 3's size
+ *   threshold, is far larger than the MLP's. */
 #define LEAFI_FILTER_MLP 0
 #define LEAFI_FILTER_CNN 1
 

@@ -314,9 +314,13 @@ constexpr double kPreallocLimit = 1.0 * (1 << 30);
 // items_bound >= 0 is an upper bound of the round's items: buffers are sized
 // from it and nothing is read back.  Otherwise the counts are read back
 // first.  Returns the item count when it was read back, else -1.
-// Rows per scan tile for a pass: the preferred size, doubled while the
-// per-item merge of the chunk candidate lists (chunks x kprime keys) would
-// exceed kMaxRerankKeys.
+// Rows per scan tile for a pass: the preferred size, doubled while the largest
+// leaf's candidate lists (chunks x kprime keys) exceed kMaxRerankKeys: one
+// wavefront merges an item's lists one after the other, and with many of them
+// that chain outlasts the shorter scan of the tiles.  With and without the
+// limit, 1M series, schedule 1, 0: k = 256 over leaves of up to 10,000, one query
+// 288 and 319 us, 256 queries 647 and 648; k = 100 over leaves of 25,000, 235 and
+// 257, 747 and 915; k = 10 over leaves of 60,000, 171 and 211, 342 and 488.
 constexpr int kMaxRerankKeys = 4096;
 constexpr int kFp32ChunkRows = 128;  // the FP32 scan streams 4 m bytes per row: finer tiles
 // Tiles that an all-pairs rescan should have before they grow longer (73 items
@@ -459,8 +463,8 @@ int64_t scan_round(leafi_index *ix, int64_t nq, bool bf16, int kprime, int kmax,
   else launch_scan_fp32(s, q, b, mq, kprime, w.cand.get(), grid_scan, st);
   if (e1 && !ext) HIP_OK(hipEventRecord(e1, st));
   int64_t ib = items >= 0 ? items : std::max<int64_t>(items_bound, 1);
-  // one wavefront per item, a persistent grid of what is resident at once
-  // (three four-wavefront work-groups per CU)
+  // one wavefront per item, a persistent grid of what can be resident at once
+  // (four four-wavefront work-groups per CU, which its registers allow)
   int grid_r = static_cast<int>(std::min<int64_t>(ib, static_cast<int64_t>(ix->num_cus) * (ro->small ? 1 : 16)));
   // a search round's rerank skips candidates that cannot enter their query's
   // top k; not in a round of one leaf per query, whose bound comes from that

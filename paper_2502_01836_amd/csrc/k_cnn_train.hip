@@ -150,7 +150,7 @@ __device__ float ct_batch(float *wf, int nb, float lr, const CtShape &s, const C
     lane = tid & (kWave - 1);
     col = lane & 15;
     q = lane >> 4;
-    // rows past ne are stale: their errors are taken as zero below
+    // rows past ne are stale: no column tile reads them
     for (int i = tid; i < ne * m; i += kCtThreads) {
       const int e = i / m, p = i - e * m;
       l.xp[e * R + p + 1] = row(e0 + e)[p];

@@ -26,14 +26,12 @@ namespace {
 constexpr int kSelectMax = kCandFill;
 constexpr int kSelectPerLane = 16;
 
-// One wavefront per item.  LDS: merged keys [P], then per candidate the fp32
-// key, FP64 distance and row.
 // The kp smallest of an item's n chunk-list keys (kprime slots per chunk)
 // into buf (ascending, kKeyMax past the last real key): kp rounds of a
-// the keys above the previous one (keys are unique), U per lane in registers
-// (unconditional loads of clamped entries, so all of a lane's loads are in
-// flight together; the first kp <= kCandFill slots of each list, n = lists x
-// kp >= 1 in all, so entry 0 exists; n <= 64 U).
+// wavefront minimum over the keys above the round before's (keys are unique),
+// U per lane in registers (unconditional loads of clamped entries, so all of a
+// lane's loads are in flight together; the first kp <= kCandFill slots of each
+// list, n = lists x kp >= 1 in all, so entry 0 exists; n <= 64 U).
 template <int U>
 __device__ inline void select_keys(const uint64_t *__restrict__ cand, int64_t t0, int G, int g, int mq, int j,
                                    int kprime, int kp, int n, int lane, uint64_t *buf) {

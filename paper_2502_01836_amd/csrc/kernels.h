@@ -191,8 +191,10 @@ void launch_worklist(int64_t nq, int N, const float *lbs, const int32_t *order, 
 
 // (query, visit position) pairs whose filter test a later round can reach,
 // grouped by filter into plist [F, nq] (entries q * N + position) with counts
-// pcnt [F] (zeroed by the caller).  Every other position ahead of the cursor
-// gets dfo = -inf (never pruned by a filter).
+// pcnt [F] (zeroed by the caller).  The other positions ahead of the cursor that
+// tau's bound leaves get dfo = -inf (never pruned by a filter).  From the first
+// one that the bound prunes on, dfo is not written: tau only falls, so every
+// later walk ends there, by the bound, before it looks at a filter.
 void launch_filter_pairs(int64_t nq, int N, int F, const float *lbs, const int32_t *order, const int32_t *filt_of_leaf,
                          RoundBufs b, int64_t *plist, int32_t *pcnt, float *dfo, hipStream_t st,
                          const int32_t *qround = nullptr);
