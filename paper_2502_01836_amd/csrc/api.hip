@@ -370,10 +370,12 @@ PassShape pass_shape(const leafi_index *ix, bool bf16, int kprime, const ItemsEs
   scan_geometry(bf16, kprime, mq, ix->m, &s.mq, &s.cap);
   return s;
 }
-// Items of a search round of `want` leaves per query (0: every survivor, of
-// which an eighth of all leaves stands for what the bounds and filters leave).
-ItemsEst round_items_est(const leafi_index *ix, int64_t nq, int want) {
-  return ItemsEst{nq * (want == 0 ? std::max(1, ix->N / 8) : std::min(want, ix->N)), false};
+// Items of a search's round r of `want` leaves per query (0: every survivor, of
+// which an eighth of all leaves stands for what the bounds and filters leave;
+// all of them in a first round, which has no distance to prune by).
+ItemsEst round_items_est(const leafi_index *ix, int64_t nq, int r, int want) {
+  const int all = r == 0 ? ix->N : std::max(1, ix->N / 8);
+  return ItemsEst{nq * (want == 0 ? all : std::min(want, ix->N)), false};
 }
 
 int64_t tiles_bound(const leafi_index *ix, int64_t nq, int64_t items_bound, int mq, int chunk) {
@@ -612,7 +614,7 @@ void search_batch(leafi_index *ix, const float *raw, int64_t nq, const int32_t *
     launch_round_worklist(ix, nq, want, use_f && filters_ready, st, deferred > 0);
     const int64_t bound = nq * static_cast<int64_t>(want == 0 ? N : std::min(want, N)) + deferred;
     ro.one_leaf = r == 0 && want == 1;
-    ro.est = round_items_est(ix, nq, want);
+    ro.est = round_items_est(ix, nq, r, want);
     int64_t items = scan_round(ix, nq, p.bf16, p.kprime, p.kmax, st, stats ? &tm : nullptr, bound, &ro);
     if (items == 0) break;
     launch_query_merge(nq, N, p.kmax, true, r > 0, views(w), st);
@@ -677,7 +679,7 @@ PassCap planned_cap(const leafi_index *ix, int64_t nq, const SearchPlan &p, int 
   const int kp = bf16 ? p.kprime : default_kprime(p.kmax, false);
   // one first-leaf round per query is sized with its one-leaf tiles
   const bool one = bf16 && r == 0 && p.schedule[0] == 1;
-  const PassShape shape = pass_shape(ix, bf16, kp, round_items_est(ix, nq, p.schedule[r]), one);
+  const PassShape shape = pass_shape(ix, bf16, kp, round_items_est(ix, nq, r, p.schedule[r]), one);
   const int mq = shape.mq, chunk = shape.chunk;
   auto bytes = [&](int64_t items, int64_t tiles) {
     return static_cast<double>(items) * (p.kmax * 12.0 + 32.0) + static_cast<double>(tiles) * mq * kp * 8.0;
@@ -757,7 +759,7 @@ void prepare_planned(leafi_index *ix, int64_t nq, const SearchPlan &p, bool use_
       const PassCap c = planned_cap(ix, nq, p, r, bf);
       items = std::max(items, c.items);
       const int kp = bf ? p.kprime : kprime_fb;
-      const int mq = pass_shape(ix, bf, kp, round_items_est(ix, nq, p.schedule[r]), bf && r == 0 && p.schedule[0] == 1).mq;
+      const int mq = pass_shape(ix, bf, kp, round_items_est(ix, nq, r, p.schedule[r]), bf && r == 0 && p.schedule[0] == 1).mq;
       cand = std::max(cand, static_cast<size_t>(std::max<int64_t>(c.tiles, 1)) * mq * kp);
     }
   }
@@ -803,7 +805,7 @@ void enqueue_planned(leafi_index *ix, const float *raw, int64_t nq, const int32_
     ro.may_read = false;
     ro.first_leaf = first_leaf;
     ro.one_leaf = r == 0 && p.schedule[0] == 1;
-    ro.est = round_items_est(ix, nq, p.schedule[r]);
+    ro.est = round_items_est(ix, nq, r, p.schedule[r]);
     ro.use_tau = true;
     ro.kp_query = p.kp_query;
     ro.row_bytes = scan_row_bytes(ix, true);

@@ -74,7 +74,7 @@ struct ItemsEst {
   int64_t items = -1;
   bool all_pairs = false;
 };
-ItemsEst round_items_est(const leafi_index *ix, int64_t nq, int want);
+ItemsEst round_items_est(const leafi_index *ix, int64_t nq, int r, int want);
 
 // Queries per scan tile, list capacity and rows per tile of a pass (one_leaf:
 // see RoundOpts).

@@ -172,7 +172,7 @@ void leafi_server::engine_round(int n_new, int &n_active) {
   ro.may_read = !device_rounds;
   ro.use_tau = true;
   ro.kp_query = true;
-  ro.est = round_items_est(ix, slots, 0);
+  ro.est = round_items_est(ix, slots, 1, 0);
   if (scan_round(ix, slots, bf16, kprime, kmax, st, nullptr, bound, &ro) != 0)
     launch_query_merge(slots, N, kmax, true, false, views(w), st);
   if (device_rounds) {
@@ -364,7 +364,7 @@ int leafi_server_create(leafi_index *ix, const leafi_server_opts *o, leafi_serve
       const int64_t bnd = sv->round_bound();
       const bool bf = o->scan == LEAFI_SCAN_BF16;
       sv->device_rounds =
-          round_bytes_bound(ix, slots, bnd, bf, sv->kprime, o->k_max, round_items_est(ix, slots, 0)) <= kPlannedLimit &&
+          round_bytes_bound(ix, slots, bnd, bf, sv->kprime, o->k_max, round_items_est(ix, slots, 1, 0)) <= kPlannedLimit &&
           round_bytes_bound(ix, slots, bnd, false, default_kprime(o->k_max, false), o->k_max, ItemsEst()) <=
               kPlannedLimit;
     }
