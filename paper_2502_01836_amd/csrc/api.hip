@@ -342,11 +342,16 @@ int pick_chunk(const leafi_index *ix, int kprime, int pref) {
 // queries 3.22 -> 2.61 ms; 2.5M x 96 ragged, 4,096 queries 8.62 -> 4.86 ms
 // (fewer tiles, each starting with a tighter shared bound); 20k x 256, 100
 // queries 116 -> 108 us and one query at 1M 169 -> 166 (256 rows); 1M x 256,
-// 1,000 queries 354 and 356.  An all-pairs pass, whose
-// lists fill once per tile however long it is, takes 4,096 rows (500 queries
-// x 128 leaves 1,618 -> 1,465 us), whatever shape the caller's searches use.  A
-// round of one leaf per query keeps 16 queries per tile (few share a leaf).
+// 1,000 queries 354 and 356.  A round of one leaf per query keeps 16 queries per
+// tile (few share a leaf).  An all-pairs pass, whatever shape the caller's
+// searches use, has every tile's lists filled from the start, once per tile
+// however long it is: its tiles grow up to 4,096 rows, from two per CU on, and
+// stay at 32 queries, three work-groups per CU.  Node-wise 1-NN with 2,048 tiles
+// of 48 queries, with this, and at 1,024 x 32: 100,000 series of 96, 500 queries,
+// 32 leaves 373, 297 and 310 us, 128 leaves 469, 394 and 394; 1M of 256, 128
+// leaves, 50 queries 498, 364 and 365, 500 queries 1,171, 1,068 and 1,265.
 constexpr int kShapeTiles = 2048;  // tiles a pass should have before its tiles grow longer
+constexpr int kAllPairsTiles = 512;
 PassShape pass_shape(const leafi_index *ix, bool bf16, int kprime, const ItemsEst &est, bool one_leaf) {
   PassShape s;
   int chunk = bf16 ? kChunkRows : kFp32ChunkRows, mq = 32;
@@ -354,11 +359,12 @@ PassShape pass_shape(const leafi_index *ix, bool bf16, int kprime, const ItemsEs
     chunk = ix->tune_chunk;
     mq = one_leaf ? 16 : ix->tune_mq;
   } else if (bf16 && est.items >= 0) {
-    mq = one_leaf ? 16 : 48;
+    mq = one_leaf ? 16 : est.all_pairs ? 32 : 48;
     chunk = 2 * kRowAlign;
+    const int64_t tiles = est.all_pairs ? kAllPairsTiles : kShapeTiles;
     const int64_t groups = std::max(ceil_div(est.items, mq), std::min<int64_t>(est.items, ix->N));
     for (int c = chunk; c <= (est.all_pairs ? 4096 : 2048); c *= 2)
-      if (groups * ix->total_chunks_for(c) >= static_cast<int64_t>(kShapeTiles) * ix->N) chunk = c;
+      if (groups * ix->total_chunks_for(c) >= tiles * ix->N) chunk = c;
   } else if (bf16 && one_leaf) {
     mq = 16;
   } else if (!bf16 && est.all_pairs) {
