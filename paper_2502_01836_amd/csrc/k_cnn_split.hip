@@ -43,6 +43,7 @@ struct ConvArgs {
   const float *offsets;
   float *dfo;
   int mt, ng;            // 16-channel tiles, position groups
+  int bufs;              // sets of planes: 2, or 1 where a work-group takes one query
 };
 
 // First-layer activation of a channel (its three taps, then its bias) at
@@ -76,8 +77,8 @@ __device__ __forceinline__ float conv_plain(const float *__restrict__ wf, int m,
 
 __host__ __device__ inline int conv_rows(int m) { return (m + 15) / 16 * 16 + 16; }  // positions per plane
 __host__ __device__ inline int conv_xrow(int m) { return (m + 2 + 3) / 4 * 4; }
-size_t conv_lds(int m, int C, int ks, int waves) {
-  return 2 * 3 * static_cast<size_t>(conv_rows(m)) * 32 * (ks / 3) * 2 + 3 * conv_xrow(m) * 4 + C * 16 +
+size_t conv_lds(int m, int C, int ks, int waves, int bufs) {
+  return 3 * bufs * static_cast<size_t>(conv_rows(m)) * 32 * (ks / 3) * 2 + 3 * conv_xrow(m) * 4 + C * 16 +
          2 * waves * 4 + 32;
 }
 
@@ -92,8 +93,8 @@ __global__ void __launch_bounds__(KS <= 9 ? 768 : 512, KS <= 9 ? 3 : 2) k_cnn_in
   if (static_cast<int64_t>(blockIdx.y) >= n) return;  // uniform
   const int m = a.m, C = a.C, T = blockDim.x;
   const int rows8 = conv_rows(m) * 8, plane = rows8 * (CP / 8), xrow = conv_xrow(m);
-  uint16_t *planes = reinterpret_cast<uint16_t *>(smem);             // [2][3][CP / 8][positions][8]
-  float *xs = reinterpret_cast<float *>(planes + 6 * plane);         // [3][xrow] padded queries
+  uint16_t *planes = reinterpret_cast<uint16_t *>(smem);             // [bufs][3][CP / 8][positions][8]
+  float *xs = reinterpret_cast<float *>(planes + 3 * a.bufs * plane);  // [3][xrow] padded queries
   float4 *w1s = reinterpret_cast<float4 *>(xs + 3 * xrow);           // [C] first-layer taps and bias
   float *red = reinterpret_cast<float *>(w1s + C);                   // [2][waves]
   int *bad = reinterpret_cast<int *>(red + 2 * (T / kWave));         // [4] queries, [1] weights
@@ -105,7 +106,8 @@ __global__ void __launch_bounds__(KS <= 9 ? 768 : 512, KS <= 9 ? 3 : 2) k_cnn_in
   const float *W2 = wf + 4 * C, *b2p = W2 + 3 * C * C, *w3p = b2p + C;
   // the planes' zero positions and channels stay zero; everything is cleared
   // once, so positions past m + 1 hold finite values too
-  for (int e = tid; e < 6 * plane / 8; e += T) reinterpret_cast<uint4 *>(planes)[e] = make_uint4(0u, 0u, 0u, 0u);
+  for (int e = tid; e < 3 * a.bufs * plane / 8; e += T)
+    reinterpret_cast<uint4 *>(planes)[e] = make_uint4(0u, 0u, 0u, 0u);
   if (tid < 5) bad[tid] = 0;
   for (int e = tid; e < 3 * xrow; e += T) xs[e] = 0.0f;
   // W2's parts: lane holds output channel 16 tile + col, step (tap t, block
@@ -229,7 +231,7 @@ __global__ void __launch_bounds__(KS <= 9 ? 768 : 512, KS <= 9 ? 3 : 2) k_cnn_in
 
 template <int KS>
 void conv_launch(const ConvArgs &a, dim3 grid, int waves, hipStream_t st) {
-  const size_t lds = conv_lds(a.m, a.C, KS, waves);
+  const size_t lds = conv_lds(a.m, a.C, KS, waves, a.bufs);
   auto kern = k_cnn_infer_split<KS>;
   allow_lds(reinterpret_cast<const void *>(kern), lds);
   hipLaunchKernelGGL(kern, grid, dim3(kWave * waves), lds, st, a);
@@ -241,20 +243,27 @@ void conv_launch(const ConvArgs &a, dim3 grid, int waves, hipStream_t st) {
 // Up to 128 channels and 256 positions whose planes fit in LDS; false, with
 // nothing launched, otherwise.  Wavefronts: one per 16 output channels, times
 // as many position groups as 12 wavefronts (8 above 96 channels, whose parts
-// take twice the registers) and the positions allow.  Work-groups share a
-// filter's queries like the MLP inference's, the read of the weights standing
-// for two queries.
+// take twice the registers) and the positions allow; with more filters than CUs
+// and up to 64 channels half as many, so that two work-groups share a CU where
+// their planes fit, and one's waits are the other's work (300 filters of 64
+// channels x 64 positions, one query 45 -> 19 us, 100 queries 431 -> 296; not
+// for 96 channels: 626 -> 642).  That follows from the filters alone: the
+// position groups are the order of a sum.  Work-groups share a filter's queries
+// like the MLP inference's, the read of the weights standing for two queries;
+// those with one query each have one set of planes, which lets more of them
+// share a CU (1,024 filters of 32 channels x 96 positions, one query 42 -> 34 us).
 bool launch_cnn_infer_split(const float *w, int F, int m, int C, const float *x, int64_t nq, float *out,
                             const int64_t *plist, const int32_t *pcnt, int64_t stride, int N, const int32_t *pair,
                             const float *offsets, float *dfo, hipStream_t st) {
   const int ks = 3 * ((C + 31) / 32);
   if (C > 128 || m > 256) return false;
-  ConvArgs a{w, F, m, C, x, nq, out, plist, pcnt, stride, N, pair, offsets, dfo, 0, 0};
+  ConvArgs a{w, F, m, C, x, nq, out, plist, pcnt, stride, N, pair, offsets, dfo, 0, 0, 2};
   a.mt = (C + 15) / 16;
-  const int most = ks <= 9 ? kConvMaxWaves : 8;
+  int most = ks <= 9 ? kConvMaxWaves : 8;
+  if (F > device_cus() && ks <= 6 && conv_lds(m, C, ks, most, 2) <= 80 * 1024) most /= 2;
   a.ng = std::max(1, std::min(most / a.mt, (m + 15) / 16));
   const int waves = a.mt * a.ng;
-  if (conv_lds(m, C, ks, waves) > 160 * 1024) return false;
+  if (conv_lds(m, C, ks, waves, 2) > 160 * 1024) return false;
   const int64_t n = plist ? ceil_div(stride, 8) : nq;
   int share = 1;
   int64_t best = 0;
@@ -265,6 +274,7 @@ bool launch_cnn_infer_split(const float *w, int F, int m, int C, const float *x,
       share = c;
     }
   }
+  if (!plist && nq <= share) a.bufs = 1;
   const dim3 grid(F, share);
   switch (ks) {
     case 3: conv_launch<3>(a, grid, waves, st); break;

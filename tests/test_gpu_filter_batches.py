@@ -89,3 +89,14 @@ def test_listed_pairs_have_the_dense_predictions(arch, n_leaves, nq):
         _, _, st = ix.search(q, k=1, target=t, k_max=1, schedule=(1, 0), with_stats=True)
         assert st["filter_evals"] > nq
         assert st["leaves_filter_pruned"] == share * st["filter_evals"]
+
+
+@pytest.mark.parametrize("F,m,C", [(3, 96, 32), (256, 64, 64), (257, 64, 64), (300, 128, 32), (257, 96, 96), (1024, 33, 4)])
+def test_cnn_rows_in_calls_of_any_size(F, m, C):
+    pkg = _pkg()
+    g = np.random.default_rng(F + m)
+    w = torch.from_numpy(g.uniform(-0.5, 0.5, (F, 3 * C * C + 6 * C + 1)).astype(np.float32)).cuda()
+    x = torch.from_numpy(_rows(70, m, C)).cuda()
+    want = pkg.cnn_infer(w, m, C, x)
+    for a, b in ((0, 1), (3, 5), (20, 37), (69, 70)):
+        assert torch.equal(pkg.cnn_infer(w, m, C, x[a:b].clone()), want[a:b]), (a, b)
