@@ -91,7 +91,7 @@ def test_listed_pairs_have_the_dense_predictions(arch, n_leaves, nq):
         assert st["leaves_filter_pruned"] == share * st["filter_evals"]
 
 
-@pytest.mark.parametrize("F,m,C", [(3, 96, 32), (256, 64, 64), (257, 64, 64), (300, 128, 32), (257, 96, 96), (1024, 33, 4)])
+@pytest.mark.parametrize("F,m,C", [(3, 96, 32), (256, 64, 64), (257, 64, 64), (300, 128, 32), (257, 96, 96), (1024, 36, 4)])
 def test_cnn_rows_in_calls_of_any_size(F, m, C):
     pkg = _pkg()
     g = np.random.default_rng(F + m)
