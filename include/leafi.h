@@ -570,7 +570,8 @@ int leafi_cnn_infer(const float *weights_dev, int32_t n_filters, int32_t m, int3
 /* One plain SGD step per CNN filter on its own batch (as leafi_mlp_sgd_step):
  * x_dev [n_filters, batch, m], y_dev [n_filters, batch]; loss_dev
  * [n_filters] receives the batch loss before the step.  Returns once the
- * step is done. */
+ * step is done; on a stream that is being captured, a shape that the
+ * matrix-core step takes is recorded instead. */
 int leafi_cnn_sgd_step(float *weights_dev, int32_t n_filters, int32_t m, int32_t channels, const float *x_dev,
                        const float *y_dev, int32_t batch, float lr, float *loss_dev, void *stream);
 

@@ -2110,11 +2110,15 @@ int leafi_cnn_sgd_step(float *w, int32_t F, int32_t m, int32_t C, const float *x
     LEAFI_CHECK_ARG(F <= 65535, "too many filters in one call");
     hipStream_t st = as_stream(stream);
     DevBuf<float> gbuf;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (!launch_cnn_sgd_step_mfma(w, F, m, C, x, y, batch, lr, loss, st)) {
       gbuf.alloc(static_cast<size_t>(F) * cnn_param_count(C));
       launch_cnn_sgd_step(w, F, m, C, x, y, batch, lr, loss, gbuf.get(), st);
+    } else {
+      HIP_OK(hipStreamIsCapturing(st, &cs));  // one kernel and no memory: it may be captured
     }
-    HIP_OK(hipStreamSynchronize(st));  // the step is done on return (and gbuf is freed)
+    // the step is done on return (and gbuf is freed)
+    if (cs == hipStreamCaptureStatusNone) HIP_OK(hipStreamSynchronize(st));
   });
 }
 

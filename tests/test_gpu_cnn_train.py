@@ -80,6 +80,25 @@ def test_cnn_step_is_done_on_return(F, m, C, B):
             assert stream.query()
 
 
+def test_cnn_step_in_a_captured_graph():
+    """The matrix-core step may be captured; each replay is one more step."""
+    pkg = _pkg()
+    F, m, C, B = 5, 48, 16, 8
+    w = torch.from_numpy(W.cnn_weights(F, C, seed=3)).cuda()
+    x, y = torch.randn((F, B, m), device="cuda"), torch.rand((F, B), device="cuda")
+    want = w.clone()
+    pkg.cnn_sgd_step(want, m, C, x, y, 0.02)
+    graph, held = torch.cuda.CUDAGraph(), w.clone()
+    with torch.cuda.graph(graph):
+        pkg.cnn_sgd_step(held, m, C, x, y, 0.02)
+    assert torch.equal(held, w)
+    for _ in range(4):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(held, want)
+        pkg.cnn_sgd_step(want, m, C, x, y, 0.02)
+
+
 def test_cnn_training_allocates_no_gradients_it_does_not_use():
     """Training on the matrix cores keeps the weights and the best ones, and no
     third array of their size."""
