@@ -243,15 +243,19 @@ void conv_launch(const ConvArgs &a, dim3 grid, int waves, hipStream_t st) {
 // Up to 128 channels and 256 positions whose planes fit in LDS; false, with
 // nothing launched, otherwise.  Wavefronts: one per 16 output channels, times
 // as many position groups as 12 wavefronts (8 above 96 channels, whose parts
-// take twice the registers) and the positions allow; with more filters than CUs
-// and up to 64 channels half as many, so that two work-groups share a CU where
-// their planes fit, and one's waits are the other's work (300 filters of 64
-// channels x 64 positions, one query 45 -> 19 us, 100 queries 431 -> 296; not
-// for 96 channels: 626 -> 642).  That follows from the filters alone: the
-// position groups are the order of a sum.  Work-groups share a filter's queries
-// like the MLP inference's, the read of the weights standing for two queries;
-// those with one query each have one set of planes, which lets more of them
-// share a CU (1,024 filters of 32 channels x 96 positions, one query 42 -> 34 us).
+// take twice the registers) and the positions allow.  With more filters than CUs
+// and up to 64 channels the 12 are dealt to as many work-groups as there are
+// filters per CU and their planes fit its LDS: a work-group with a CU to itself
+// leaves it idle while it waits for the weights and at the barriers.  One query
+// and 100, plain kernel, 12 wavefronts, this: 300 filters of 64 channels x 64
+// positions 27, 45, 19 us and 1,326, 431, 289; 1,024 of 20 x 40 9.7, 19.6, 10.1 and
+// 475, 506, 232; 8,192 of 32 x 96 121, 387, 96 and (20 queries) 1,495, 1,336, 680.
+// Not for 96 channels (300 x 48 positions, 100 queries: 626 and 642).  All of
+// it follows from the filters alone: the position groups are the order of a sum.
+//
+// Work-groups share a filter's queries like the MLP inference's, the read of the
+// weights standing for two queries; those with one query each have one set of
+// planes, which lets more of them share a CU.
 bool launch_cnn_infer_split(const float *w, int F, int m, int C, const float *x, int64_t nq, float *out,
                             const int64_t *plist, const int32_t *pcnt, int64_t stride, int N, const int32_t *pair,
                             const float *offsets, float *dfo, hipStream_t st) {
@@ -260,7 +264,11 @@ bool launch_cnn_infer_split(const float *w, int F, int m, int C, const float *x,
   ConvArgs a{w, F, m, C, x, nq, out, plist, pcnt, stride, N, pair, offsets, dfo, 0, 0, 2};
   a.mt = (C + 15) / 16;
   int most = ks <= 9 ? kConvMaxWaves : 8;
-  if (F > device_cus() && ks <= 6 && conv_lds(m, C, ks, most, 2) <= 80 * 1024) most /= 2;
+  if (ks <= 6) {
+    const int64_t fit = 160 * 1024 / conv_lds(m, C, ks, most, 2);
+    const int64_t per_cu = std::min({ceil_div(F, device_cus()), fit, static_cast<int64_t>(most / a.mt)});
+    most /= static_cast<int>(std::max<int64_t>(1, per_cu));
+  }
   a.ng = std::max(1, std::min(most / a.mt, (m + 15) / 16));
   const int waves = a.mt * a.ng;
   if (conv_lds(m, C, ks, waves, 2) > 160 * 1024) return false;

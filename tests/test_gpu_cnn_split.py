@@ -100,3 +100,17 @@ def test_finite_operands_whose_products_overflow():
     x = np.abs(np.random.default_rng(1).standard_normal((7, m))).astype(np.float32) + np.float32(0.01)
     got = pkg.cnn_infer(torch.from_numpy(w).cuda(), m, C, torch.from_numpy(x).cuda()).cpu().numpy()
     assert np.all(np.isposinf(got))
+
+
+@pytest.mark.parametrize("F,m,C", [(257, 64, 64), (520, 96, 32), (600, 128, 32), (1030, 40, 20), (1030, 96, 16),
+                                   (2050, 256, 8), (4100, 16, 4)])
+@pytest.mark.parametrize("nq", [1, 5])
+def test_split_cnn_inference_with_more_filters_than_cus(F, m, C, nq):
+    """Work-groups of fewer wavefronts, with one and two sets of planes."""
+    pkg = _pkg()
+    w = W.cnn_weights(F, C, seed=F + C, out_bias=0.5)
+    x = np.random.default_rng(m).standard_normal((nq, m)).astype(np.float32)
+    got = pkg.cnn_infer(torch.from_numpy(w).cuda(), m, C, torch.from_numpy(x).cuda()).cpu().numpy()
+    for f in (0, 1, F // 2, F - 1):
+        want, mag = _forward(w[f], x, C)
+        assert np.all(np.abs(got[:, f] - want) <= (4 * C + m + 11) * 2.0 ** -24 * mag)
