@@ -310,9 +310,10 @@ void launch_items_to_leaf_knn(int64_t n_items, int N, int k, int kmax, const int
 // Compute units of the current device.
 int device_cus();
 
-// MLP inference on bf16 parts of the FP32 operands (k_mlp_split.hip), for m
-// and h up to 256: dense into out [nq, F] (plist null), or the listed pairs
-// as launch_mlp_infer_pairs.  False, with nothing launched, for other shapes.
+// MLP inference on bf16 parts of the FP32 operands (k_mlp_split.hip), for at
+// least one filter per CU, m and h up to 256: dense into out [nq, F] (plist
+// null), or the listed pairs as launch_mlp_infer_pairs.  False, with nothing
+// launched, for fewer filters and other shapes; never by the rows of a call.
 bool launch_mlp_infer_split(const float *w, int F, int m, int h, const float *x, int64_t nq, float *out,
                             const int64_t *plist, const int32_t *pcnt, int64_t stride, int N, const int32_t *pair,
                             const float *offsets, float *dfo, bool small_batches, hipStream_t st);
